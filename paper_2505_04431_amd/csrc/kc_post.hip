@@ -62,32 +62,56 @@ __global__ void __launch_bounds__(kTB) k_keep_count(const uint32_t* __restrict__
   if (threadIdx.x == 0) tsum[blockIdx.x] = s;
 }
 
-// Step 2 (one block): exclusive scan of the tile sums; tsum[nt] = total.
-__global__ void __launch_bounds__(1024) k_scan_tiles(unsigned long long* __restrict__ tsum,
-                                                     uint64_t nt) {
-  __shared__ unsigned long long part[1024];
-  const uint64_t per = (nt + 1023) / 1024;
-  const uint64_t b = threadIdx.x * per, e = b + per < nt ? b + per : nt;
-  unsigned long long s = 0;
-  for (uint64_t i = b; i < e; ++i) s += tsum[i];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long run = 0;
-    for (int t = 0; t < 1024; ++t) {
-      const unsigned long long x = part[t];
-      part[t] = run;
-      run += x;
+// Step 2 (one block): exclusive scan of the tile sums; tsum[nt] = total. Rows
+// of kScanTB * 8 sums, eight consecutive ones a thread, loaded while the row
+// before is still being scanned (a chain of latencies, not of bytes: 9,500 sums
+// 23.3 us with one thread adding up 1,024 partial sums, 21,800 sums 18.9 us so).
+constexpr int kScanTB = 1024, kScanPer = 8;
+__global__ void __launch_bounds__(kScanTB) k_scan_tiles(unsigned long long* __restrict__ tsum,
+                                                        uint64_t nt) {
+  __shared__ unsigned long long wtot[2][kScanTB / 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  unsigned long long carry = 0;
+  unsigned long long v[kScanPer];
+  const auto load = [&](uint64_t row) {
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      const uint64_t i = row + (uint64_t)threadIdx.x * kScanPer + q;
+      v[q] = i < nt ? tsum[i] : 0ull;
     }
-    tsum[nt] = run;
+  };
+  load(0);
+  int buf = 0;
+  for (uint64_t row = 0; row < nt; row += (uint64_t)kScanTB * kScanPer, buf ^= 1) {
+    unsigned long long now[kScanPer], s = 0;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      now[q] = s;
+      s += v[q];
+    }
+    load(row + (uint64_t)kScanTB * kScanPer);
+    unsigned long long x = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const unsigned long long y = __shfl_up(x, (unsigned)off, 64);
+      if (lane >= off) x += y;
+    }
+    if (lane == 63) wtot[buf][w] = x;
+    __syncthreads();
+    unsigned long long before = carry, all = 0;
+#pragma unroll
+    for (int t = 0; t < kScanTB / 64; ++t) {
+      if (t < w) before += wtot[buf][t];
+      all += wtot[buf][t];
+    }
+    carry += all;
+#pragma unroll
+    for (int q = 0; q < kScanPer; ++q) {
+      const uint64_t i = row + (uint64_t)threadIdx.x * kScanPer + q;
+      if (i < nt) tsum[i] = before + (x - s) + now[q];
+    }
   }
-  __syncthreads();
-  unsigned long long run = part[threadIdx.x];
-  for (uint64_t i = b; i < e; ++i) {
-    const unsigned long long x = tsum[i];
-    tsum[i] = run;
-    run += x;
-  }
+  if (threadIdx.x == 0) tsum[nt] = carry;
 }
 
 // Step 3: each tile writes its kept pairs in order from its offset.
@@ -210,7 +234,7 @@ int kc_filter_min_count(const uint64_t* keys, const uint32_t* counts, uint64_t n
     unsigned long long* tsum = (unsigned long long*)d;
     hipLaunchKernelGGL(k_keep_count, dim3((unsigned)nt), dim3(kTB), 0, st, counts, n, min_count,
                        tsum);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, tsum, nt);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanTB), 0, st, tsum, nt);
     hipLaunchKernelGGL(k_keep_write, dim3((unsigned)nt), dim3(kTB), 0, st, keys, counts, n, words,
                        min_count, tsum, out_keys, out_counts);
     chk(hipGetLastError(), "filter launch");
@@ -274,26 +298,36 @@ __device__ __forceinline__ void key_put(uint64_t* keys, uint64_t i,
   }
 }
 
-constexpr int kMergeItems = 8;
-
-constexpr uint64_t kMergeTile = (uint64_t)kTB * kMergeItems;  // merged positions per block
+// Merged positions per thread and per block (words of a key W): a block's keys
+// and counts are staged in LDS, 21 KiB for one-word keys, so seven 256-thread
+// blocks share a CU; wider keys take fewer positions for the same LDS. The
+// number is odd so that the threads' positions spread over all LDS banks (8 a
+// thread, keys 64 bytes apart: the second pass below 327 instead of 154 us).
+template <int W> constexpr int kMergeItems = W == 1 ? 7 : W == 2 ? 5 : 3;
+template <int W> constexpr int kMergeTileOf = kTB * kMergeItems<W>;
 
 // Number of a's among the first d merged positions (a first on ties), by
 // binary search over i in [lo, hi]: the largest i with a[i-1] <= b[d-i].
-template <int W>
-__device__ __forceinline__ uint64_t merge_split(const uint64_t* __restrict__ ak, uint64_t na,
-                                                const uint64_t* __restrict__ bk, uint64_t nb,
-                                                uint64_t d, uint64_t lo, uint64_t hi) {
+template <int W, typename I>
+__device__ __forceinline__ I merge_split(const uint64_t* ak, const uint64_t* bk, I nb, I d, I lo,
+                                         I hi) {
   while (lo < hi) {
-    const uint64_t i = (lo + hi + 1) >> 1;  // candidate: take i items of a
+    const I i = (lo + hi + 1) >> 1;  // candidate: take i items of a
     if (d - i >= nb || !(key_at<W>(bk, d - i) < key_at<W>(ak, i - 1))) lo = i;
     else hi = i - 1;
   }
   return lo;
 }
 
-// Split of every block boundary (part[q] for diagonal q * kMergeTile, q =
-// 0..nblocks), so that each thread of k_merge searches only its block's window.
+// Split of every block boundary: part[2q], part[2q + 1] are the a's and b's
+// before diagonal q * tile, q = 0..nblocks. A key that both inputs hold is
+// never cut: if a's copy is the last one before the diagonal, b's is taken
+// with it (a block has up to tile + 1 positions), so every output pair is
+// made by one block. The search is a chain of dependent loads (25 halvings of
+// 20M pairs: 32 us; by 4 or 16 lanes a search no less, 35 and 56 us: more
+// pages are touched), so it starts where the split lies if both inputs are
+// spread alike over the keys, as two results of one genome are, and widens
+// from there (18.7 us).
 template <int W>
 __global__ void __launch_bounds__(kTB) k_merge_part(const uint64_t* __restrict__ ak, uint64_t na,
                                                     const uint64_t* __restrict__ bk, uint64_t nb,
@@ -301,106 +335,198 @@ __global__ void __launch_bounds__(kTB) k_merge_part(const uint64_t* __restrict__
                                                     unsigned long long* __restrict__ part) {
   const uint64_t q = (uint64_t)blockIdx.x * kTB + threadIdx.x;
   if (q > nblocks) return;
-  const uint64_t total = na + nb;
-  const uint64_t d = q * kMergeTile < total ? q * kMergeTile : total;
-  part[q] = merge_split<W>(ak, na, bk, nb, d, d > nb ? d - nb : 0, d < na ? d : na);
-}
-
-// Merge path: thread t writes merged positions [t*items, t*items + items) of
-// the ordered union of a and b (ties: a first). Its start in a is the
-// largest i with i + j = d and a[i-1] <= b[j] ... found by binary search.
-template <int W>
-__global__ void __launch_bounds__(kTB) k_merge(const uint64_t* __restrict__ ak,
-                                               const uint32_t* __restrict__ ac, uint64_t na,
-                                               const uint64_t* __restrict__ bk,
-                                               const uint32_t* __restrict__ bc, uint64_t nb,
-                                               uint64_t* __restrict__ mk,
-                                               uint32_t* __restrict__ mc,
-                                               const unsigned long long* __restrict__ part) {
-  const uint64_t total = na + nb;
-  const uint64_t d = ((uint64_t)blockIdx.x * kTB + threadIdx.x) * kMergeItems;
-  if (d >= total) return;
-  // i in [max(0, d - nb), min(d, na)] and within this block's split range
-  const uint64_t p0 = part[blockIdx.x], p1 = part[blockIdx.x + 1];
+  const uint64_t total = na + nb, at = q * kMergeTileOf<W>;
+  const uint64_t d = at < total ? at : total;
   uint64_t lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
-  lo = lo > p0 ? lo : p0;
-  hi = hi < p1 ? hi : p1;
-  const uint64_t i0 = merge_split<W>(ak, na, bk, nb, d, lo, hi);
-  uint64_t i = i0, j = d - i0;
-  for (int t = 0; t < kMergeItems && d + t < total; ++t) {
-    bool take_a;
-    if (i >= na) take_a = false;
-    else if (j >= nb) take_a = true;
-    else take_a = !(key_at<W>(bk, j) < key_at<W>(ak, i));
-    if (take_a) {
-      key_put<W>(mk, d + t, key_at<W>(ak, i));
-      mc[d + t] = ac[i];
-      ++i;
-    } else {
-      key_put<W>(mk, d + t, key_at<W>(bk, j));
-      mc[d + t] = bc[j];
-      ++j;
+  // held(i): i a's lie before the diagonal (true up to the split, and at lo)
+  const auto held = [&](uint64_t i) {
+    return i == 0 || d - i >= nb || !(key_at<W>(bk, d - i) < key_at<W>(ak, i - 1));
+  };
+  uint64_t g = (uint64_t)((double)d * (double)na / (double)total);
+  g = g < lo ? lo : g > hi ? hi : g;
+  uint64_t w = kMergeTileOf<W>;
+  if (held(g)) {
+    lo = g;
+    for (; hi - lo > w; w *= 8) {
+      if (!held(lo + w)) {
+        hi = lo + w - 1;
+        break;
+      }
+      lo += w;
     }
+  } else {
+    hi = g - 1;  // g > lo: held(lo)
+    for (; hi - lo > w; w *= 8) {
+      if (held(hi - w)) {
+        lo = hi - w;
+        break;
+      }
+      hi -= w + 1;
+    }
+  }
+  const uint64_t i = merge_split<W, uint64_t>(ak, bk, nb, d, lo, hi);
+  uint64_t j = d - i;
+  if (i > 0 && j < nb && key_at<W>(ak, i - 1) == key_at<W>(bk, j)) ++j;
+  part[2 * q] = i;
+  part[2 * q + 1] = j;
+}
+
+// One block's part of the ordered union: its a's and b's are staged in LDS
+// (coalesced loads); each thread finds its diagonal there by binary search,
+// with a pair of equal keys kept whole as in k_merge_part, and walks its
+// kMergeItems positions once, an equal pair giving one output with the counts
+// added. WRITE = false: only the number of outputs (tsum[block]); WRITE: the
+// outputs, gathered in LDS by a block scan and written as one coalesced run
+// from tsum[block] (the exclusive scan of the first pass's numbers).
+// Reading the keys twice costs less than a merged copy of both inputs written
+// and read again: bound by HBM (W = 1: 8 bytes of each input pair in the first
+// pass, 12 read and 12 written in the second). 20M + 19M pairs of one-word keys,
+// 34M results: 84 and 154 us, 3.7 and 5.7 TB/s; the whole call 0.31 ms (a
+// merged copy by threads that read and wrote eight positions each on their
+// own, then two passes over it: 1.49 of 1.91 ms in the merge itself).
+template <int W, bool WRITE>
+__global__ void __launch_bounds__(kTB) k_merge(const uint64_t* __restrict__ ak,
+                                               const uint32_t* __restrict__ ac,
+                                               const uint64_t* __restrict__ bk,
+                                               const uint32_t* __restrict__ bc,
+                                               const unsigned long long* __restrict__ part,
+                                               unsigned long long* __restrict__ tsum,
+                                               uint64_t* __restrict__ out_keys,
+                                               uint32_t* __restrict__ out_counts,
+                                               unsigned int* __restrict__ overflow) {
+  constexpr int ITEMS = kMergeItems<W>, TILE = kMergeTileOf<W>;
+  typedef typename KeyOf<W>::type Key;
+  __shared__ uint64_t sk[W * (TILE + 1)];      // a's keys, then b's; then the outputs'
+  __shared__ uint32_t sc[WRITE ? TILE + 1 : 1];  // their counts
+  __shared__ uint32_t split[kTB + 1];          // per thread: a's and b's before it (16 bits each)
+  __shared__ uint32_t wsum[kTB / 64];
+  const uint64_t a0 = part[2 * blockIdx.x], b0 = part[2 * blockIdx.x + 1];
+  const uint32_t la = (uint32_t)(part[2 * blockIdx.x + 2] - a0);
+  const uint32_t lb = (uint32_t)(part[2 * blockIdx.x + 3] - b0);
+  const uint32_t n = la + lb;
+  // the block's key words, a's then b's, all loads in flight together (the
+  // last word of a tile of TILE + 1 positions by itself)
+  uint64_t v[ITEMS * W];
+  uint32_t vc[WRITE ? ITEMS : 1];
+  const uint64_t* const ka0 = ak + W * a0;
+  const uint64_t* const kb0 = bk + W * b0 - W * (uint64_t)la;
+#pragma unroll
+  for (int s = 0; s < ITEMS * W; ++s) {
+    const uint32_t t = (uint32_t)s * kTB + threadIdx.x;
+    if (t < W * n) v[s] = t < W * la ? ka0[t] : kb0[t];
+  }
+  if (WRITE) {
+#pragma unroll
+    for (int s = 0; s < ITEMS; ++s) {
+      const uint32_t t = (uint32_t)s * kTB + threadIdx.x;
+      if (t < n) vc[s] = t < la ? ac[a0 + t] : bc[b0 + (t - la)];
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < ITEMS * W; ++s) {
+    const uint32_t t = (uint32_t)s * kTB + threadIdx.x;
+    if (t < W * n) sk[t] = v[s];
+  }
+  if (n > TILE && threadIdx.x < W) {
+    const uint32_t t = W * TILE + threadIdx.x;
+    sk[t] = t < W * la ? ka0[t] : kb0[t];
+  }
+  if (WRITE) {
+#pragma unroll
+    for (int s = 0; s < ITEMS; ++s) {
+      const uint32_t t = (uint32_t)s * kTB + threadIdx.x;
+      if (t < n) sc[t] = vc[s];
+    }
+    if (n > TILE && threadIdx.x == 0) sc[TILE] = TILE < la ? ac[a0 + TILE] : bc[b0 + (TILE - la)];
+  }
+  __syncthreads();
+  const uint64_t* const sb = sk + W * la;
+  const uint32_t d = min(n, (uint32_t)threadIdx.x * ITEMS);
+  uint32_t i = merge_split<W, uint32_t>(sk, sb, lb, d, d > lb ? d - lb : 0u, min(d, la));
+  uint32_t j = d - i;
+  if (i > 0 && j < lb && key_at<W>(sk, i - 1) == key_at<W>(sb, j)) ++j;
+  split[threadIdx.x] = i << 16 | j;
+  if (threadIdx.x == 0) split[kTB] = la << 16 | lb;
+  __syncthreads();
+  // a tile of TILE + 1 positions leaves its last one to the last thread
+  const uint32_t next = split[threadIdx.x + 1], i1 = next >> 16, j1 = next & 0xFFFFu;
+  Key key[WRITE ? ITEMS + 1 : 1];
+  uint32_t cnt[WRITE ? ITEMS + 1 : 1];
+  uint32_t u = 0;
+  bool over = false;
+  Key ka{}, kb{};
+  if (i < i1) ka = key_at<W>(sk, i);
+  if (j < j1) kb = key_at<W>(sb, j);
+#pragma unroll
+  for (int s = 0; s < ITEMS + 1; ++s) {
+    const bool ha = i < i1, hb = j < j1;
+    if (!(ha || hb)) break;
+    const bool take_a = ha && (!hb || !(kb < ka)), take_b = hb && (!ha || !(ka < kb));
+    if (WRITE) {
+      key[s] = take_a ? ka : kb;
+      const unsigned long long c =
+          (unsigned long long)(take_a ? sc[i] : 0u) + (take_b ? sc[la + j] : 0u);
+      over |= c > 0xFFFFFFFFull;
+      cnt[s] = (uint32_t)c;
+    }
+    ++u;
+    if (take_a && ++i < i1) ka = key_at<W>(sk, i);
+    if (take_b && ++j < j1) kb = key_at<W>(sb, j);
+  }
+  // exclusive prefix of u over the block
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  uint32_t x = u;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const uint32_t y = __shfl_up(x, (unsigned)off, 64);
+    if (lane >= off) x += y;
+  }
+  if (lane == 63) wsum[w] = x;
+  __syncthreads();  // also: every thread has taken its keys and counts from LDS
+  uint32_t before = 0, all = 0;
+#pragma unroll
+  for (int v = 0; v < kTB / 64; ++v) {
+    if (v < w) before += wsum[v];
+    all += wsum[v];
+  }
+  if (!WRITE) {
+    if (threadIdx.x == 0) tsum[blockIdx.x] = all;
+    return;
+  }
+  const uint32_t at = before + x - u;
+#pragma unroll
+  for (int s = 0; s < ITEMS + 1; ++s) {
+    if (s >= (int)u) break;
+    key_put<W>(sk, at + s, key[s]);
+    sc[at + s] = cnt[s];
+  }
+  if (over) atomicOr(overflow, 1u);
+  __syncthreads();
+  const unsigned long long o = tsum[blockIdx.x];
+#pragma unroll
+  for (int s = 0; s <= ITEMS * W; ++s) {
+    const uint32_t t = (uint32_t)s * kTB + threadIdx.x;
+    if (t < W * all) out_keys[W * o + t] = sk[t];
+  }
+#pragma unroll
+  for (int s = 0; s <= ITEMS; ++s) {
+    const uint32_t t = (uint32_t)s * kTB + threadIdx.x;
+    if (t < all) out_counts[o + t] = sc[t];
   }
 }
 
-// Dedup of the merged sequence: a key present in both inputs sits at two
-// neighbouring positions (a's first); the first keeps the summed count.
 template <int W>
-__global__ void __launch_bounds__(kTB) k_dedup_count(const uint64_t* __restrict__ mk, uint64_t n,
-                                                     unsigned long long* __restrict__ tsum) {
-  __shared__ uint32_t s;
-  if (threadIdx.x == 0) s = 0;
-  __syncthreads();
-  const uint64_t base = (uint64_t)blockIdx.x * kTile;
-  uint32_t c = 0;
-  for (int j = 0; j < kPer; ++j) {
-    const uint64_t i = base + (uint64_t)j * kTB + threadIdx.x;
-    c += (i < n && (i == 0 || key_at<W>(mk, i) != key_at<W>(mk, i - 1))) ? 1u : 0u;
-  }
-  atomicAdd(&s, c);
-  __syncthreads();
-  if (threadIdx.x == 0) tsum[blockIdx.x] = s;
-}
-
-template <int W>
-__global__ void __launch_bounds__(kTB) k_dedup_write(const uint64_t* __restrict__ mk,
-                                                     const uint32_t* __restrict__ mc, uint64_t n,
-                                                     const unsigned long long* __restrict__ tsum,
-                                                     uint64_t* __restrict__ out_keys,
-                                                     uint32_t* __restrict__ out_counts,
-                                                     unsigned int* __restrict__ overflow) {
-  __shared__ uint32_t wsum[kTB / 64 + 1];
-  const uint64_t base = (uint64_t)blockIdx.x * kTile;
-  unsigned long long at = tsum[blockIdx.x];
-  for (int j = 0; j < kPer; ++j) {
-    const uint64_t i = base + (uint64_t)j * kTB + threadIdx.x;
-    bool keep = false;
-    typename KeyOf<W>::type key{};
-    if (i < n) {
-      key = key_at<W>(mk, i);
-      keep = i == 0 || key != key_at<W>(mk, i - 1);
-    }
-    const unsigned long long m = __ballot(keep);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) wsum[w] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t before = 0, row = 0;
-    for (int v = 0; v < kTB / 64; ++v) {
-      if (v < w) before += wsum[v];
-      row += wsum[v];
-    }
-    if (keep) {
-      unsigned long long c = mc[i];
-      if (i + 1 < n && key_at<W>(mk, i + 1) == key) c += mc[i + 1];
-      if (c > 0xFFFFFFFFull) atomicOr(overflow, 1u);
-      const unsigned long long o = at + before + __popcll(m & ((1ull << lane) - 1));
-      key_put<W>(out_keys, o, key);
-      out_counts[o] = (uint32_t)c;
-    }
-    at += row;
-    __syncthreads();
-  }
+void launch_merge(const uint64_t* ak, const uint32_t* ac, uint64_t na, const uint64_t* bk,
+                  const uint32_t* bc, uint64_t nb, uint64_t nblk, unsigned long long* part,
+                  unsigned long long* tsum, uint64_t* out_keys, uint32_t* out_counts,
+                  unsigned int* ovf, hipStream_t st) {
+  hipLaunchKernelGGL(k_merge_part<W>, dim3(grid_of(nblk + 1, kTB, ~0u)), dim3(kTB), 0,
+                     st, ak, na, bk, nb, nblk, part);
+  hipLaunchKernelGGL((k_merge<W, false>), dim3((unsigned)nblk), dim3(kTB), 0, st, ak, ac, bk, bc,
+                     part, tsum, out_keys, out_counts, ovf);
+  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanTB), 0, st, tsum, nblk);
+  hipLaunchKernelGGL((k_merge<W, true>), dim3((unsigned)nblk), dim3(kTB), 0, st, ak, ac, bk, bc,
+                     part, tsum, out_keys, out_counts, ovf);
 }
 
 }  // namespace
@@ -420,53 +546,29 @@ extern "C" int kc_merge_counts(const uint64_t* a_keys, const uint32_t* a_counts,
   if (n == 0) return KC_OK;
   const int words = k <= 32 ? 1 : (k <= 64 ? 2 : 4);
   const hipStream_t st = (hipStream_t)stream;
-  const uint64_t nt = (n + kTile - 1) / kTile;
+  const uint64_t tile = words == 4 ? kMergeTileOf<4> : words == 2 ? kMergeTileOf<2> : kMergeTileOf<1>;
+  const uint64_t nblk = (n + tile - 1) / tile;
+  if (nblk > 0x7fffffffull) return bad("too many pairs");
   void* d = nullptr;
   try {
-    // merged sequence, tile sums and the overflow flag in one allocation
-    const size_t kb = n * 8 * (size_t)words, cb = n * 4, tb = (nt + 1) * 8;
-    const uint64_t nblk = (n + kMergeTile - 1) / kMergeTile;
-    // layout: merged keys, counts, (pad to 8), tile sums, flag (16 bytes), splits
-    d = post_scratch(kb + cb + 8 + tb + 16 + (nblk + 1) * 8, st);
-    uint64_t* mk = (uint64_t*)d;
-    uint32_t* mc = (uint32_t*)((char*)d + kb);
-    unsigned long long* tsum = (unsigned long long*)((char*)d + kb + cb + (8 - (cb & 7)) % 8);
-    unsigned int* ovf = (unsigned int*)(tsum + nt + 1);
-    unsigned long long* part = (unsigned long long*)(ovf + 4);
+    // tile sums (and their total), splits, the overflow flag
+    d = post_scratch((nblk + 1 + 2 * (nblk + 1) + 1) * 8, st);
+    unsigned long long* tsum = (unsigned long long*)d;
+    unsigned long long* part = tsum + nblk + 1;
+    unsigned int* ovf = (unsigned int*)(part + 2 * (nblk + 1));
     hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, (unsigned long long*)ovf, (uint64_t)1);
-    const dim3 gm((unsigned)nblk), gt((unsigned)nt), gp((unsigned)((nblk + kTB) / kTB));
-    if (words == 4) {
-      hipLaunchKernelGGL(k_merge_part<4>, gp, dim3(kTB), 0, st, a_keys, na, b_keys, nb, nblk,
-                         part);
-      hipLaunchKernelGGL(k_merge<4>, gm, dim3(kTB), 0, st, a_keys, a_counts, na, b_keys, b_counts,
-                         nb, mk, mc, part);
-      hipLaunchKernelGGL(k_dedup_count<4>, gt, dim3(kTB), 0, st, mk, n, tsum);
-    } else if (words == 2) {
-      hipLaunchKernelGGL(k_merge_part<2>, gp, dim3(kTB), 0, st, a_keys, na, b_keys, nb, nblk,
-                         part);
-      hipLaunchKernelGGL(k_merge<2>, gm, dim3(kTB), 0, st, a_keys, a_counts, na, b_keys, b_counts,
-                         nb, mk, mc, part);
-      hipLaunchKernelGGL(k_dedup_count<2>, gt, dim3(kTB), 0, st, mk, n, tsum);
-    } else {
-      hipLaunchKernelGGL(k_merge_part<1>, gp, dim3(kTB), 0, st, a_keys, na, b_keys, nb, nblk,
-                         part);
-      hipLaunchKernelGGL(k_merge<1>, gm, dim3(kTB), 0, st, a_keys, a_counts, na, b_keys, b_counts,
-                         nb, mk, mc, part);
-      hipLaunchKernelGGL(k_dedup_count<1>, gt, dim3(kTB), 0, st, mk, n, tsum);
-    }
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(1024), 0, st, tsum, nt);
     if (words == 4)
-      hipLaunchKernelGGL(k_dedup_write<4>, gt, dim3(kTB), 0, st, mk, mc, n, tsum, out_keys,
-                         out_counts, ovf);
+      launch_merge<4>(a_keys, a_counts, na, b_keys, b_counts, nb, nblk, part, tsum, out_keys,
+                      out_counts, ovf, st);
     else if (words == 2)
-      hipLaunchKernelGGL(k_dedup_write<2>, gt, dim3(kTB), 0, st, mk, mc, n, tsum, out_keys,
-                         out_counts, ovf);
+      launch_merge<2>(a_keys, a_counts, na, b_keys, b_counts, nb, nblk, part, tsum, out_keys,
+                      out_counts, ovf, st);
     else
-      hipLaunchKernelGGL(k_dedup_write<1>, gt, dim3(kTB), 0, st, mk, mc, n, tsum, out_keys,
-                         out_counts, ovf);
+      launch_merge<1>(a_keys, a_counts, na, b_keys, b_counts, nb, nblk, part, tsum, out_keys,
+                      out_counts, ovf, st);
     chk(hipGetLastError(), "merge launch");
     uint64_t h[2] = {0, 0};
-    chk(hipMemcpyAsync(&h[0], tsum + nt, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+    chk(hipMemcpyAsync(&h[0], tsum + nblk, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
     chk(hipMemcpyAsync(&h[1], ovf, 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
     chk(hipStreamSynchronize(st), "hipStreamSynchronize");
     if ((uint32_t)h[1]) {
