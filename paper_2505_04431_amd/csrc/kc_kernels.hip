@@ -922,10 +922,12 @@ __global__ void k_clear_overflow(DevState* __restrict__ st) {
 // table: such leaves are the dense clusters that overflow the first table
 // (on 40,000,000 reads at k = 31 the overflowed leaves average 147,000
 // records, the others 4,600), and the first count would read part of them
-// before giving up.
+// before giving up. d_zero != nullptr (no one-wave kernel follows): the counts
+// of empty leaves are set to 0 there.
 __global__ void k_classify_leaves(const Leaf* __restrict__ leaves, DevState* __restrict__ st,
                                   uint64_t small_max, uint32_t* __restrict__ large,
-                                  uint64_t huge_min, uint32_t* __restrict__ huge) {
+                                  uint64_t huge_min, uint32_t* __restrict__ huge,
+                                  uint32_t* __restrict__ d_zero) {
   const unsigned long long n = st->n_leaves;
   const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
   const int lane = threadIdx.x & 63;
@@ -935,6 +937,7 @@ __global__ void k_classify_leaves(const Leaf* __restrict__ leaves, DevState* __r
     const uint64_t len = lf.end - lf.begin;
     const bool to_huge = huge && len > huge_min;
     const bool big = !to_huge && len > small_max;
+    if (d_zero && i < n && len == 0) d_zero[i] = 0;
     const unsigned long long m = __ballot(big);
     if (m) {
       const int leader = __ffsll((long long)m) - 1;
@@ -1413,6 +1416,13 @@ constexpr int kLeafGroupShift = 3;
 constexpr int kLeafOccTB = 512;
 constexpr int kLeafOccWaves = 6;
 
+// Up to this many leaves, all go to the block-wide kernel: a wave alone needs
+// 15 us or more for a leaf (a chain of LDS latencies) while most of the chip
+// is idle, and the block-wide kernel that follows as long again; five rounds
+// of 768 resident workgroups count as many leaves in less (100 kB of reads:
+// 119 us by one-wave workgroups, 13 us so).
+constexpr uint64_t kFewLeaves = 4096;
+
 // 64-bit keys: EMPTY (all ones) is never a canonical key for k <= 32, so a
 // slot is claimed by a 64-bit CAS of the key word itself; the count is then
 // added with an atomic add. FULL_FIRST: the first table is the full one (the
@@ -1464,8 +1474,11 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     uint64_t* dst = lf.buf ? bufA : bufB;
     // First try a table sized for half the records being distinct; if it
     // fills up, count the leaf again with a table large enough for all.
-    const uint32_t Cfull = leaf_slots<TB, CMAX>(n, cmax_rt);
-    uint32_t Cn = FULL_FIRST ? Cfull : leaf_slots<TB, CMAX>(n / 2, cmax_rt);
+    // With few leaves the chip is not full and a leaf's chain of latencies
+    // counts, not its work: one table then, with room to spare.
+    const bool few = list && count <= kFewLeaves;
+    const uint32_t Cfull = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
+    uint32_t Cn = FULL_FIRST || few ? Cfull : leaf_slots<TB, CMAX>(n / 2, cmax_rt);
     // pre-aggregated records: (count - 1) in bits [cshift, 64), the shard above
     const uint32_t cshift = MERGED ? lf.cshift : 0u;
     const uint64_t low = cshift ? (1ull << cshift) - 1 : ~0ull;
@@ -1487,6 +1500,11 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     __syncthreads();
     const uint32_t limit = Cn - (Cn >> 3);
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
+    // a half table is given up at the first probe chain as long as chains get
+    // near its limit, not only after a whole batch of records: in the full
+    // half table that a batch can leave, chains run to its whole length (256
+    // leaves of 312 records by one wave each: 119 us, capped 59 us)
+    const uint32_t max_probes = Cn < Cfull ? 64u : Cn;
     my_windows = 0;
     // records are loaded R per thread before inserting, so that the loads of a
     // batch are in flight together instead of one round trip per insert. The
@@ -1539,7 +1557,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
           if (todo) take(nx);
         } else {
           pos = (pos + 1) & cmask;
-          todo = ++probes < Cn;
+          todo = ++probes < max_probes;
           if (!todo) ovf_set(&s_ovf);  // table full: the leaf overflows
         }
       }
@@ -2060,16 +2078,6 @@ __global__ void __launch_bounds__(TB) k_leaf_radix64(int keybits, uint64_t* bufA
   }
 }
 
-// Empty leaves of the sort-based count (the others are all in the list).
-__global__ void k_empty_leaves(const Leaf* __restrict__ leaves, const DevState* __restrict__ st,
-                               uint32_t* __restrict__ d_out) {
-  const unsigned long long n = st->n_leaves;
-  const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
-  for (unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += stride)
-    if (leaves[i].end == leaves[i].begin) d_out[i] = 0;
-}
-
 // ---------------------------------------------------------------- concat + check
 
 template <typename K>
@@ -2585,7 +2593,8 @@ hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uin
                              uint32_t* d_out, uint32_t* large_list, uint32_t* ovf_list,
                              int slots_log2, hipStream_t s, int mode, bool refine, bool merged) {
   const bool wide = words == 2;
-  const uint64_t small_max = mode == 1 ? 0 : small_leaf_max(words);
+  const bool one_wave = mode != 1 && words != 4 && max_leaves > kFewLeaves;
+  const uint64_t small_max = one_wave ? small_leaf_max(words) : 0;
   // leaves of more than 8 first tables of records go straight to the second
   // count (where it runs: launch_leaf_second)
   const bool second = words == 1 && mode != 1 && slots_log2 < kRescueSlotsLog2 && ovf_list;
@@ -2593,12 +2602,9 @@ hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uin
   // n_large and n_ovf
   hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, &st->n_large, (uint64_t)2, 0ull);
   hipLaunchKernelGGL(k_classify_leaves, dim3(grid_for(max_leaves, 256, 2048)), dim3(256), 0, s,
-                     leaves, st, small_max, large_list, huge_min, second ? ovf_list : nullptr);
-  if (mode == 1 || words == 4) {  // every non-empty leaf is in the list
-    hipLaunchKernelGGL(k_empty_leaves, dim3(grid_for(max_leaves, 256, 2048)), dim3(256), 0, s,
-                       leaves, st, d_out);
-    return hipGetLastError();
-  }
+                     leaves, st, small_max, large_list, huge_min, second ? ovf_list : nullptr,
+                     one_wave ? nullptr : d_out);
+  if (!one_wave) return hipGetLastError();  // every non-empty leaf is in the list
   const unsigned gsmall = persistent(max_leaves, kSmallGrid);
 #define KC_SMALLW(HI, FF)                                                                        \
   hipLaunchKernelGGL((k_leaf_countw<u128, 64, kSmallCmax128, 8, HI, FF>), dim3(gsmall), dim3(64), \
