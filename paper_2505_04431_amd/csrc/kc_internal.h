@@ -55,6 +55,21 @@ struct DevState {
   CheckResult check;
 };
 
+// Device words to clear (up to kN arrays of n[r] words).
+struct ZeroRanges {
+  static constexpr int kN = 3;
+  unsigned long long* p[kN];
+  uint64_t n[kN];
+};
+
+// Where the leaves go: those of more than small_max records to large[], with
+// huge those of more than huge_min there; with d_zero the counts of empty
+// leaves are cleared.
+struct LeafLists {
+  uint64_t small_max, huge_min;
+  uint32_t *large, *huge, *d_zero;
+};
+
 // Read sets of a batch, for the window kernels: set_byte_off[s] is the first
 // byte of set s relative to the packed stream (n_sets + 1 entries), and
 // set_local[s] its id within the k-class being counted (kNoSet if the set
@@ -87,22 +102,22 @@ hipError_t launch_pack(const uint8_t* src, uint64_t n_bytes, const uint64_t* off
 // byte_end), from the invalid-byte and read-end masks of launch_pack: bit j of
 // valid[w] is set iff the window starting at byte 64w + j is valid. Writes the
 // words the window kernels below read for the same byte range (valid holds as
-// many words as inv).
+// many words as inv). Also clears the words of z (the counters of the
+// pipeline that this launch starts).
 hipError_t launch_valid_mask(int words, const uint64_t* inv, const uint64_t* endm,
                              uint64_t byte_begin, uint64_t byte_end, int k, uint64_t* valid,
-                             hipStream_t s);
+                             const ZeroRanges& z, hipStream_t s);
 
 // Window kernels over the bytes [byte_begin, byte_end) of the packed stream,
 // with the valid-start mask of launch_valid_mask for the same range and k.
 // keybits = 2k (plain) or 2k + set id bits (batch: batch != nullptr).
-// hist: (1 + kXcds) << shard_bits entries, zeroed: per-shard totals, then
-// per class of the owner scatter's tiles (tile index mod kXcds; the scatter's
-// shape follows from words and starts_per_thread).
+// hist: (1 + kXcds) << shard_bits entries, zeroed: per-shard totals (left to
+// launch_plan_shards), then per class of the owner scatter's tiles (tile index
+// mod kXcds; the scatter's shape follows from words and starts_per_thread).
 hipError_t launch_window_hist(int words, const uint64_t* packed, const uint64_t* valid,
                               uint64_t byte_begin, uint64_t byte_end, int k,
                               int keybits, int shard_bits, const BatchSets* batch,
-                              unsigned long long* hist, unsigned long long* wcount,
-                              int starts_per_thread, hipStream_t s);
+                              unsigned long long* hist, int starts_per_thread, hipStream_t s);
 
 // starts_per_thread: 8, or 16 for one-word keys (16,384-record LDS tiles).
 // cursor[]: the class cursors of launch_plan_shards; a tile of class x takes
@@ -118,15 +133,15 @@ hipError_t launch_window_scatter(int words, const uint64_t* packed, const uint64
 // (kXcds << shard_bits entries) where each tile class's part of each shard
 // slice starts (from the class counts of hist[]); bins[] the split of each shard; items[] the tiles of
 // the split shards (item_off[] holds nb+1 prefix offsets of them); subhist[]
-// (ncls * max_leaves entries: one part per item class of the split) is
-// prepared: zeros, but the shard size at the leaf of each unsplit shard in
-// the first part; st->n_items and st->n_leaves are set.
-hipError_t launch_plan_shards(const unsigned long long* hist, const int* order, int shard_bits,
+// (one part per item class of the split, zeroed) gets the shard size at the
+// leaf of each unsplit shard in the first part; hist[] its totals;
+// st->W (their sum), st->n_items and st->n_leaves are set.
+hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int shard_bits,
                               int keybits, uint64_t leaf_target, uint64_t leaf_attempt,
                               int tile, unsigned long long* sbegin, unsigned long long* cursor,
                               SplitBin* bins, SplitItem* items, unsigned long long* item_off,
-                              unsigned long long* subhist, uint64_t max_leaves,
-                              uint64_t max_items, int ncls, DevState* st, hipStream_t s);
+                              unsigned long long* subhist, uint64_t max_items, DevState* st,
+                              hipStream_t s);
 
 // Device planning of the leaves (one block): leaf table in key order and the
 // sub-bin cursors of the split shards.
@@ -136,11 +151,16 @@ hipError_t launch_plan_shards(const unsigned long long* hist, const int* order, 
 // counts of class x are at subhist[x * cls_stride + leaf], and the split
 // scatter's cursors of class x at cursor[x * cls_stride + leaf] (each class
 // writes its own part of every sub-bin, the classes in order).
-hipError_t launch_plan_leaves(const unsigned long long* hist, const unsigned long long* sbegin,
-                              const SplitBin* bins, int shard_bits,
-                              const unsigned long long* subhist, Leaf* leaves,
+// Unless the split pre-aggregates, the leaves are classified at once (see
+// launch_leaf_small, whose list arguments these are; st->n_large and st->n_ovf
+// must be 0).
+hipError_t launch_plan_leaves(int words, const unsigned long long* hist,
+                              const unsigned long long* sbegin, const SplitBin* bins,
+                              int shard_bits, const unsigned long long* subhist, Leaf* leaves,
                               unsigned long long* cursor, int merge_cshift, int ncls,
-                              uint64_t cls_stride, hipStream_t s);
+                              uint64_t cls_stride, DevState* st, uint64_t max_leaves,
+                              uint32_t* d_out, uint32_t* large_list, uint32_t* ovf_list,
+                              int slots_log2, int mode, hipStream_t s);
 
 // Split kernels loop over st->n_items items (persistent grid of at most max_items blocks).
 hipError_t launch_split_hist(int words, const void* src, const SplitItem* items,
@@ -173,14 +193,17 @@ hipError_t launch_leaf_ends(Leaf* leaves, const unsigned long long* cursor, cons
 // merged: leaves may hold pre-aggregated records (one-word keys).
 // ovf_list (max_leaves entries, or nullptr): one-word keys in mode 0 list
 // there the leaves whose table overflows, for launch_leaf_second.
-// launch_leaf_small also classifies the leaves: large ones into large_list;
+// With few leaves (max_leaves) none is small: all go to the block-wide kernel.
+// launch_leaf_small also classifies the leaves unless launch_plan_leaves has
+// (classified): large ones into large_list;
 // for one-word keys in mode 0 with ovf_list (and the second count running,
 // slots_log2 below its table), leaves of more than 8 << slots_log2 records
 // straight into ovf_list for launch_leaf_second.
 hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
                              uint32_t* d_out, uint32_t* large_list, uint32_t* ovf_list,
-                             int slots_log2, hipStream_t s, int mode, bool refine, bool merged);
+                             int slots_log2, hipStream_t s, int mode, bool refine, bool merged,
+                             bool classified);
 hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
                              uint32_t* d_out, int slots_log2, const uint32_t* large_list,
@@ -188,18 +211,20 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                              bool merged);
 // Second count of the leaves launch_leaf_large listed in ovf_list, with a
 // table twice as large (one 1,024-thread workgroup per CU); only what
-// overflows that table too stays marked overflowed (st->overflow is raised
-// again by those, and by launch_plan_out from the leaf counts). A no-op
-// where launch_leaf_large lists nothing.
+// overflows that table too stays marked overflowed (launch_plan_out raises
+// st->overflow from the leaf counts). A no-op where launch_leaf_large lists
+// nothing.
 hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                               const Leaf* leaves, DevState* st, uint32_t* d_out, int slots_log2,
                               const uint32_t* ovf_list, hipStream_t s, int mode, bool merged);
 uint64_t small_leaf_max(int words);
 
 // Exclusive scan of leaf counts into output offsets; st->D = total. bsum
-// holds scan_blocks(max_leaves) values.
+// holds scan_blocks(max_leaves) values. pub (device-visible host memory, or
+// nullptr) receives a copy of the state.
 hipError_t launch_plan_out(const uint32_t* d, DevState* st, unsigned long long* bsum,
-                           uint64_t max_leaves, unsigned long long* out_off, hipStream_t s);
+                           uint64_t max_leaves, unsigned long long* out_off, hipStream_t s,
+                           DevState* pub = nullptr);
 uint64_t scan_blocks(uint64_t max_leaves);
 
 // Overflow refinement: list the overflowed leaves (indices and entries; *count

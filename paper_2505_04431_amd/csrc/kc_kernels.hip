@@ -422,12 +422,19 @@ __device__ __forceinline__ u256 smear256(u256 x, int len) {
   return x;
 }
 
-// One thread per mask word w in [w_begin, w_end).
+// One thread per mask word w in [w_begin, w_end). Also clears the counters of
+// the pipeline that starts with this kernel (z): a launch of its own for each
+// array costs 4 to 5 us whatever its size, a third of a small count's time.
 template <bool WIDE>
 __global__ void __launch_bounds__(256) k_valid_mask(const uint64_t* __restrict__ inv,
                                                     const uint64_t* __restrict__ endm,
                                                     uint64_t w_begin, uint64_t w_end, int k,
-                                                    uint64_t* __restrict__ valid) {
+                                                    uint64_t* __restrict__ valid, ZeroRanges z) {
+#pragma unroll
+  for (int r = 0; r < ZeroRanges::kN; ++r)
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < z.n[r];
+         i += (uint64_t)gridDim.x * 256)
+      z.p[r][i] = 0;
   const uint64_t w = w_begin + (uint64_t)blockIdx.x * 256 + threadIdx.x;
   if (w >= w_end) return;
   uint64_t bad;
@@ -564,75 +571,66 @@ __device__ __forceinline__ uint32_t bits24(uint64_t p0, uint64_t p1, int q) {
 }
 
 // Shard histogram over the owner scatter's tiles: tile j holds the window
-// starts [w_begin + j*tile_starts, w_begin + (j+1)*tile_starts) ∩ [.., w_end),
-// taken S per thread. Totals go to hist[0, nb); the counts of the tiles of
-// class c = j mod kXcds to hist[(1 + c)*nb, ..) (gridDim.x is a multiple of
-// kXcds, so all of a workgroup's tiles are of class blockIdx.x mod kXcds).
+// starts [w_begin + j*R*TB*S, w_begin + (j+1)*R*TB*S) ∩ [.., w_end), taken S per
+// thread in R units of TB*S. The counts of the tiles of class c = j mod kXcds
+// go to hist[(1 + c)*nb, ..) (gridDim.x is a multiple of R*kXcds, so all of a
+// workgroup's units are of class blockIdx.x / R mod kXcds); k_plan_shards adds
+// up the totals, hist[0, nb). In smaller inputs every unit has a workgroup of
+// its own and a thread one step, not R dependent ones. The number of valid
+// windows is the sum of the totals: counted here, by one atomic per wave on one
+// word, it took most of the kernel (8,192 of them at 12 ns each; 1,000,000
+// reads: 139 -> 61 us, 3.7 MB: 27.6 -> 7.5 us).
 template <typename K, typename Kc, int S, int TB, bool BATCH>
 __global__ void __launch_bounds__(TB) k_window_hist(const uint64_t* __restrict__ packed,
                                                     const uint64_t* __restrict__ valid,
                                                     uint64_t w_begin, uint64_t w_end,
-                                                    uint64_t tile_starts, int k, int keybits,
+                                                    int R, int k, int keybits,
                                                     int shard_bits, BatchSets bs,
-                                                    unsigned long long* __restrict__ hist,
-                                                    unsigned long long* __restrict__ wcount) {
+                                                    unsigned long long* __restrict__ hist) {
   __shared__ uint32_t sh[1 << kMaxShardBits];
   const int nb = 1 << shard_bits;
   for (int i = threadIdx.x; i < nb; i += TB) sh[i] = 0;
   __syncthreads();
-  uint32_t w = 0;
-  const uint64_t n_tiles = (w_end - w_begin + tile_starts - 1) / tile_starts;
-  for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-    const uint64_t g_end = min(w_end, w_begin + (tile + 1) * tile_starts);
-    for (uint64_t g = w_begin + tile * tile_starts + (uint64_t)threadIdx.x * S; g < g_end;
-         g += (uint64_t)TB * S) {
-      uint32_t vm = valid_starts<S>(valid, g);
-      if (!vm) continue;
-      if constexpr (!BATCH && std::is_same<Kc, uint64_t>::value && S <= 8) {
-        if (k >= 5) {
-          // only the shard is needed: the top bits of min(fwd, rc) are the
-          // smaller of the top bits of fwd and of rc (if those are equal, so
-          // are both keys' top bits). The top 10 bits of fwd are its first 5
-          // bases, those of rc the complements of its last 5 bases, last first.
-          const uint64_t w0 = g >> 5;
-          const uint64_t p0 = packed[w0], p1 = packed[w0 + 1];
-          const int s0 = (int)(g & 31);
-          const uint32_t head = bits24(p0, p1, 2 * s0);            // bases g .. g+11
-          const uint32_t tail = bits24(p0, p1, 2 * (s0 + k - 5));  // bases g+k-5 .. g+k+6
-          // the 12 head bases in reverse order (each base's 2-bit code kept):
-          // reverse all bits, then swap the two bits of every base
-          const uint32_t hb = __builtin_bitreverse32(head) >> 8;
-          const uint32_t hr = ((hb >> 1) & 0x555555u) | ((hb & 0x555555u) << 1);
+  for (uint64_t g = w_begin + ((uint64_t)blockIdx.x * TB + threadIdx.x) * S; g < w_end;
+       g += (uint64_t)gridDim.x * TB * S) {
+    uint32_t vm = valid_starts<S>(valid, g);
+    if (!vm) continue;
+    if constexpr (!BATCH && std::is_same<Kc, uint64_t>::value && S <= 8) {
+      if (k >= 5) {
+        // only the shard is needed: the top bits of min(fwd, rc) are the
+        // smaller of the top bits of fwd and of rc (if those are equal, so
+        // are both keys' top bits). The top 10 bits of fwd are its first 5
+        // bases, those of rc the complements of its last 5 bases, last first.
+        const uint64_t w0 = g >> 5;
+        const uint64_t p0 = packed[w0], p1 = packed[w0 + 1];
+        const int s0 = (int)(g & 31);
+        const uint32_t head = bits24(p0, p1, 2 * s0);            // bases g .. g+11
+        const uint32_t tail = bits24(p0, p1, 2 * (s0 + k - 5));  // bases g+k-5 .. g+k+6
+        // the 12 head bases in reverse order (each base's 2-bit code kept):
+        // reverse all bits, then swap the two bits of every base
+        const uint32_t hb = __builtin_bitreverse32(head) >> 8;
+        const uint32_t hr = ((hb >> 1) & 0x555555u) | ((hb & 0x555555u) << 1);
 #pragma unroll
-          for (int i = 0; i < S; ++i) {
-            if (!(vm & (1u << i))) continue;
-            // bases g+i .. g+i+4, the first most significant
-            const uint32_t f = (hr >> (2 * (7 - i))) & 0x3FFu;
-            const uint32_t r = ((tail >> (2 * i)) & 0x3FFu) ^ 0x3FFu;
-            atomicAdd(&sh[min(f, r) >> (10 - shard_bits)], 1u);
-          }
-          w += __builtin_popcount(vm);
-          continue;
+        for (int i = 0; i < S; ++i) {
+          if (!(vm & (1u << i))) continue;
+          // bases g+i .. g+i+4, the first most significant
+          const uint32_t f = (hr >> (2 * (7 - i))) & 0x3FFu;
+          const uint32_t r = ((tail >> (2 * i)) & 0x3FFu) ^ 0x3FFu;
+          atomicAdd(&sh[min(f, r) >> (10 - shard_bits)], 1u);
         }
+        continue;
       }
-      K keys[S];
-      vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, keys);
+    }
+    K keys[S];
+    vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, keys);
 #pragma unroll
-      for (int i = 0; i < S; ++i)
-        if (vm & (1u << i)) atomicAdd(&sh[shard_of(keys[i], keybits, shard_bits)], 1u);
-      w += __builtin_popcount(vm);
-    }
+    for (int i = 0; i < S; ++i)
+      if (vm & (1u << i)) atomicAdd(&sh[shard_of(keys[i], keybits, shard_bits)], 1u);
   }
-  // per-wave sum of valid windows, one global atomic per wave
-  for (int off = 32; off > 0; off >>= 1) w += __shfl_xor(w, off);
-  if ((threadIdx.x & 63) == 0 && w) atomicAdd(wcount, (unsigned long long)w);
   __syncthreads();
-  unsigned long long* const hc = hist + (uint64_t)(1 + blockIdx.x % kXcds) * nb;
+  unsigned long long* const hc = hist + (uint64_t)(1 + blockIdx.x / R % kXcds) * nb;
   for (int i = threadIdx.x; i < nb; i += TB)
-    if (sh[i]) {
-      atomicAdd(&hist[i], (unsigned long long)sh[i]);
-      atomicAdd(&hc[i], (unsigned long long)sh[i]);
-    }
+    if (sh[i]) atomicAdd(&hc[i], (unsigned long long)sh[i]);
 }
 
 // Owner-major scatter of window records into shard slices (cursor[x*nb + i]
@@ -731,6 +729,9 @@ k_window_scatter64(const uint64_t* __restrict__ packed, const uint64_t* __restri
 // ---------------------------------------------------------------- planning (one block)
 
 constexpr int kPlanTB = 1024;
+// Up to this many split items are listed by the one planning workgroup itself
+// (a few rounds of its waves); more by a launch of their own.
+constexpr uint64_t kFewItems = 4096;
 
 __device__ __forceinline__ int ceil_log2_dev(uint64_t x) {
   return x <= 1 ? 0 : 64 - __builtin_clzll(x - 1);
@@ -739,21 +740,34 @@ __device__ __forceinline__ int ceil_log2_dev(uint64_t x) {
 // Shard plan: owner-major record ranges, split decision per shard, split
 // work items, leaf slot offsets (leaf slots follow key order).
 __global__ void __launch_bounds__(kPlanTB) k_plan_shards(
-    const unsigned long long* __restrict__ hist, const int* __restrict__ order, int shard_bits,
+    unsigned long long* __restrict__ hist, const int* __restrict__ order, int shard_bits,
     int keybits, uint64_t leaf_target, uint64_t leaf_attempt, int tile,
     unsigned long long* __restrict__ sbegin, unsigned long long* __restrict__ cursor,
     SplitBin* __restrict__ bins, unsigned long long* __restrict__ item_off,
-    unsigned long long* __restrict__ subhist, DevState* __restrict__ st) {
+    unsigned long long* __restrict__ subhist, DevState* __restrict__ st,
+    SplitItem* __restrict__ items) {
   __shared__ unsigned long long wsum[kPlanTB / 64];
+  __shared__ unsigned long long s_hist[kPlanTB], s_off[kPlanTB + 1], s_begin[kPlanTB];
   const int nb = 1 << shard_bits;  // <= kPlanTB
   const int t = threadIdx.x;
   unsigned long long total;
+  // shard sizes: the sum over the tile classes
+  unsigned long long h = 0;
+  if (t < nb) {
+#pragma unroll
+    for (int x = 0; x < kXcds; ++x) h += hist[(uint64_t)(1 + x) * nb + t];
+    hist[t] = h;
+    s_hist[t] = h;
+  }
+  __syncthreads();
   // owner-major exclusive scan: the t-th shard in owner order
   const int co = t < nb ? order[t] : 0;
-  const unsigned long long ho = t < nb ? hist[co] : 0ull;
+  const unsigned long long ho = t < nb ? s_hist[co] : 0ull;
   const unsigned long long b0 = block_exscan<kPlanTB, unsigned long long>(ho, wsum, &total);
+  if (t == 0) st->W = total;  // every valid window has one shard
   if (t < nb) {
     sbegin[co] = b0;
+    s_begin[co] = b0;
     // each class's part of the slice: after the earlier classes' records
     unsigned long long c = b0;
     for (int x = 0; x < kXcds; ++x) {
@@ -762,7 +776,6 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_shards(
     }
   }
   // split decision for shard t (key order)
-  const unsigned long long h = t < nb ? hist[t] : 0ull;
   int nbits = 0;
   const int remaining = keybits - shard_bits;
   if (h > leaf_attempt && remaining > 0) {
@@ -784,6 +797,18 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_shards(
     item_off[nb] = n_items;
     st->n_items = n_items;
     st->n_leaves = n_leaves;
+  }
+  if (!items) return;  // many items: k_plan_items lists them
+  if (t < nb) s_off[t] = ioff;
+  if (t == 0) s_off[nb] = n_items;
+  __syncthreads();
+  // a shard's items by one wave
+  for (int c = t >> 6; c < nb; c += kPlanTB / 64) {
+    const unsigned long long i0 = s_off[c], i1 = s_off[c + 1], b = s_begin[c], e = b + s_hist[c];
+    for (unsigned long long i = i0 + (t & 63); i < i1; i += 64) {
+      const unsigned long long a = b + (i - i0) * (unsigned long long)tile;
+      items[i] = SplitItem{a, min(e, a + (unsigned long long)tile), (uint32_t)c, 0};
+    }
   }
 }
 
@@ -807,19 +832,80 @@ __global__ void k_plan_items(const unsigned long long* __restrict__ hist,
   }
 }
 
-// Leaf table (key order) and sub-bin cursors: block c handles shard c.
+// Classification of the leaves, a lane each (id i of len records; has: the
+// lane has a leaf). Leaves above the small-leaf size go to a list of their own
+// (order irrelevant); with huge != nullptr, leaves of more than huge_min
+// records go straight to that list instead (st->n_ovf), for the second count's
+// larger table: such leaves are the dense clusters that overflow the first
+// table (on 40,000,000 reads at k = 31 the overflowed leaves average 147,000
+// records, the others 4,600), and the first count would read part of them
+// before giving up. d_zero != nullptr (no one-wave kernel follows): the counts
+// of empty leaves are set to 0 there.
+// Called by all threads of a workgroup of up to 1,024; sh holds 2 * 17 words.
+// One atomic per list and workgroup: one per wave, on one word, took 130 us for
+// the 2^20 leaves of 20,000,000 reads at 12 ns each (the whole kernel now 21 us).
+__device__ __forceinline__ void classify_leaves(bool has, uint32_t i, uint64_t len,
+                                                DevState* __restrict__ st, const LeafLists& q,
+                                                uint32_t* sh, unsigned long long* base) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
+  const bool to_huge = has && q.huge && len > q.huge_min;
+  const bool big = has && !to_huge && len > q.small_max;
+  if (q.d_zero && has && len == 0) q.d_zero[i] = 0;
+  const unsigned long long m = __ballot(big), mh = __ballot(to_huge);
+  if (lane == 0) {
+    sh[w] = (uint32_t)__popcll(m);
+    sh[17 + w] = (uint32_t)__popcll(mh);
+  }
+  __syncthreads();
+  if (threadIdx.x < 2) {
+    uint32_t* const c = sh + 17 * threadIdx.x;
+    uint32_t run = 0;
+    for (int v = 0; v < nw; ++v) {
+      const uint32_t x = c[v];
+      c[v] = run;
+      run += x;
+    }
+    base[threadIdx.x] =
+        run ? atomicAdd(threadIdx.x == 0 ? &st->n_large : &st->n_ovf, (unsigned long long)run) : 0;
+  }
+  __syncthreads();
+  const unsigned long long below = (1ull << lane) - 1;
+  if (big) q.large[base[0] + sh[w] + __popcll(m & below)] = i;
+  if (to_huge) q.huge[base[1] + sh[17 + w] + __popcll(mh & below)] = i;
+  __syncthreads();
+}
+
+__global__ void k_classify_leaves(const Leaf* __restrict__ leaves, DevState* __restrict__ st,
+                                  LeafLists q) {
+  __shared__ uint32_t sh[34];
+  __shared__ unsigned long long base[2];
+  const unsigned long long n = st->n_leaves;
+  const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
+  for (unsigned long long i0 = (unsigned long long)blockIdx.x * blockDim.x; i0 < n; i0 += stride) {
+    const unsigned long long i = i0 + threadIdx.x;
+    const Leaf lf = i < n ? leaves[i] : Leaf{0, 0, 0, 0, 0, 0};
+    classify_leaves(i < n, (uint32_t)i, lf.end - lf.begin, st, q, sh, base);
+  }
+}
+
+// Leaf table (key order) and sub-bin cursors: block c handles shard c. With
+// q.large the leaves are classified here as well (not where pre-aggregation
+// still shortens them).
 __global__ void __launch_bounds__(kPlanTB) k_plan_leaves(
     const unsigned long long* __restrict__ hist, const unsigned long long* __restrict__ sbegin,
     const SplitBin* __restrict__ bins, int shard_bits,
     const unsigned long long* __restrict__ subhist, Leaf* __restrict__ leaves,
-    unsigned long long* __restrict__ cursor, int merge_cshift, int ncls, uint64_t cls_stride) {
-  __shared__ unsigned long long wsum[kPlanTB / 64];
+    unsigned long long* __restrict__ cursor, int merge_cshift, int ncls, uint64_t cls_stride,
+    DevState* __restrict__ st, LeafLists q) {
+  __shared__ unsigned long long wsum[kPlanTB / 64], base[2];
+  __shared__ uint32_t sh[34];
   const int c = blockIdx.x;
   const unsigned long long h = hist[c];
   if (!h) return;
   const SplitBin b = bins[c];
   if (b.nbits == 0) {
     if (threadIdx.x == 0) leaves[b.hist_off] = Leaf{sbegin[c], sbegin[c] + h, 0u, (uint32_t)shard_bits};
+    if (q.large) classify_leaves(threadIdx.x == 0, (uint32_t)b.hist_off, h, st, q, sh, base);
     return;
   }
   const uint32_t nsub = 1u << b.nbits;  // <= kPlanTB
@@ -840,6 +926,7 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_leaves(
       at += subhist[x * cls_stride + b.hist_off + j];
     }
   }
+  if (q.large) classify_leaves(j < nsub, (uint32_t)(b.hist_off + j), n, st, q, sh, base);
 }
 
 // ---------------------------------------------------------------- refinement support
@@ -909,54 +996,6 @@ __global__ void k_splice_parts(const uint32_t* __restrict__ root_leaf,
   }
 }
 
-// Before a second-chance count of overflowed leaves: the flag is raised again
-// by that count's own overflows (and by the output-offset scan, from the leaf
-// counts).
-__global__ void k_clear_overflow(DevState* __restrict__ st) {
-  if (threadIdx.x == 0) st->overflow = 0;
-}
-
-// Leaves above the small-leaf size go to a list of their own (order
-// irrelevant); with huge != nullptr, leaves of more than huge_min records go
-// straight to that list instead (st->n_ovf), for the second count's larger
-// table: such leaves are the dense clusters that overflow the first table
-// (on 40,000,000 reads at k = 31 the overflowed leaves average 147,000
-// records, the others 4,600), and the first count would read part of them
-// before giving up. d_zero != nullptr (no one-wave kernel follows): the counts
-// of empty leaves are set to 0 there.
-__global__ void k_classify_leaves(const Leaf* __restrict__ leaves, DevState* __restrict__ st,
-                                  uint64_t small_max, uint32_t* __restrict__ large,
-                                  uint64_t huge_min, uint32_t* __restrict__ huge,
-                                  uint32_t* __restrict__ d_zero) {
-  const unsigned long long n = st->n_leaves;
-  const unsigned long long stride = (unsigned long long)gridDim.x * blockDim.x;
-  const int lane = threadIdx.x & 63;
-  for (unsigned long long i0 = (unsigned long long)blockIdx.x * blockDim.x; i0 < n; i0 += stride) {
-    const unsigned long long i = i0 + threadIdx.x;
-    const Leaf lf = i < n ? leaves[i] : Leaf{0, 0, 0, 0, 0, 0};
-    const uint64_t len = lf.end - lf.begin;
-    const bool to_huge = huge && len > huge_min;
-    const bool big = !to_huge && len > small_max;
-    if (d_zero && i < n && len == 0) d_zero[i] = 0;
-    const unsigned long long m = __ballot(big);
-    if (m) {
-      const int leader = __ffsll((long long)m) - 1;
-      unsigned long long base = 0;
-      if (lane == leader) base = atomicAdd(&st->n_large, (unsigned long long)__popcll(m));
-      base = __shfl(base, leader);
-      if (big) large[base + __popcll(m & ((1ull << lane) - 1))] = (uint32_t)i;
-    }
-    const unsigned long long mh = __ballot(to_huge);
-    if (mh) {
-      const int leader = __ffsll((long long)mh) - 1;
-      unsigned long long base = 0;
-      if (lane == leader) base = atomicAdd(&st->n_ovf, (unsigned long long)__popcll(mh));
-      base = __shfl(base, leader);
-      if (to_huge) huge[base + __popcll(mh & ((1ull << lane) - 1))] = (uint32_t)i;
-    }
-  }
-}
-
 // Output offsets: exclusive scan of the leaf counts in leaf (= key) order, in
 // three steps (tile sums, scan of tile sums, tile scans). Overflowed leaves
 // count zero and raise st->overflow.
@@ -1001,11 +1040,24 @@ __global__ void __launch_bounds__(kPlanTB) k_scan_top(unsigned long long* __rest
   if (threadIdx.x == 0) st->D = total;
 }
 
+// The call's state into host memory, once it is final: the host then only
+// waits for the stream, with no copy queued behind the last kernel.
+__device__ __forceinline__ void publish_state(DevState* st, DevState* pub) {
+  static_assert(sizeof(DevState) % 8 == 0, "copied by words");
+  // (loads past this CU's caches: some words may just have been written)
+  if (pub && threadIdx.x < sizeof(DevState) / 8)
+    ((unsigned long long*)pub)[threadIdx.x] =
+        __hip_atomic_load((unsigned long long*)st + threadIdx.x, __ATOMIC_RELAXED,
+                          __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __global__ void __launch_bounds__(kScanTB) k_scan_down(const uint32_t* __restrict__ d,
-                                                       const DevState* __restrict__ st,
+                                                       DevState* st,
                                                        const unsigned long long* __restrict__ bsum,
-                                                       unsigned long long* __restrict__ out_off) {
+                                                       unsigned long long* __restrict__ out_off,
+                                                       DevState* pub) {
   __shared__ unsigned long long wsum[kScanTB / 64];
+  if (blockIdx.x == 0) publish_state(st, pub);
   const unsigned long long n = st->n_leaves;
   // thread t owns kScanPer consecutive leaves of the tile
   const unsigned long long base = (unsigned long long)blockIdx.x * kScanTile +
@@ -1027,6 +1079,42 @@ __global__ void __launch_bounds__(kScanTB) k_scan_down(const uint32_t* __restric
     if (i < n) out_off[i] = run;
     run += v[j];
   }
+}
+
+// The same by one workgroup, for up to kScanOneMax leaves: one launch instead
+// of three.
+constexpr uint32_t kScanOnePer = 16;
+constexpr uint64_t kScanOneMax = (uint64_t)kPlanTB * kScanOnePer;
+__global__ void __launch_bounds__(kPlanTB) k_scan_one(const uint32_t* __restrict__ d, DevState* st,
+                                                      unsigned long long* __restrict__ out_off,
+                                                      DevState* pub) {
+  __shared__ unsigned long long wsum[kPlanTB / 64];
+  const uint32_t n = (uint32_t)min(st->n_leaves, (unsigned long long)kScanOneMax);
+  const uint32_t per = (n + kPlanTB - 1) / kPlanTB, base = threadIdx.x * per;
+  uint32_t v[kScanOnePer];
+  unsigned long long s = 0;
+  bool ovf = false;
+#pragma unroll
+  for (uint32_t j = 0; j < kScanOnePer; ++j) {
+    v[j] = j < per && base + j < n ? d[base + j] : 0u;
+    if (v[j] == kLeafOverflow) {
+      ovf = true;
+      v[j] = 0;
+    }
+    s += v[j];
+  }
+  if (ovf) atomicOr(&st->overflow, 1u);
+  unsigned long long total;
+  unsigned long long run = block_exscan<kPlanTB, unsigned long long>(s, wsum, &total);
+#pragma unroll
+  for (uint32_t j = 0; j < kScanOnePer; ++j) {
+    if (j < per && base + j < n) out_off[base + j] = run;
+    run += v[j];
+  }
+  if (threadIdx.x == 0) st->D = total;
+  __threadfence();
+  __syncthreads();
+  publish_state(st, pub);
 }
 
 // ---------------------------------------------------------------- split (MSD step)
@@ -1573,7 +1661,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     if (ovf_get(&s_ovf)) {
       if (threadIdx.x == 0) {
         d_out[l] = kLeafOverflow;
-        atomicOr(&st->overflow, 1u);
+        // (st->overflow is raised from the leaf counts by the output-offset scan)
         if (ovf_list) ovf_list[atomicAdd(&st->n_ovf, 1ull)] = (uint32_t)l;
       }
       __syncthreads();
@@ -2323,7 +2411,7 @@ __global__ void __launch_bounds__(256) k_check(const uint64_t* __restrict__ keys
 }
 
 constexpr int kHistTB = 256;
-constexpr unsigned kHistGrid = 2048;  // a multiple of kXcds
+constexpr unsigned kHistGrid = 2048;  // a multiple of kXcds times the units of a tile (1 to 8)
 constexpr int kScatterTB64 = 1024;
 constexpr int kScatterTB128 = 512;
 constexpr int kSplitTB64 = 1024;
@@ -2397,41 +2485,45 @@ hipError_t launch_pack(const uint8_t* src, uint64_t n_bytes, const uint64_t* off
 
 hipError_t launch_valid_mask(int words, const uint64_t* inv, const uint64_t* endm,
                              uint64_t byte_begin, uint64_t byte_end, int k, uint64_t* valid,
-                             hipStream_t s) {
+                             const ZeroRanges& z, hipStream_t s) {
   // the words the window kernels read: starts [byte_begin, byte_end) rounded
   // out to whole threads, which stay inside whole words
-  const uint64_t w_begin = byte_begin >> 6, w_end = (byte_end + 63) >> 6;
-  if (w_end <= w_begin) return hipSuccess;
-  const unsigned grid = (unsigned)((w_end - w_begin + 255) / 256);
+  const uint64_t w_begin = byte_begin >> 6;
+  const uint64_t w_end = std::max(w_begin, (byte_end + 63) >> 6);
+  uint64_t zeros = 0;
+  for (uint64_t n : z.n) zeros += n;
+  if (w_end == w_begin && !zeros) return hipSuccess;
+  const unsigned grid = (unsigned)std::max<uint64_t>(
+      (w_end - w_begin + 255) / 256, std::min<uint64_t>((zeros + 1023) / 1024, 1024));
   if (words == 4)
     hipLaunchKernelGGL(k_valid_mask<true>, dim3(grid), dim3(256), 0, s, inv, endm, w_begin, w_end,
-                       k, valid);
+                       k, valid, z);
   else
     hipLaunchKernelGGL(k_valid_mask<false>, dim3(grid), dim3(256), 0, s, inv, endm, w_begin,
-                       w_end, k, valid);
+                       w_end, k, valid, z);
   return hipGetLastError();
 }
 
 #define KC_HIST_LAUNCH(K, KC, BATCH)                                                            \
   hipLaunchKernelGGL((k_window_hist<K, KC, kWinStarts, kHistTB, BATCH>), dim3(grid),            \
-                     dim3(kHistTB), 0, s, packed, valid, w_begin, w_end, tile_starts, k, keybits, \
-                     shard_bits, bs, hist, wcount)
+                     dim3(kHistTB), 0, s, packed, valid, w_begin, w_end, R, k, keybits,         \
+                     shard_bits, bs, hist)
 
 hipError_t launch_window_hist(int words, const uint64_t* packed, const uint64_t* valid,
                               uint64_t byte_begin, uint64_t byte_end, int k,
                               int keybits, int shard_bits, const BatchSets* batch,
-                              unsigned long long* hist, unsigned long long* wcount,
-                              int starts_per_thread, hipStream_t s) {
+                              unsigned long long* hist, int starts_per_thread, hipStream_t s) {
   // the owner scatter's tiles (see launch_window_scatter)
   const int S = words == 1 && starts_per_thread == 16 ? 16 : kWinStarts;
   const int TBs = words == 4 ? kScatterTB256 : words == 2 ? kScatterTB128 : kScatterTB64;
   const uint64_t w_begin = byte_begin / S * S;
   const uint64_t w_end = (byte_end + S - 1) / S * S;
-  const uint64_t tile_starts = (uint64_t)TBs * S;
-  const uint64_t n_tiles = (w_end - w_begin + tile_starts - 1) / tile_starts;
-  // a multiple of kXcds workgroups (every workgroup's tiles share a class)
-  const unsigned grid = (unsigned)std::min<uint64_t>((n_tiles + kXcds - 1) / kXcds * kXcds,
-                                                     kHistGrid);
+  const uint64_t unit = (uint64_t)kHistTB * kWinStarts;
+  const int R = (int)((uint64_t)TBs * S / unit);  // units per tile
+  const uint64_t n_units = (w_end - w_begin + unit - 1) / unit;
+  // a multiple of R * kXcds workgroups (every workgroup's units share a class)
+  const uint64_t step = (uint64_t)R * kXcds;
+  const unsigned grid = (unsigned)std::min<uint64_t>((n_units + step - 1) / step * step, kHistGrid);
   if (grid == 0) return hipSuccess;
   const BatchSets bs = batch ? *batch : BatchSets{nullptr, nullptr, 0};
   const bool wide = words == 2;
@@ -2498,29 +2590,46 @@ hipError_t launch_window_scatter(int words, const uint64_t* packed, const uint64
 #undef KC_WINDOW_LAUNCH
 #undef KC_WINDOW_LAUNCH_S
 
-hipError_t launch_plan_shards(const unsigned long long* hist, const int* order, int shard_bits,
+hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int shard_bits,
                               int keybits, uint64_t leaf_target, uint64_t leaf_attempt,
                               int tile, unsigned long long* sbegin, unsigned long long* cursor,
                               SplitBin* bins, SplitItem* items, unsigned long long* item_off,
-                              unsigned long long* subhist, uint64_t max_leaves,
-                              uint64_t max_items, int ncls, DevState* st, hipStream_t s) {
-  hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(max_leaves * ncls, 256, 1024)), dim3(256), 0, s,
-                     subhist, max_leaves * ncls, 0ull);
+                              unsigned long long* subhist, uint64_t max_items, DevState* st,
+                              hipStream_t s) {
+  const bool few = max_items <= kFewItems;
   hipLaunchKernelGGL(k_plan_shards, dim3(1), dim3(kPlanTB), 0, s, hist, order, shard_bits,
                      keybits, leaf_target, leaf_attempt, tile, sbegin, cursor, bins, item_off,
-                     subhist, st);
-  hipLaunchKernelGGL(k_plan_items, dim3(grid_for(max_items, 256, 2048)), dim3(256), 0, s, hist,
+                     subhist, st, few ? items : (SplitItem*)nullptr);
+  if (!few)
+    hipLaunchKernelGGL(k_plan_items, dim3(grid_for(max_items, 256, 2048)), dim3(256), 0, s, hist,
                      sbegin, item_off, shard_bits, tile, st, items);
   return hipGetLastError();
 }
 
-hipError_t launch_plan_leaves(const unsigned long long* hist, const unsigned long long* sbegin,
-                              const SplitBin* bins, int shard_bits,
-                              const unsigned long long* subhist, Leaf* leaves,
+// Which leaves go where (see classify_leaves).
+static LeafLists leaf_lists(int words, uint64_t max_leaves, uint32_t* d_out, uint32_t* large_list,
+                            uint32_t* ovf_list, int slots_log2, int mode) {
+  const bool one_wave = mode != 1 && words != 4 && max_leaves > kFewLeaves;
+  // leaves of more than 8 first tables of records go straight to the second
+  // count (where it runs: launch_leaf_second)
+  const bool second = words == 1 && mode != 1 && slots_log2 < kRescueSlotsLog2 && ovf_list;
+  return LeafLists{one_wave ? small_leaf_max(words) : 0, 8ull << slots_log2, large_list,
+                   second ? ovf_list : nullptr, one_wave ? nullptr : d_out};
+}
+
+hipError_t launch_plan_leaves(int words, const unsigned long long* hist,
+                              const unsigned long long* sbegin, const SplitBin* bins,
+                              int shard_bits, const unsigned long long* subhist, Leaf* leaves,
                               unsigned long long* cursor, int merge_cshift, int ncls,
-                              uint64_t cls_stride, hipStream_t s) {
+                              uint64_t cls_stride, DevState* st, uint64_t max_leaves,
+                              uint32_t* d_out, uint32_t* large_list, uint32_t* ovf_list,
+                              int slots_log2, int mode, hipStream_t s) {
+  LeafLists q{};
+  if (!merge_cshift)
+    q = leaf_lists(words, max_leaves, d_out, large_list, ovf_list, slots_log2, mode);
   hipLaunchKernelGGL(k_plan_leaves, dim3(1u << shard_bits), dim3(kPlanTB), 0, s, hist, sbegin,
-                     bins, shard_bits, subhist, leaves, cursor, merge_cshift, ncls, cls_stride);
+                     bins, shard_bits, subhist, leaves, cursor, merge_cshift, ncls, cls_stride, st,
+                     q);
   return hipGetLastError();
 }
 
@@ -2591,20 +2700,18 @@ uint64_t small_leaf_max(int words) {
 hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
                              uint32_t* d_out, uint32_t* large_list, uint32_t* ovf_list,
-                             int slots_log2, hipStream_t s, int mode, bool refine, bool merged) {
+                             int slots_log2, hipStream_t s, int mode, bool refine, bool merged,
+                             bool classified) {
   const bool wide = words == 2;
-  const bool one_wave = mode != 1 && words != 4 && max_leaves > kFewLeaves;
-  const uint64_t small_max = one_wave ? small_leaf_max(words) : 0;
-  // leaves of more than 8 first tables of records go straight to the second
-  // count (where it runs: launch_leaf_second)
-  const bool second = words == 1 && mode != 1 && slots_log2 < kRescueSlotsLog2 && ovf_list;
-  const uint64_t huge_min = 8ull << slots_log2;
-  // n_large and n_ovf
-  hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, &st->n_large, (uint64_t)2, 0ull);
-  hipLaunchKernelGGL(k_classify_leaves, dim3(grid_for(max_leaves, 256, 2048)), dim3(256), 0, s,
-                     leaves, st, small_max, large_list, huge_min, second ? ovf_list : nullptr,
-                     one_wave ? nullptr : d_out);
-  if (!one_wave) return hipGetLastError();  // every non-empty leaf is in the list
+  const LeafLists q = leaf_lists(words, max_leaves, d_out, large_list, ovf_list, slots_log2, mode);
+  const uint64_t small_max = q.small_max;
+  if (!classified) {
+    // n_large and n_ovf
+    hipLaunchKernelGGL(k_fill_u64, dim3(1), dim3(64), 0, s, &st->n_large, (uint64_t)2, 0ull);
+    hipLaunchKernelGGL(k_classify_leaves, dim3(grid_for(max_leaves, 256, 2048)), dim3(256), 0, s,
+                       leaves, st, q);
+  }
+  if (q.d_zero) return hipGetLastError();  // every non-empty leaf is in a list
   const unsigned gsmall = persistent(max_leaves, kSmallGrid);
 #define KC_SMALLW(HI, FF)                                                                        \
   hipLaunchKernelGGL((k_leaf_countw<u128, 64, kSmallCmax128, 8, HI, FF>), dim3(gsmall), dim3(64), \
@@ -2701,7 +2808,6 @@ hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, ui
   // its distinct keys: clusters of keys that share a long prefix, the
   // erroneous and diverged copies of frequent k-mers, which a split on the
   // next key bits barely thins out)
-  hipLaunchKernelGGL(k_clear_overflow, dim3(1), dim3(64), 0, s, st);
   if (merged)
     hipLaunchKernelGGL((k_leaf_count64<kRescueTB, kRescueCmax64, 4, true, true>),
                        dim3(kRescueGrid), dim3(kRescueTB), 0, s, keybits, (uint64_t*)bufA,
@@ -2749,12 +2855,18 @@ hipError_t launch_splice(const Leaf* leaves, const uint32_t* d, uint64_t n,
 uint64_t scan_blocks(uint64_t max_leaves) { return (max_leaves + kScanTile - 1) / kScanTile; }
 
 hipError_t launch_plan_out(const uint32_t* d, DevState* st, unsigned long long* bsum,
-                           uint64_t max_leaves, unsigned long long* out_off, hipStream_t s) {
+                           uint64_t max_leaves, unsigned long long* out_off, hipStream_t s,
+                           DevState* pub) {
+  if (max_leaves <= kScanOneMax) {
+    hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(kPlanTB), 0, s, d, st, out_off, pub);
+    return hipGetLastError();
+  }
   const uint64_t nb = scan_blocks(max_leaves);
   if (nb > 65536u * kPlanTB) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_scan_reduce, dim3((unsigned)nb), dim3(kScanTB), 0, s, d, st, bsum);
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kPlanTB), 0, s, bsum, (uint32_t)nb, st);
-  hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanTB), 0, s, d, st, bsum, out_off);
+  hipLaunchKernelGGL(k_scan_down, dim3((unsigned)nb), dim3(kScanTB), 0, s, d, st, bsum, out_off,
+                     pub);
   return hipGetLastError();
 }
 

@@ -106,6 +106,7 @@ struct Ctx {
   int order_P = -1, order_sb = -1;
   void* host = nullptr;  // pinned staging for small device<->host copies
   size_t host_cap = 0;
+  void* host_dev = nullptr;  // its device address
   hipEvent_t ev[32] = {};
   bool ev_ok = false;
   // The end of the last call's work: a call may return with kernels still
@@ -258,6 +259,13 @@ void grow(DevBuf& b, size_t bytes, const char* name, hipStream_t st) {
   b.pooled = true;
 }
 
+// Device address of pinned staging memory that kernels of the call may write
+// themselves, or nullptr (allocation-free calls stage in pageable memory).
+void* host_stage_dev(Ctx& c) {
+  if (g_carve && g_carve->static_host) return nullptr;
+  return c.host_dev;
+}
+
 void* host_stage(Ctx& c, size_t bytes) {
   if (g_carve && g_carve->static_host) {
     // allocation-free call: the static host array (held under g_noalloc_m)
@@ -275,6 +283,8 @@ void* host_stage(Ctx& c, size_t bytes) {
     size_t want = std::max<size_t>(bytes, 1 << 20);
     hipchk(hipHostMalloc(&c.host, want, hipHostMallocDefault), "hipHostMalloc");
     c.host_cap = want;
+    c.host_dev = nullptr;
+    hipchk(hipHostGetDevicePointer(&c.host_dev, c.host, 0), "hipHostGetDevicePointer");
   }
   return c.host;
 }
@@ -374,6 +384,17 @@ __global__ void k_offsets_ok(const uint64_t* off, uint64_t n, unsigned int* bad)
   if (i < n && off[i + 1] < off[i]) atomicOr(bad, 1u);
 }
 
+// The same check for a plain call, with the first and last offset: info[0],
+// info[1], and info[2] != 0 if decreasing. info is in host memory, zeroed by the
+// host, so that nothing is cleared or copied by a launch of its own.
+__global__ void k_offsets_info(const uint64_t* off, uint64_t n, uint64_t* info) {
+  uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0) {
+    info[0] = off[0];
+    info[1] = off[n];
+  }
+  if (i < n && off[i + 1] < off[i]) info[2] = 1;
+}
 
 struct Call {
   const uint8_t* reads;
@@ -620,7 +641,7 @@ void refine_overflowed(Ctx& c, Call& q, kc_stats& S, Timer& tm, uint64_t nl0,
     hipchk(kc::launch_leaf_small(q.words, q.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                  (kc::Leaf*)c.aleaves.p, dst_state, na, (uint32_t*)c.adcnt.p,
                                  (uint32_t*)c.alarge.p, (uint32_t*)c.aovfl.p, q.slots_log2, st,
-                                 q.o.mode, true, q.merged),
+                                 q.o.mode, true, q.merged, false),
            "leaf count launch");
     hipchk(kc::launch_leaf_large(q.words, q.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                  (kc::Leaf*)c.aleaves.p, dst_state, na, (uint32_t*)c.adcnt.p,
@@ -809,29 +830,31 @@ struct PipeOut {
   uint32_t* set;  // batch form only
   uint64_t cap;
   bool concat = true;  // false: stop after the output offsets
+  bool zero_state = false;      // the pipeline clears its state first
+  kc::DevState* pub = nullptr;  // device-visible host memory that receives the state
 };
 
 void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, const PipeOut& out,
                       hipStream_t st) {
   // item classes of the split scatter (one when a leaf's end is its cursor's last value)
   const int ncls = p.merge_cshift ? 1 : kc::kXcds;
-  hipchk(kc::launch_fill_u64((unsigned long long*)c.hist.p, (1ull + kc::kXcds) << p.sb, 0, st),
-         "fill launch");
+  const kc::ZeroRanges z = {
+      {(unsigned long long*)c.hist.p, (unsigned long long*)c.subhist.p, (unsigned long long*)dstate},
+      {(1ull + kc::kXcds) << p.sb, p.max_leaves * ncls,
+       out.zero_state ? sizeof(kc::DevState) / 8 : 0}};
   hipchk(kc::launch_valid_mask(p.words, (uint64_t*)c.inv.p, (uint64_t*)c.endm.p, p.byte_begin,
-                               p.byte_end, p.k, (uint64_t*)c.valid.p, st),
+                               p.byte_end, p.k, (uint64_t*)c.valid.p, z, st),
          "valid mask launch");
   hipchk(kc::launch_window_hist(p.words, (uint64_t*)c.packed.p, (uint64_t*)c.valid.p,
                                 p.byte_begin, p.byte_end, p.k, p.keybits,
-                                p.sb, p.batch, (unsigned long long*)c.hist.p, &dstate->W,
-                                p.scatter_s, st),
+                                p.sb, p.batch, (unsigned long long*)c.hist.p, p.scatter_s, st),
          "window histogram launch");
   tm.mark(ST_HIST);
   hipchk(kc::launch_plan_shards((unsigned long long*)c.hist.p, p.order, p.sb, p.keybits, p.T, p.H,
                                 kc::split_tile(p.words, p.split_r), (unsigned long long*)c.sbegin.p,
                                 (unsigned long long*)c.cursor.p, (kc::SplitBin*)c.bins.p,
                                 (kc::SplitItem*)c.items.p, (unsigned long long*)c.itemoff.p,
-                                (unsigned long long*)c.subhist.p, p.max_leaves, p.max_items,
-                                ncls, dstate, st),
+                                (unsigned long long*)c.subhist.p, p.max_items, dstate, st),
          "plan_shards launch");
   hipchk(kc::launch_window_scatter(p.words, (uint64_t*)c.packed.p, (uint64_t*)c.valid.p,
                                    p.byte_begin, p.byte_end, p.k, p.keybits,
@@ -844,10 +867,12 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
                                p.max_leaves, st),
          "split histogram launch");
   tm.mark(ST_SPLIT_HIST);
-  hipchk(kc::launch_plan_leaves((unsigned long long*)c.hist.p, (unsigned long long*)c.sbegin.p,
+  hipchk(kc::launch_plan_leaves(p.words, (unsigned long long*)c.hist.p, (unsigned long long*)c.sbegin.p,
                                 (kc::SplitBin*)c.bins.p, p.sb, (unsigned long long*)c.subhist.p,
                                 (kc::Leaf*)c.leaves.p, (unsigned long long*)c.cursor2.p,
-                                p.merge_cshift, ncls, p.max_leaves, st),
+                                p.merge_cshift, ncls, p.max_leaves, dstate, p.max_leaves,
+                                (uint32_t*)c.dcnt.p, (uint32_t*)c.large.p, (uint32_t*)c.ovfl.p,
+                                p.slots_log2, p.mode, st),
          "plan_leaves launch");
   hipchk(kc::launch_split_scatter(p.words, c.bufA.p, c.bufB.p, (kc::SplitItem*)c.items.p, dstate,
                                   p.max_items, (kc::SplitBin*)c.bins.p,
@@ -862,7 +887,7 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
   hipchk(kc::launch_leaf_small(p.words, p.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                (kc::Leaf*)c.leaves.p, dstate, p.max_leaves, (uint32_t*)c.dcnt.p,
                                (uint32_t*)c.large.p, (uint32_t*)c.ovfl.p, p.slots_log2, st,
-                               p.mode, false, p.merge_cshift != 0),
+                               p.mode, false, p.merge_cshift != 0, p.merge_cshift == 0),
          "leaf count launch");
   tm.mark(ST_LEAF_SMALL);
   hipchk(kc::launch_leaf_large(p.words, p.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
@@ -877,7 +902,7 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
          "leaf count launch");
   tm.mark(ST_LEAF_SECOND);
   hipchk(kc::launch_plan_out((uint32_t*)c.dcnt.p, dstate, (unsigned long long*)c.bsum.p,
-                             p.max_leaves, (unsigned long long*)c.outoff.p, st),
+                             p.max_leaves, (unsigned long long*)c.outoff.p, st, out.pub),
          "plan_out launch");
   tm.mark(ST_OUT);
   if (!out.concat) return;
@@ -968,6 +993,9 @@ const int* device_order(Ctx& c, const Call& q, kc_stats& S, hipStream_t st) {
   return (const int*)c.order.p;
 }
 
+// Host staging of a plain call: the offsets' check, then a copy of the state.
+constexpr size_t kInfoBytes = 64;
+
 // fixed: the context of an allocation-free call (buffers carved from the
 // static scratch), instead of the calling thread's arena.
 int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, int k, int P,
@@ -999,20 +1027,20 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
 
   // ---- offsets: first/last, monotonicity (host sync 1 of 2)
   grow(c.state, sizeof(kc::DevState), "device state", st);
-  hipchk(kc::launch_fill_u64((unsigned long long*)c.state.p, sizeof(kc::DevState) / 8, 0, st),
-         "fill launch");
-  if (n_reads) {
-    const unsigned g = (unsigned)((n_reads + 255) / 256);
-    hipLaunchKernelGGL(k_offsets_ok, dim3(g), dim3(256), 0, st, offsets, n_reads,
-                       &((kc::DevState*)c.state.p)->overflow);
+  uint64_t* h = (uint64_t*)host_stage(c, kInfoBytes + sizeof(kc::DevState));
+  uint64_t* const h_dev = (uint64_t*)host_stage_dev(c);
+  const unsigned og = (unsigned)((n_reads + 256) / 256);
+  if (h_dev) {
+    h[2] = 0;
+    hipLaunchKernelGGL(k_offsets_info, dim3(og), dim3(256), 0, st, offsets, n_reads, h_dev);
     hipchk(hipGetLastError(), "offsets check launch");
+  } else {
+    hipchk(kc::launch_fill_u64((unsigned long long*)c.state.p, 3, 0, st), "fill launch");
+    hipLaunchKernelGGL(k_offsets_info, dim3(og), dim3(256), 0, st, offsets, n_reads,
+                       (uint64_t*)c.state.p);
+    hipchk(hipGetLastError(), "offsets check launch");
+    hipchk(hipMemcpyAsync(h, c.state.p, 24, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
   }
-  uint64_t* h = (uint64_t*)host_stage(c, 64);
-  hipchk(hipMemcpyAsync(h, offsets, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-  hipchk(hipMemcpyAsync(h + 1, offsets + n_reads, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-  hipchk(hipMemcpyAsync(h + 2, &((kc::DevState*)c.state.p)->overflow, 4, hipMemcpyDeviceToHost,
-                        st),
-         "hipMemcpyAsync");
   hipchk(hipStreamSynchronize(st), "hipStreamSynchronize");
   const uint64_t off0 = h[0], offn = h[1];
   if ((uint32_t)h[2] != 0 || offn < off0) fail(KC_E_INVAL, "offsets must be non-decreasing");
@@ -1056,9 +1084,18 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
                          (uint64_t*)c.inv.p, (uint64_t*)c.endm.p, nchunks, st),
          "pack launch");
   tm.mark(ST_PACK);
-  enqueue_pipeline(c, p, dstate, tm, PipeOut{out_keys, out_counts, nullptr, cap, !oa}, st);
+  PipeOut po{out_keys, out_counts, nullptr, cap, !oa};
+  po.zero_state = true;
+  po.pub = h_dev ? (kc::DevState*)((char*)h_dev + kInfoBytes) : nullptr;
+  enqueue_pipeline(c, p, dstate, tm, po, st);
   q.concat_leaves = p.max_leaves;
-  kc::DevState ds = read_state(c, st);  // host sync 2 of 2 (3 with an output allocator)
+  kc::DevState ds;  // host sync 2 of 2 (3 with an output allocator)
+  if (po.pub) {
+    hipchk(hipStreamSynchronize(st), "hipStreamSynchronize");
+    std::memcpy(&ds, (const char*)h + kInfoBytes, sizeof(ds));
+  } else {
+    ds = read_state(c, st);
+  }
   S.n_levels = 1;
   S.n_leaves = ds.n_leaves;
   // the block-wide leaf kernel's own launch (refinement launches are counted apart)
