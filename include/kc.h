@@ -357,7 +357,7 @@ void kc_pred_free(kc_predictor* pred);
  *   not overlap the inputs; *n_out receives the number of pairs. KC_E_OVERFLOW
  *   if a sum exceeds 2^32-1. Lets inputs larger than device memory be counted
  *   in pieces whose results are merged. Synchronous on stream.
- * The temporaries of kc_merge_counts (24 bytes per 2,048 / words pairs of na +
+ * The temporaries of kc_spectrum (8 bytes a bin), kc_merge_counts (24 bytes per 2,048 / words pairs of na +
  * nb) and kc_filter_min_count sit in one device buffer per host thread, part of the
  * thread's scratch arena: it grows stream-ordered from the library pool as
  * needed and is kept between calls (kc_release_scratch frees it).

@@ -89,12 +89,17 @@ int count_in_block(WorkerArena* wa, void* block, uint64_t block_bytes, Slab* spi
                    const kc_options* opt, hipStream_t st, const OutAlloc& oa, uint64_t* n_out,
                    kc_stats* stats, std::string* err);
 
-// Device temporaries of the merge and the filter: a buffer of the calling
+// Device temporaries of the merge, the filter, the spectrum and the parser: a buffer of the calling
 // thread's context on the current device, grown stream-ordered on st from the
 // library pool and kept between calls (the callers are synchronous, so the
 // buffer is idle when a call starts). Returns nullptr on failure, with the
 // error message in *err and its status in *code.
 void* thread_scratch(size_t bytes, hipStream_t st, std::string* err, int* code) noexcept;
+
+// Pinned host memory of the calling thread's context, at least `bytes` bytes,
+// for results of its synchronous calls; *dev receives its device address.
+// Returns nullptr on failure as thread_scratch does.
+void* thread_pinned(size_t bytes, void** dev, std::string* err, int* code) noexcept;
 
 // The library's stream-ordered memory pool of a device (created on first
 // use): the count arenas of plain calls come from it. It keeps the blocks

@@ -6,6 +6,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <cstring>
 #include <string>
 
 #include "../../include/kc.h"
@@ -17,23 +18,59 @@ constexpr int kTB = 256;
 constexpr int kPer = 16;  // items per thread in the compaction
 constexpr int kTile = kTB * kPer;
 constexpr uint32_t kLdsBins = 4096;
+constexpr unsigned kSpectrumGrid = 1024;
+constexpr size_t kPinBytes = 1 << 20;
+
+// Counts [i, i + 4) of an array of n, past its end 0; one 16-byte load where
+// the array is aligned and all four are in range.
+__device__ __forceinline__ uint4 counts4(const uint32_t* __restrict__ counts, uint64_t i,
+                                         uint64_t n, bool aligned) {
+  if (aligned && i + 4 <= n) return *reinterpret_cast<const uint4*>(counts + i);
+  uint4 v = make_uint4(0, 0, 0, 0);
+  if (i < n) v.x = counts[i];
+  if (i + 1 < n) v.y = counts[i + 1];
+  if (i + 2 < n) v.z = counts[i + 2];
+  if (i + 3 < n) v.w = counts[i + 3];
+  return v;
+}
 
 // Spectrum: bins 1..max_count-1 hold exact counts, bin max_count everything
-// at or above it. Small bin indices are counted in LDS first.
+// at or above it. Small bin indices are counted in LDS first. Bin 1 (a k-mer
+// of a read error mostly occurs once: four of five pairs) is counted in a
+// register, or every lane of a wave would add to one LDS word; and the grid is
+// small, as each workgroup adds its bins to the same words of hist, 12 ns an
+// atomic (4,096 workgroups of one count a load: 36M counts 113 us, so 47 us).
 __global__ void __launch_bounds__(kTB) k_spectrum(const uint32_t* __restrict__ counts, uint64_t n,
-                                                  uint32_t max_count,
+                                                  uint32_t max_count, bool aligned,
                                                   unsigned long long* __restrict__ hist) {
   __shared__ uint32_t h[kLdsBins];
   const uint32_t nl = max_count + 1 < kLdsBins ? max_count + 1 : kLdsBins;
   for (uint32_t i = threadIdx.x; i < nl; i += kTB) h[i] = 0;
   __syncthreads();
-  const uint64_t stride = (uint64_t)gridDim.x * kTB;
-  for (uint64_t i = (uint64_t)blockIdx.x * kTB + threadIdx.x; i < n; i += stride) {
-    const uint32_t c = counts[i];
+  uint32_t ones = 0;  // below 2^32: a thread takes n / (threads of the grid) counts
+  const auto add = [&](uint32_t c) {
     const uint32_t b = c < max_count ? c : max_count;
-    if (b < nl) atomicAdd(&h[b], 1u);
+    if (b == 1) ++ones;
+    else if (b < nl) atomicAdd(&h[b], 1u);
     else atomicAdd(&hist[b], 1ull);
+  };
+  constexpr int U = 4;
+  const uint64_t stride = (uint64_t)gridDim.x * kTB * 4;
+  for (uint64_t i0 = ((uint64_t)blockIdx.x * kTB + threadIdx.x) * 4; i0 < n; i0 += U * stride) {
+    uint4 v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = counts4(counts, i0 + u * stride, n, aligned);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t i = i0 + u * stride;
+      if (i < n) add(v[u].x);
+      if (i + 1 < n) add(v[u].y);
+      if (i + 2 < n) add(v[u].z);
+      if (i + 3 < n) add(v[u].w);
+    }
   }
+  for (int off = 32; off > 0; off >>= 1) ones += __shfl_xor(ones, off);
+  if ((threadIdx.x & 63) == 0 && ones) atomicAdd(&h[1], ones);
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < nl; i += kTB)
     if (h[i]) atomicAdd(&hist[i], (unsigned long long)h[i]);
@@ -46,29 +83,39 @@ __global__ void k_zero(unsigned long long* p, uint64_t n) {
 
 // Compaction, step 1: kept pairs per tile.
 __global__ void __launch_bounds__(kTB) k_keep_count(const uint32_t* __restrict__ counts,
-                                                    uint64_t n, uint32_t min_count,
+                                                    uint64_t n, uint32_t min_count, bool aligned,
                                                     unsigned long long* __restrict__ tsum) {
-  __shared__ uint32_t s;
-  if (threadIdx.x == 0) s = 0;
-  __syncthreads();
+  __shared__ uint32_t wsum[kTB / 64];
   const uint64_t base = (uint64_t)blockIdx.x * kTile;
+  uint4 v[kPer / 4];
+#pragma unroll
+  for (int j = 0; j < kPer / 4; ++j)
+    v[j] = counts4(counts, base + ((uint64_t)j * kTB + threadIdx.x) * 4, n, aligned);
   uint32_t c = 0;
-  for (int j = 0; j < kPer; ++j) {
-    const uint64_t i = base + (uint64_t)j * kTB + threadIdx.x;
-    c += (i < n && counts[i] >= min_count) ? 1u : 0u;
+#pragma unroll
+  for (int j = 0; j < kPer / 4; ++j) {
+    const uint64_t i = base + ((uint64_t)j * kTB + threadIdx.x) * 4;
+    c += (i < n && v[j].x >= min_count) + (i + 1 < n && v[j].y >= min_count) +
+         (i + 2 < n && v[j].z >= min_count) + (i + 3 < n && v[j].w >= min_count);
   }
-  atomicAdd(&s, c);
+  for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off);
+  if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = c;
   __syncthreads();
-  if (threadIdx.x == 0) tsum[blockIdx.x] = s;
+  if (threadIdx.x == 0) {
+    uint32_t all = 0;
+    for (int w = 0; w < kTB / 64; ++w) all += wsum[w];
+    tsum[blockIdx.x] = all;
+  }
 }
 
-// Step 2 (one block): exclusive scan of the tile sums; tsum[nt] = total. Rows
+// Step 2 (one block): exclusive scan of the tile sums; *total (host
+// memory) = their sum. Rows
 // of kScanTB * 8 sums, eight consecutive ones a thread, loaded while the row
 // before is still being scanned (a chain of latencies, not of bytes: 9,500 sums
 // 23.3 us with one thread adding up 1,024 partial sums, 21,800 sums 18.9 us so).
 constexpr int kScanTB = 1024, kScanPer = 8;
 __global__ void __launch_bounds__(kScanTB) k_scan_tiles(unsigned long long* __restrict__ tsum,
-                                                        uint64_t nt) {
+                                                        uint64_t nt, uint64_t* total) {
   __shared__ unsigned long long wtot[2][kScanTB / 64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   unsigned long long carry = 0;
@@ -111,39 +158,67 @@ __global__ void __launch_bounds__(kScanTB) k_scan_tiles(unsigned long long* __re
       if (i < nt) tsum[i] = before + (x - s) + now[q];
     }
   }
-  if (threadIdx.x == 0) tsum[nt] = carry;
+  if (threadIdx.x == 0) *total = carry;
 }
 
-// Step 3: each tile writes its kept pairs in order from its offset.
+// Step 3: each tile writes its kept pairs in order from its offset. A wave
+// takes kTile / 4 consecutive pairs, four a lane and row, and ranks them by
+// ballots (the kept pairs of earlier lanes, then the lane's own earlier ones):
+// one exchange between the waves per tile instead of two barriers per row
+// (36M pairs of one word, 18% kept: 145 -> 110 us, bound by the keys of kept
+// pairs, which touch four of five 64-byte segments).
+template <int W>
 __global__ void __launch_bounds__(kTB) k_keep_write(const uint64_t* __restrict__ keys,
                                                     const uint32_t* __restrict__ counts,
-                                                    uint64_t n, int words, uint32_t min_count,
+                                                    uint64_t n, uint32_t min_count, bool aligned,
                                                     const unsigned long long* __restrict__ tsum,
                                                     uint64_t* __restrict__ out_keys,
                                                     uint32_t* __restrict__ out_counts) {
-  __shared__ uint32_t wsum[kTB / 64 + 1];
-  const uint64_t base = (uint64_t)blockIdx.x * kTile;
+  constexpr int ROWS = kPer / 4;
+  __shared__ uint32_t wsum[kTB / 64];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint64_t base = (uint64_t)blockIdx.x * kTile + (uint64_t)w * (kTile / (kTB / 64));
+  uint32_t c[ROWS][4];
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    const uint4 v = counts4(counts, base + (uint64_t)j * 256 + lane * 4, n, aligned);
+    c[j][0] = v.x;
+    c[j][1] = v.y;
+    c[j][2] = v.z;
+    c[j][3] = v.w;
+  }
+  const unsigned long long below = (1ull << lane) - 1;
+  uint32_t rank[ROWS], keep[ROWS], sum = 0;  // rank of the lane's first kept pair in the wave
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    keep[j] = 0;
+    rank[j] = sum;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint64_t i = base + (uint64_t)j * 256 + lane * 4 + q;
+      const bool k = i < n && c[j][q] >= min_count;
+      const unsigned long long m = __ballot(k);
+      rank[j] += __popcll(m & below);
+      sum += __popcll(m);
+      keep[j] |= (k ? 1u : 0u) << q;
+    }
+  }
+  if (lane == 0) wsum[w] = sum;
+  __syncthreads();
   unsigned long long at = tsum[blockIdx.x];
-  for (int j = 0; j < kPer; ++j) {
-    const uint64_t i = base + (uint64_t)j * kTB + threadIdx.x;
-    const bool keep = i < n && counts[i] >= min_count;
-    // rank among the kept items of this row of the tile, in index order
-    const unsigned long long m = __ballot(keep);
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) wsum[w] = (uint32_t)__popcll(m);
-    __syncthreads();
-    uint32_t before = 0, row = 0;
-    for (int v = 0; v < kTB / 64; ++v) {
-      if (v < w) before += wsum[v];
-      row += wsum[v];
+  for (int v = 0; v < w; ++v) at += wsum[v];
+#pragma unroll
+  for (int j = 0; j < ROWS; ++j) {
+    unsigned long long o = at + rank[j];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (!(keep[j] >> q & 1)) continue;
+      const uint64_t i = base + (uint64_t)j * 256 + lane * 4 + q;
+      out_counts[o] = c[j][q];
+#pragma unroll
+      for (int x = 0; x < W; ++x) out_keys[W * o + x] = keys[W * i + x];
+      ++o;
     }
-    if (keep) {
-      const unsigned long long o = at + before + __popcll(m & ((1ull << lane) - 1));
-      out_counts[o] = counts[i];
-      for (int q = 0; q < words; ++q) out_keys[words * o + q] = keys[words * i + q];
-    }
-    at += row;
-    __syncthreads();
   }
 }
 
@@ -177,6 +252,21 @@ void* post_scratch(size_t bytes, hipStream_t st) {
   return p;
 }
 
+// Host words that kernels write their results to (with their device address):
+// the calling thread's pinned staging memory.
+uint64_t* post_words(size_t n, uint64_t** dev) {
+  std::string err;
+  int code = KC_E_NOMEM;
+  void* d = nullptr;
+  uint64_t* p = (uint64_t*)kc::thread_pinned(n * 8, &d, &err, &code);
+  if (!p) {
+    kc::set_last_error(err);
+    throw Fail{code};
+  }
+  *dev = (uint64_t*)d;
+  return p;
+}
+
 unsigned grid_of(uint64_t n, uint64_t per, unsigned cap) {
   const uint64_t g = (n + per - 1) / per;
   return (unsigned)(g < 1 ? 1 : (g > cap ? cap : g));
@@ -194,23 +284,25 @@ int kc_spectrum(const uint32_t* counts, uint64_t n, uint32_t max_count, uint64_t
   if (n && !counts) return bad("counts is NULL");
   if (max_count < 1 || max_count > (1u << 24)) return bad("max_count must be in [1, 2^24]");
   const hipStream_t st = (hipStream_t)stream;
-  void* d = nullptr;
   try {
-    chk(hipMallocAsync(&d, (size_t)(max_count + 1) * 8, st), "hipMallocAsync");
-    unsigned long long* hist = (unsigned long long*)d;
+    const size_t bytes = (size_t)(max_count + 1) * 8;
+    unsigned long long* hist = (unsigned long long*)post_scratch(bytes, st);
     hipLaunchKernelGGL(k_zero, dim3(grid_of(max_count + 1, 256, 1u << 20)), dim3(256), 0, st,
                        hist, (uint64_t)max_count + 1);
     if (n)
-      hipLaunchKernelGGL(k_spectrum, dim3(grid_of(n, (uint64_t)kTB * 16, 4096)), dim3(kTB), 0, st,
-                         counts, n, max_count, hist);
+      hipLaunchKernelGGL(k_spectrum, dim3(grid_of(n, (uint64_t)kTB * 16, kSpectrumGrid)),
+                         dim3(kTB), 0, st, counts, n, max_count, ((uintptr_t)counts & 15) == 0,
+                         hist);
     chk(hipGetLastError(), "spectrum launch");
-    chk(hipMemcpyAsync(host_hist, hist, (size_t)(max_count + 1) * 8, hipMemcpyDeviceToHost, st),
+    // through pinned memory where it is small: a copy to pageable memory is
+    // staged piece by piece
+    uint64_t* dev = nullptr;
+    uint64_t* const pin = bytes <= kPinBytes ? post_words(max_count + 1, &dev) : nullptr;
+    chk(hipMemcpyAsync(pin ? pin : host_hist, hist, bytes, hipMemcpyDeviceToHost, st),
         "hipMemcpyAsync");
-    chk(hipFreeAsync(d, st), "hipFreeAsync");
-    d = nullptr;
     chk(hipStreamSynchronize(st), "hipStreamSynchronize");
+    if (pin) std::memcpy(host_hist, pin, bytes);
   } catch (const Fail& f) {
-    if (d) (void)hipFreeAsync(d, st);
     return f.code;
   }
   return KC_OK;
@@ -230,18 +322,26 @@ int kc_filter_min_count(const uint64_t* keys, const uint32_t* counts, uint64_t n
   const uint64_t nt = (n + kTile - 1) / kTile;
   void* d = nullptr;
   try {
-    d = post_scratch((size_t)(nt + 1) * 8, st);
+    d = post_scratch((size_t)nt * 8, st);
     unsigned long long* tsum = (unsigned long long*)d;
+    uint64_t* total_dev = nullptr;
+    const uint64_t* const total = post_words(1, &total_dev);
+    const bool aligned = ((uintptr_t)counts & 15) == 0;
     hipLaunchKernelGGL(k_keep_count, dim3((unsigned)nt), dim3(kTB), 0, st, counts, n, min_count,
-                       tsum);
-    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanTB), 0, st, tsum, nt);
-    hipLaunchKernelGGL(k_keep_write, dim3((unsigned)nt), dim3(kTB), 0, st, keys, counts, n, words,
-                       min_count, tsum, out_keys, out_counts);
+                       aligned, tsum);
+    hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanTB), 0, st, tsum, nt, total_dev);
+    if (words == 4)
+      hipLaunchKernelGGL(k_keep_write<4>, dim3((unsigned)nt), dim3(kTB), 0, st, keys, counts, n,
+                         min_count, aligned, tsum, out_keys, out_counts);
+    else if (words == 2)
+      hipLaunchKernelGGL(k_keep_write<2>, dim3((unsigned)nt), dim3(kTB), 0, st, keys, counts, n,
+                         min_count, aligned, tsum, out_keys, out_counts);
+    else
+      hipLaunchKernelGGL(k_keep_write<1>, dim3((unsigned)nt), dim3(kTB), 0, st, keys, counts, n,
+                         min_count, aligned, tsum, out_keys, out_counts);
     chk(hipGetLastError(), "filter launch");
-    uint64_t total = 0;
-    chk(hipMemcpyAsync(&total, tsum + nt, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
     chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-    *n_out = total;
+    *n_out = *total;
   } catch (const Fail& f) {
     return f.code;
   }
@@ -393,7 +493,7 @@ __global__ void __launch_bounds__(kTB) k_merge(const uint64_t* __restrict__ ak,
                                                unsigned long long* __restrict__ tsum,
                                                uint64_t* __restrict__ out_keys,
                                                uint32_t* __restrict__ out_counts,
-                                               unsigned int* __restrict__ overflow) {
+                                               uint64_t* overflow) {
   constexpr int ITEMS = kMergeItems<W>, TILE = kMergeTileOf<W>;
   typedef typename KeyOf<W>::type Key;
   __shared__ uint64_t sk[W * (TILE + 1)];      // a's keys, then b's; then the outputs'
@@ -500,7 +600,7 @@ __global__ void __launch_bounds__(kTB) k_merge(const uint64_t* __restrict__ ak,
     key_put<W>(sk, at + s, key[s]);
     sc[at + s] = cnt[s];
   }
-  if (over) atomicOr(overflow, 1u);
+  if (over) *overflow = 1;
   __syncthreads();
   const unsigned long long o = tsum[blockIdx.x];
 #pragma unroll
@@ -519,14 +619,14 @@ template <int W>
 void launch_merge(const uint64_t* ak, const uint32_t* ac, uint64_t na, const uint64_t* bk,
                   const uint32_t* bc, uint64_t nb, uint64_t nblk, unsigned long long* part,
                   unsigned long long* tsum, uint64_t* out_keys, uint32_t* out_counts,
-                  unsigned int* ovf, hipStream_t st) {
+                  uint64_t* result, hipStream_t st) {
   hipLaunchKernelGGL(k_merge_part<W>, dim3(grid_of(nblk + 1, kTB, ~0u)), dim3(kTB), 0,
                      st, ak, na, bk, nb, nblk, part);
   hipLaunchKernelGGL((k_merge<W, false>), dim3((unsigned)nblk), dim3(kTB), 0, st, ak, ac, bk, bc,
-                     part, tsum, out_keys, out_counts, ovf);
-  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanTB), 0, st, tsum, nblk);
+                     part, tsum, out_keys, out_counts, result + 1);
+  hipLaunchKernelGGL(k_scan_tiles, dim3(1), dim3(kScanTB), 0, st, tsum, nblk, result);
   hipLaunchKernelGGL((k_merge<W, true>), dim3((unsigned)nblk), dim3(kTB), 0, st, ak, ac, bk, bc,
-                     part, tsum, out_keys, out_counts, ovf);
+                     part, tsum, out_keys, out_counts, result + 1);
 }
 
 }  // namespace
@@ -551,31 +651,30 @@ extern "C" int kc_merge_counts(const uint64_t* a_keys, const uint32_t* a_counts,
   if (nblk > 0x7fffffffull) return bad("too many pairs");
   void* d = nullptr;
   try {
-    // tile sums (and their total), splits, the overflow flag
-    d = post_scratch((nblk + 1 + 2 * (nblk + 1) + 1) * 8, st);
+    // tile sums, splits
+    d = post_scratch((nblk + 2 * (nblk + 1)) * 8, st);
     unsigned long long* tsum = (unsigned long long*)d;
-    unsigned long long* part = tsum + nblk + 1;
-    unsigned int* ovf = (unsigned int*)(part + 2 * (nblk + 1));
-    hipLaunchKernelGGL(k_zero, dim3(1), dim3(64), 0, st, (unsigned long long*)ovf, (uint64_t)1);
+    unsigned long long* part = tsum + nblk;
+    // the number of results and whether a count passed 2^32-1, in host memory
+    uint64_t* res_dev = nullptr;
+    volatile uint64_t* const res = post_words(2, &res_dev);
+    res[1] = 0;
     if (words == 4)
       launch_merge<4>(a_keys, a_counts, na, b_keys, b_counts, nb, nblk, part, tsum, out_keys,
-                      out_counts, ovf, st);
+                      out_counts, res_dev, st);
     else if (words == 2)
       launch_merge<2>(a_keys, a_counts, na, b_keys, b_counts, nb, nblk, part, tsum, out_keys,
-                      out_counts, ovf, st);
+                      out_counts, res_dev, st);
     else
       launch_merge<1>(a_keys, a_counts, na, b_keys, b_counts, nb, nblk, part, tsum, out_keys,
-                      out_counts, ovf, st);
+                      out_counts, res_dev, st);
     chk(hipGetLastError(), "merge launch");
-    uint64_t h[2] = {0, 0};
-    chk(hipMemcpyAsync(&h[0], tsum + nblk, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    chk(hipMemcpyAsync(&h[1], ovf, 4, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
     chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-    if ((uint32_t)h[1]) {
+    if (res[1]) {
       kc::set_last_error("a merged count exceeds 2^32-1");
       return KC_E_OVERFLOW;
     }
-    *n_out = h[0];
+    *n_out = res[0];
   } catch (const Fail& f) {
     return f.code;
   }

@@ -1756,6 +1756,22 @@ void* thread_scratch(size_t bytes, hipStream_t st, std::string* err, int* code) 
   return nullptr;
 }
 
+void* thread_pinned(size_t bytes, void** dev, std::string* err, int* code) noexcept {
+  try {
+    Ctx& c = context();
+    void* p = host_stage(c, bytes);
+    *dev = c.host_dev;
+    return p;
+  } catch (const Fail& f) {
+    if (err) *err = g_err;
+    if (code) *code = f.code;
+  } catch (...) {
+    if (err) *err = "pinned staging: allocation failed";
+    if (code) *code = KC_E_NOMEM;
+  }
+  return nullptr;
+}
+
 void trim_device_pool(int device) {
   free_orphans();  // arenas of ended threads (a server's workers) first
   hipMemPool_t p = nullptr;
