@@ -60,8 +60,8 @@ typedef struct kc_options {
   int shard_bits;      /* log2 of the number of first-level key-range shards
                           (owner buckets are unions of shards); 1..10 */
   int leaf_target;     /* target valid windows per leaf partition when splitting
-                          (automatic: 1.5 x the largest table for k <= 32, 0.75 x
-                          for wider keys) */
+                          (automatic: 1.5 x the largest table for k <= 32, 1 x for
+                          k <= 64, 0.75 x for wider keys) */
   int leaf_attempt;    /* partitions up to this many windows are counted directly */
   int table_slots_log2;/* log2 of the largest LDS open-addressing table per leaf
                           (10..12 for k<=32, 10..11 for k>32) */
@@ -99,7 +99,7 @@ typedef struct kc_stats {
   uint64_t n_leaves;       /* leaf partitions counted */
   uint64_t n_levels;       /* partitioning levels below the shard level */
   uint64_t n_overflow;     /* leaf attempts that overflowed their table and were split
-                              (one-word keys: after a second count with a table twice
+                              (after a second count with a table twice
                               as large also overflowed) */
   uint64_t max_leaf_windows;
   uint64_t max_owner_windows; /* windows in the largest of the P owner buckets */
@@ -109,7 +109,7 @@ typedef struct kc_stats {
                                launch (leaves above the one-wave size) */
   uint64_t large_distinct;  /* distinct keys that launch wrote */
   uint64_t second_records;  /* records counted by the second count of overflowed
-                               leaves (one-word keys), refinement excluded */
+                               leaves, refinement excluded */
   uint64_t second_distinct; /* distinct keys it wrote */
   double   ms_total;        /* host wall time of the call */
   double   ms_stage[12];    /* timing=1, device events on the call's stream (ms):
@@ -118,7 +118,7 @@ typedef struct kc_stats {
                                5 small-leaf count (with leaf classification), 6 large-leaf
                                count, 7 output offsets, 8 concat, 9 self-check, 10 refinement
                                of overflowed leaves (its splits and part counts), 11 second
-                               count of the leaves whose table overflowed (one-word keys) */
+                               count of the leaves whose table overflowed */
 } kc_stats;
 
 /* Count canonical k-mers (plain form).

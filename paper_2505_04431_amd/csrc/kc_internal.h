@@ -191,12 +191,12 @@ hipError_t launch_leaf_ends(Leaf* leaves, const unsigned long long* cursor, cons
 // refine: the leaves are parts of overflowed leaves (first table full size;
 // the launches are separate kernel instantiations, so profiles tell them apart).
 // merged: leaves may hold pre-aggregated records (one-word keys).
-// ovf_list (max_leaves entries, or nullptr): one-word keys in mode 0 list
-// there the leaves whose table overflows, for launch_leaf_second.
+// ovf_list (max_leaves entries, or nullptr): in mode 0 the leaves whose table
+// overflows are listed there, for launch_leaf_second.
 // With few leaves (max_leaves) none is small: all go to the block-wide kernel.
 // launch_leaf_small also classifies the leaves unless launch_plan_leaves has
 // (classified): large ones into large_list;
-// for one-word keys in mode 0 with ovf_list (and the second count running,
+// in mode 0 with ovf_list (and the second count running,
 // slots_log2 below its table), leaves of more than 8 << slots_log2 records
 // straight into ovf_list for launch_leaf_second.
 hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,

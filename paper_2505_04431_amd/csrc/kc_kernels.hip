@@ -1402,8 +1402,10 @@ __device__ __forceinline__ uint32_t leaf_slots(uint64_t n, uint32_t cmax_rt) {
   return c < (uint32_t)TB ? (uint32_t)TB : c;
 }
 
-// Epilogue shared by both key widths: the table (tk, tc) has been filled with
-// Cn slots. The distinct keys are grouped by a counting sort on the key bits
+// Epilogue shared by all key widths: the table has been filled with Cn slots;
+// table.load(s, ref, count) reads slot s (count 0: empty), table.bits(ref, shift,
+// nbits) gives key bits of what the slot refers to and table.key(ref) its key;
+// tk and tc, where the table may have been, then hold the distinct keys. These are grouped by a counting sort on the key bits
 // just below the leaf's common prefix; each key then finds its place inside
 // its group by counting the smaller keys of the group, and the pair is written
 // to dst/tmp_cnt at [begin, begin + d) in key order. Keys of one group share a
@@ -1411,25 +1413,26 @@ __device__ __forceinline__ uint32_t leaf_slots(uint64_t n, uint32_t cmax_rt) {
 // copies of one k-mer), so groups are not always tiny; a group larger than
 // kRankMax switches the leaf to a bitonic sort. Cn >> GSHIFT groups: aux holds
 // 2 * Cn >> GSHIFT counters. Returns d.
-constexpr uint32_t kRankMax = 256;
+// (wider keys: groups of up to 1,024 are still ranked sooner
+// than a bitonic sort moves its 20 to 36 bytes a key: the large leaves of
+// 1,000,000 reads at k = 100, 12% repeats, 3.36 -> 2.84 ms)
+template <typename K> constexpr uint32_t kRankMax = sizeof(K) > 8 ? 1024 : 256;
 
-template <typename K, typename C, int TB, int PER, int GSHIFT>
-__device__ __forceinline__ uint32_t leaf_sort_write(K* tk, C* tc, uint32_t* aux, uint32_t* wsum,
-                                                    uint32_t* s_max, uint32_t Cn, int keybits,
-                                                    int prefix_bits, K* __restrict__ dst,
+template <typename K, int TB, int PER, int GSHIFT, typename Table>
+__device__ __forceinline__ uint32_t leaf_sort_write(K* tk, uint32_t* tc, uint32_t* aux,
+                                                    uint32_t* wsum, uint32_t* s_max, uint32_t Cn,
+                                                    int keybits, int prefix_bits,
+                                                    K* __restrict__ dst,
                                                     uint32_t* __restrict__ tmp_cnt,
-                                                    uint64_t begin, bool (*occupied)(C)) {
-  K rk[PER];
-  C rc[PER];
+                                                    uint64_t begin, const Table& table) {
+  typename Table::Ref rk[PER];
+  uint32_t rc[PER];
   uint32_t rank[PER], bk[PER];
 #pragma unroll
   for (int j = 0; j < PER; ++j) {  // slot j*TB + tid: consecutive lanes, consecutive slots
     const uint32_t s = (uint32_t)j * TB + threadIdx.x;
     rc[j] = 0;
-    if (s < Cn) {
-      rk[j] = tk[s];
-      rc[j] = tc[s];
-    }
+    if (s < Cn) table.load(s, rk[j], rc[j]);
   }
   int nbk_bits = 31 - __builtin_clz(Cn) - GSHIFT;
   if (nbk_bits > keybits - prefix_bits) nbk_bits = keybits - prefix_bits;
@@ -1443,9 +1446,9 @@ __device__ __forceinline__ uint32_t leaf_sort_write(K* tk, C* tc, uint32_t* aux,
     if ((uint32_t)j * TB >= Cn) break;  // uniform: Cn is a multiple of TB
     // every slot adds 0 or 1 (empty slots add 0 to a spread-out counter), so
     // no branch per slot
-    const bool o = occupied(rc[j]);
+    const bool o = rc[j] != 0;
     const uint32_t s = (uint32_t)j * TB + threadIdx.x;
-    bk[j] = o ? (nbk_bits ? Key<K>::bits(rk[j], shift, nbk_bits) : 0u) : (s & (nbk - 1));
+    bk[j] = o ? (nbk_bits ? table.bits(rk[j], shift, nbk_bits) : 0u) : (s & (nbk - 1));
     rank[j] = atomicAdd(&aux[bk[j]], o ? 1u : 0u);
   }
   __syncthreads();
@@ -1454,26 +1457,27 @@ __device__ __forceinline__ uint32_t leaf_sort_write(K* tk, C* tc, uint32_t* aux,
   const uint32_t* boff = aux + nbk;
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
-    if (occupied(rc[j])) {
+    if (rc[j]) {
       const uint32_t p = boff[bk[j]] + rank[j];
-      tk[p] = rk[j];
+      tk[p] = table.key(rk[j]);
       tc[p] = rc[j];
     }
   }
   __syncthreads();
-  if (maxb <= kRankMax) {
+  if (maxb <= kRankMax<K>) {
     for (uint32_t i = threadIdx.x; i < d; i += TB) {
       const K x = tk[i];
       const uint32_t b = nbk_bits ? Key<K>::bits(x, shift, nbk_bits) : 0u;
       const uint32_t a = boff[b], m = aux[b];
       uint32_t r = 0;
       uint32_t t = a;
+      if constexpr (sizeof(K) <= 16)
       for (; t + 4 <= a + m; t += 4)
         r += (uint32_t)(tk[t] < x) + (uint32_t)(tk[t + 1] < x) + (uint32_t)(tk[t + 2] < x) +
              (uint32_t)(tk[t + 3] < x);
       for (; t < a + m; ++t) r += tk[t] < x;
       dst[begin + a + r] = x;
-      tmp_cnt[begin + a + r] = (uint32_t)tc[i];
+      tmp_cnt[begin + a + r] = tc[i];
     }
     return d;
   }
@@ -1483,16 +1487,13 @@ __device__ __forceinline__ uint32_t leaf_sort_write(K* tk, C* tc, uint32_t* aux,
     tc[i] = 0;
   }
   __syncthreads();
-  bitonic_sort<K, C, TB>(tk, tc, n2);
+  bitonic_sort<K, uint32_t, TB>(tk, tc, n2);
   for (uint32_t i = threadIdx.x; i < d; i += TB) {
     dst[begin + i] = tk[i];
-    tmp_cnt[begin + i] = (uint32_t)tc[i];
+    tmp_cnt[begin + i] = tc[i];
   }
   return d;
 }
-
-__device__ bool occ32(uint32_t c) { return c != 0; }
-__device__ bool occ64(unsigned long long c) { return c != 0; }
 
 // One-word leaf tables: the epilogue's counting sort uses Cn/8 groups (8 KiB
 // of group counters for 4,096 slots instead of 32 KiB with Cn/2), so that
@@ -1510,6 +1511,21 @@ constexpr int kLeafOccWaves = 6;
 // of 768 resident workgroups count as many leaves in less (100 kB of reads:
 // 119 us by one-wave workgroups, 13 us so).
 constexpr uint64_t kFewLeaves = 4096;
+
+// Tables whose slots hold the keys themselves, for the epilogue.
+template <typename K> struct TableK {
+  typedef K Ref;
+  const K* tk;
+  const uint32_t* tc;
+  __device__ __forceinline__ void load(uint32_t s, Ref& r, uint32_t& c) const {
+    r = tk[s];
+    c = tc[s];
+  }
+  __device__ __forceinline__ uint32_t bits(const Ref& r, int shift, int nbits) const {
+    return Key<K>::bits(r, shift, nbits);
+  }
+  __device__ __forceinline__ K key(const Ref& r) const { return r; }
+};
 
 // 64-bit keys: EMPTY (all ones) is never a canonical key for k <= 32, so a
 // slot is claimed by a 64-bit CAS of the key word itself; the count is then
@@ -1685,9 +1701,9 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
       __syncthreads();
       if (threadIdx.x == 0 && s_sum != windows) s_cov = 1;
     }
-    const uint32_t d = leaf_sort_write<unsigned long long, uint32_t, TB, CMAX / TB, kLeafGroupShift>(
+    const uint32_t d = leaf_sort_write<unsigned long long, TB, CMAX / TB, kLeafGroupShift>(
         tk, tc, aux, wsum, &s_max, Cn, keybits, (int)lf.bits, (unsigned long long*)dst, tmp_cnt,
-        lf.begin, occ32);
+        lf.begin, TableK<unsigned long long>{tk, tc});
     if (threadIdx.x == 0) {
       d_out[l] = d;
       if (s_cov) atomicOr(&st->count_overflow, 1u);
@@ -1704,42 +1720,54 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
   }
 }
 
-// 128-bit keys: there is no 128-bit CAS.
-// HI = true (k <= 63): the high word of a key is then never all ones, so a
-//   slot is claimed by a CAS of its high word (all ones = empty); the claimer
-//   writes the low word and publishes it with the count (release). A lane
-//   that finds its high word in a slot whose count is still 0 waits for that
-//   publication (made in the claimer's same pass), then compares the low
-//   word. Counts are 32-bit.
-// HI = false (k = 64, where one key has an all-ones high word): a slot is
-//   claimed through its 64-bit count word: 0 = empty, LOCK = being written;
-//   the claimer writes the key and then publishes the count; others seeing
-//   LOCK retry the same slot.
-// FULL_FIRST only names the launches that count refined parts apart (two-word
-// and wider keys always start with the full table).
-template <typename K, int TB, int CMAX, int R, bool HI, bool FULL_FIRST>
-__global__ void __launch_bounds__(TB) k_leaf_countw(int keybits, K* bufA, K* bufB,
-                                                      uint32_t* __restrict__ tmp_cnt,
-                                                      const Leaf* __restrict__ leaves,
-                                                      DevState* __restrict__ st,
-                                                      uint32_t* __restrict__ d_out,
-                                                      int slots_log2,
-                                                      const uint32_t* __restrict__ list,
-                                                      uint64_t small_max) {
-  static_assert(!HI || std::is_same<K, u128>::value, "high-word claims need 128-bit keys");
-  typedef typename std::conditional<HI, uint32_t, unsigned long long>::type C;
-  __shared__ K tk[CMAX];
-  __shared__ C tc[CMAX];
+// Hashes of the wider keys.
+template <typename K> struct Hash2 {
+  uint32_t pos, tag;  // independent hashes of a key
+  __device__ __forceinline__ explicit Hash2(const K& key) {
+    // multilinear in the key's 32-bit words (Dietzfelbinger): two sums of
+    // words times odd constants, each finished by a multiply-shift
+    constexpr uint32_t c[16] = {0x9E3779B1u, 0x85EBCA77u, 0xC2B2AE3Du, 0x27D4EB2Fu,
+                                0x165667B1u, 0xD3A2646Du, 0xFD7046C5u, 0xB55A4F09u,
+                                0x8CB92BA7u, 0xE6546B65u, 0x9C8F4D2Bu, 0x51ED2703u,
+                                0xA0761D65u, 0xE7037ED1u, 0x8EBC6AF1u, 0x589965CDu};
+    uint32_t w[2 * Key<K>::kWords];
+    __builtin_memcpy(w, &key, sizeof(K));
+    uint32_t a = 0, b = 0;
+#pragma unroll
+    for (int i = 0; i < 2 * Key<K>::kWords; ++i) {
+      a += w[i] * c[i];
+      b += (w[i] ^ (w[i] >> 16)) * c[8 + i];
+    }
+    pos = (a ^ (a >> 15)) * 0x2C1B3C6Du;
+    tag = (b ^ (b >> 15)) * 0x846CA68Bu;
+  }
+};
+
+// 128-bit keys of k <= 63: there is no 128-bit CAS, but the high word of a key
+// is then never all ones, so a slot is claimed by a CAS of its high word (all
+// ones = empty); the claimer writes the low word and publishes it with the
+// count (release). A lane that finds its high word in a slot whose count is
+// still 0 waits for that publication (made in the claimer's same pass), then
+// compares the low word. list, n_list, ovf_list and acc as for one-word keys.
+// (By a 32-bit tag and the keys compared after a barrier: 1.11 against 0.95 ms
+// for the large leaves of 60 MB of 10 kbp reads at k = 55.)
+template <int TB, int CMAX, int R, bool FULL_FIRST>
+__global__ void __launch_bounds__(TB)
+__attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? kLeafOccWaves : 1)))
+k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_cnt,
+                const Leaf* __restrict__ leaves, DevState* __restrict__ st,
+                uint32_t* __restrict__ d_out, int slots_log2, const uint32_t* __restrict__ list,
+                const unsigned long long* __restrict__ n_list, uint32_t* __restrict__ ovf_list,
+                unsigned long long* __restrict__ acc, uint64_t small_max) {
+  __shared__ u128 tk[CMAX];
+  __shared__ uint32_t tc[CMAX];
   __shared__ uint32_t aux[CMAX];
   __shared__ uint32_t wsum[TB / 64];
   __shared__ uint32_t s_nd, s_max, s_cov;
   __shared__ unsigned long long s_sum;
   __shared__ uint32_t s_ovf;  // accessed only through ovf_get / ovf_set
-  const unsigned long long LOCK = 1ull << 63;
   const uint32_t cmax_rt = 1u << slots_log2;
-  // list != nullptr: the leaves listed there (large ones); else every leaf of
-  // at most small_max records.
-  const unsigned long long count = list ? st->n_large : st->n_leaves;
+  const unsigned long long count = list ? *n_list : st->n_leaves;
   unsigned long long my_records = 0, my_distinct = 0;  // thread 0: this workgroup's totals
   for (unsigned long long it = blockIdx.x; it < count; it += gridDim.x) {
     const unsigned long long l = list ? (unsigned long long)list[it] : it;
@@ -1750,18 +1778,15 @@ __global__ void __launch_bounds__(TB) k_leaf_countw(int keybits, K* bufA, K* buf
       continue;
     }
     if (!list && n > small_max) continue;
-    const K* src = lf.buf ? bufB : bufA;
-    K* dst = lf.buf ? bufA : bufB;
-    const uint32_t Cfull = leaf_slots<TB, CMAX>(n, cmax_rt);
-    // keys of more than 64 bases are mostly distinct: their first table is the
-    // full one (a half table would fill to its limit, with long probe runs,
-    // before the retry)
-    uint32_t Cn = (sizeof(K) >= 16 || FULL_FIRST) ? Cfull : leaf_slots<TB, CMAX>(n / 2, cmax_rt);
-    for (;;) {
+    const u128* src = lf.buf ? bufB : bufA;
+    u128* dst = lf.buf ? bufA : bufB;
+    const bool few = list && count <= kFewLeaves;
+    const uint32_t Cn = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
     const uint32_t cmask = Cn - 1;
+    const int slot_bits = 31 - __builtin_clz(Cn);
     for (uint32_t i = threadIdx.x; i < Cn; i += TB) {
       tc[i] = 0;
-      if constexpr (HI) reinterpret_cast<unsigned long long*>(&tk[i])[1] = ~0ull;
+      reinterpret_cast<unsigned long long*>(&tk[i])[1] = ~0ull;
     }
     if (threadIdx.x == 0) {
       s_nd = 0;
@@ -1773,120 +1798,85 @@ __global__ void __launch_bounds__(TB) k_leaf_countw(int keybits, K* bufA, K* buf
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
     for (uint64_t base = lf.begin; base < lf.end; base += (uint64_t)TB * R) {
       if (ovf_get(&s_ovf)) break;
-      K kb[R];
-      bool kv[R];
+      u128 kb[R];
 #pragma unroll
       for (int j = 0; j < R; ++j) {
         const uint64_t r = base + (uint64_t)j * TB + threadIdx.x;
-        kv[j] = r < lf.end;
-        kb[j] = kv[j] ? src[r] : (K)0;
+        kb[j] = r < lf.end ? src[r] : ~(u128)0;  // never a key: its high word is all ones
       }
-#pragma unroll
-      for (int j = 0; j < R; ++j) {
-      if (!kv[j]) continue;
-      const K key = kb[j];
-      uint32_t pos = (uint32_t)Key<K>::hash(key) & cmask;
-      uint32_t probe = 0, spins = 0;
-      bool done = false;
-      if constexpr (HI) {
+      // one probe loop over the thread's R records, as for one-word keys
+      u128 key = 0;
+      uint32_t pos = 0, probes = 0, spins = 0;
+      int j = 0;
+      const auto take = [&](const u128& x) {
+        key = x;
+        pos = Hash2<u128>(x).pos >> (32 - slot_bits);
+        probes = 0;
+      };
+      bool todo = (unsigned long long)(kb[0] >> 64) != ~0ull;
+      if (todo) take(kb[0]);
+      while (todo) {
+        unsigned long long* const w = reinterpret_cast<unsigned long long*>(&tk[pos]);
         const unsigned long long khi = (unsigned long long)(key >> 64);
         const unsigned long long klo = (unsigned long long)key;
-        bool todo = true;
-        while (todo) {
-          unsigned long long* w = reinterpret_cast<unsigned long long*>(&tk[pos]);
-          const unsigned long long prev = atomicCAS(&w[1], ~0ull, khi);
-          bool hit = false, wait = false;
-          if (prev == ~0ull) {
-            w[0] = klo;
-            __hip_atomic_store(&tc[pos], (C)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (track && atomicAdd(&s_nd, 1u) + 1 >= limit) ovf_set(&s_ovf);
+        const unsigned long long prev = atomicCAS(&w[1], ~0ull, khi);
+        bool hit = false, wait = false;
+        if (prev == ~0ull) {
+          w[0] = klo;
+          __hip_atomic_store(&tc[pos], 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (track && atomicAdd(&s_nd, 1u) + 1 >= limit) ovf_set(&s_ovf);
+          hit = true;
+        } else if (prev == khi) {
+          const uint32_t c =
+              __hip_atomic_load(&tc[pos], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+          if (c == 0) {
+            // the bound only guards against a hang; giving up marks the leaf
+            // overflowed, so it is counted again
+            wait = ++spins <= (1u << 22);
+            if (!wait) probes = Cn;
+          } else if (w[0] == klo) {
+            __hip_atomic_fetch_add(&tc[pos], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             hit = true;
-          } else if (prev == khi) {
-            const C c = __hip_atomic_load(&tc[pos], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (c == 0) {
-              // the bound only guards against a hang; giving up marks the
-              // leaf overflowed, so it is counted again by refinement
-              wait = ++spins <= (1u << 22);
-              if (!wait) probe = Cn;
-            } else if (w[0] == klo) {
-              __hip_atomic_fetch_add(&tc[pos], (C)1, __ATOMIC_RELAXED,
-                                     __HIP_MEMORY_SCOPE_WORKGROUP);
-              hit = true;
-            }
           }
-          done |= hit;
-          if (!hit && !wait && probe < Cn) {
-            pos = (pos + 1) & cmask;
-            ++probe;
-          }
-          todo = !hit && probe < Cn;
         }
-      } else {
-      while (probe < Cn) {
-        C c = __hip_atomic_load(&tc[pos], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (c == 0) {
-          C expect = 0;
-          if (__hip_atomic_compare_exchange_strong(&tc[pos], &expect, (C)LOCK, __ATOMIC_ACQ_REL,
-                                                   __ATOMIC_ACQUIRE,
-                                                   __HIP_MEMORY_SCOPE_WORKGROUP)) {
-            tk[pos] = key;
-            __hip_atomic_store(&tc[pos], (C)1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            if (track && atomicAdd(&s_nd, 1u) + 1 >= limit) ovf_set(&s_ovf);
-            done = true;
-            break;
-          }
-          c = expect;
+        if (hit) {
+          ++j;
+          u128 nx = ~(u128)0;
+#pragma unroll
+          for (int q = 1; q < R; ++q)
+            if (j == q) nx = kb[q];
+          todo = (unsigned long long)(nx >> 64) != ~0ull;
+          if (todo) take(nx);
+        } else if (!wait) {
+          pos = (pos + 1) & cmask;
+          todo = ++probes < Cn;
+          if (!todo) ovf_set(&s_ovf);
         }
-        if (c == (C)LOCK) {
-          if (++spins > (1u << 22)) break;  // cannot happen; guards against a hang
-          continue;
-        }
-        if (tk[pos] == key) {
-          __hip_atomic_fetch_add(&tc[pos], (C)1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-          done = true;
-          break;
-        }
-        pos = (pos + 1) & cmask;
-        ++probe;
-      }
-      }
-      if (!done) ovf_set(&s_ovf);
       }
     }
     __syncthreads();
-    if (ovf_get(&s_ovf) && Cn < Cfull) {
-      Cn = Cfull;
-      __syncthreads();
-      continue;  // retry this leaf with the full table
-    }
-    break;
-    }
     if (ovf_get(&s_ovf)) {
       if (threadIdx.x == 0) {
         d_out[l] = kLeafOverflow;
-        atomicOr(&st->overflow, 1u);
+        // (st->overflow is raised from the leaf counts by the output-offset scan)
+        if (ovf_list) ovf_list[atomicAdd(&st->n_ovf, 1ull)] = (uint32_t)l;
       }
       __syncthreads();
       continue;
     }
-    if constexpr (HI) {
-      if (n > 0xFFFFFFFFull) {
-        // 32-bit counts may have wrapped: they then sum to less than the records
-        if (threadIdx.x == 0) s_sum = 0;
-        __syncthreads();
-        unsigned long long part = 0;
-        for (uint32_t i = threadIdx.x; i < Cn; i += TB) part += tc[i];
-        atomicAdd(&s_sum, part);
-        __syncthreads();
-        if (threadIdx.x == 0 && s_sum != n) s_cov = 1;
-      }
-    } else {
-      for (uint32_t i = threadIdx.x; i < Cn; i += TB)
-        if ((unsigned long long)tc[i] > 0xFFFFFFFFull) s_cov = 1;
+    if (n > 0xFFFFFFFFull) {
+      // 32-bit counts may have wrapped: they then sum to less than the records
+      if (threadIdx.x == 0) s_sum = 0;
+      __syncthreads();
+      unsigned long long part = 0;
+      for (uint32_t i = threadIdx.x; i < Cn; i += TB) part += tc[i];
+      atomicAdd(&s_sum, part);
+      __syncthreads();
+      if (threadIdx.x == 0 && s_sum != n) s_cov = 1;
     }
-    const uint32_t d = leaf_sort_write<K, C, TB, CMAX / TB, 1>(
+    const uint32_t d = leaf_sort_write<u128, TB, CMAX / TB, 1>(
         tk, tc, aux, wsum, &s_max, Cn, keybits, (int)lf.bits, dst, tmp_cnt, lf.begin,
-        HI ? (bool (*)(C))occ32 : (bool (*)(C))occ64);
+        TableK<u128>{tk, tc});
     if (threadIdx.x == 0) {
       d_out[l] = d;
       if (s_cov) atomicOr(&st->count_overflow, 1u);
@@ -1896,9 +1886,223 @@ __global__ void __launch_bounds__(TB) k_leaf_countw(int keybits, K* bufA, K* buf
     __syncthreads();
   }
   if (list && threadIdx.x == 0 && my_records) {
-    atomicAdd(&st->large_records, my_records);
-    atomicAdd(&st->large_distinct, my_distinct);
+    atomicAdd(&acc[0], my_records);
+    atomicAdd(&acc[1], my_distinct);
   }
+}
+
+// Keys of k >= 64: a slot holds where its key is, not the key: a 24-bit tag of the key's hash above the 40-bit number of the record
+// that claimed it (all ones: empty), claimed by one 64-bit CAS. A record that
+// meets its own tag compares its key with the claimer's, read from the leaf's
+// records (which nothing writes here, so there is nothing to wait for), and
+// counts in that slot if they are equal (else, one time in 2^24, it probes on).
+// The R records of a thread are placed first, by tags alone, then all their
+// claimers' keys are loaded together and compared. A slot takes 12 bytes of LDS
+// instead of 20 to 40 (key and count), and the keys of the distinct records are
+// brought to LDS only for the sort, where the slots were: two (four-word keys)
+// and three workgroups share a CU. 1,000,000 reads of 150 bases at k = 100:
+// large leaves 6.96 -> 2.8 ms (keys in the slots, claimed through a lock in the
+// count word, one workgroup per CU; a bound is the latency of a leaf's chain of
+// steps: about 1,100 records, 0.9 of them distinct).
+// Two tables as for one-word keys: a leaf whose table overflows is listed for a
+// second launch with one twice as large (ovf_list, n_list, acc as there).
+// FULL_FIRST only names the launches that count refined parts apart.
+constexpr int kWideGroupShift = 2;  // Cn/4 groups in the epilogue's counting sort
+
+// Their tables for the epilogue: the slot's record holds the key, read once for
+// its group bits and once for the key (a thread holding four keys of four
+// words in between would spill).
+constexpr int kIdxBits = 40;
+constexpr unsigned long long kIdx = (1ull << kIdxBits) - 1;
+template <typename K> struct TableW {
+  typedef unsigned long long Ref;
+  const unsigned long long* slot;
+  const uint32_t* tc;
+  const K* src;
+  __device__ __forceinline__ void load(uint32_t s, Ref& r, uint32_t& c) const {
+    r = slot[s] & kIdx;
+    c = tc[s];
+  }
+  __device__ __forceinline__ uint32_t bits(Ref r, int shift, int nbits) const {
+    const uint64_t* w = reinterpret_cast<const uint64_t*>(src + r) + (shift >> 6);
+    const int off = shift & 63;
+    uint64_t v = w[0] >> off;
+    if (off + nbits > 64) v |= w[1] << (64 - off);
+    return (uint32_t)v & ((1u << nbits) - 1u);
+  }
+  __device__ __forceinline__ K key(Ref r) const { return src[r]; }
+};
+
+template <typename K, int TB, int CMAX, int R>
+__device__ __forceinline__ void leaf_countw_body(
+    int keybits, K* bufA, K* bufB, uint32_t* __restrict__ tmp_cnt, const Leaf* __restrict__ leaves,
+    DevState* __restrict__ st, uint32_t* __restrict__ d_out, int slots_log2,
+    const uint32_t* __restrict__ list, const unsigned long long* __restrict__ n_list,
+    uint32_t* __restrict__ ovf_list, unsigned long long* __restrict__ acc, uint64_t small_max) {
+  __shared__ __align__(16) unsigned char raw[CMAX * sizeof(K)];  // slots, then sorted keys
+  __shared__ uint32_t tc[CMAX];
+  __shared__ uint32_t aux[(2 * CMAX) >> kWideGroupShift];
+  __shared__ uint32_t wsum[TB / 64];
+  __shared__ uint32_t s_nd, s_max, s_cov;
+  __shared__ unsigned long long s_sum;
+  __shared__ uint32_t s_ovf;  // accessed only through ovf_get / ovf_set
+  unsigned long long* const slot = reinterpret_cast<unsigned long long*>(raw);
+  const unsigned long long EMPTY = ~0ull;
+  const uint32_t cmax_rt = 1u << slots_log2;
+  const unsigned long long count = list ? *n_list : st->n_leaves;
+  unsigned long long my_records = 0, my_distinct = 0;  // thread 0: this workgroup's totals
+  for (unsigned long long it = blockIdx.x; it < count; it += gridDim.x) {
+    const unsigned long long l = list ? (unsigned long long)list[it] : it;
+    const Leaf lf = leaves[l];
+    const uint64_t n = lf.end - lf.begin;
+    if (n == 0) {
+      if (threadIdx.x == 0) d_out[l] = 0;
+      continue;
+    }
+    if (!list && n > small_max) continue;
+    const K* __restrict__ src = (lf.buf ? bufB : bufA) + lf.begin;
+    K* const dst = lf.buf ? bufA : bufB;
+    const bool few = list && count <= kFewLeaves;
+    const uint32_t Cn = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
+    const uint32_t cmask = Cn - 1;
+    const int slot_bits = 31 - __builtin_clz(Cn);
+    for (uint32_t i = threadIdx.x; i < Cn; i += TB) {
+      slot[i] = EMPTY;
+      tc[i] = 0;
+    }
+    if (threadIdx.x == 0) {
+      s_nd = 0;
+      __hip_atomic_store(&s_ovf, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      s_cov = 0;
+    }
+    __syncthreads();
+    const uint32_t limit = Cn - (Cn >> 3);
+    const bool track = n >= limit;  // fewer records than the limit cannot overflow
+    for (uint64_t base = 0; base < n; base += (uint64_t)TB * R) {
+      if (ovf_get(&s_ovf)) break;
+      K kb[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const uint64_t r = base + (uint64_t)j * TB + threadIdx.x;
+        if (r < n) kb[j] = src[r];
+      }
+      // a slot each, by tags: EMPTY = claimed, else what the slot held
+      uint32_t pos[R], tag[R], probes[R];
+      unsigned long long held[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const uint64_t r = base + (uint64_t)j * TB + threadIdx.x;
+        const Hash2<K> h(kb[j]);
+        pos[j] = h.pos >> (32 - slot_bits);
+        tag[j] = h.tag >> 8;
+        probes[j] = 0;
+        held[j] = EMPTY;
+        bool todo = r < n;
+        while (todo) {
+          const unsigned long long prev =
+              atomicCAS(&slot[pos[j]], EMPTY, (unsigned long long)tag[j] << kIdxBits | r);
+          held[j] = prev;
+          todo = prev != EMPTY && (uint32_t)(prev >> kIdxBits) != tag[j];
+          if (todo) {
+            pos[j] = (pos[j] + 1) & cmask;
+            if (++probes[j] >= Cn) {
+              ovf_set(&s_ovf);  // table full: the leaf overflows
+              todo = false;
+            }
+          }
+        }
+      }
+      K kc[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const uint64_t r = base + (uint64_t)j * TB + threadIdx.x;
+        if (r < n && held[j] != EMPTY) kc[j] = src[held[j] & kIdx];
+      }
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const uint64_t r = base + (uint64_t)j * TB + threadIdx.x;
+        if (r >= n || probes[j] >= Cn) continue;
+        bool fresh = held[j] == EMPTY;
+        if (!fresh && kc[j] != kb[j]) {
+          // another key with this tag: probe on, comparing at once
+          bool todo = true;
+          while (todo) {
+            pos[j] = (pos[j] + 1) & cmask;
+            if (++probes[j] >= Cn) break;
+            const unsigned long long prev =
+                atomicCAS(&slot[pos[j]], EMPTY, (unsigned long long)tag[j] << kIdxBits | r);
+            fresh = prev == EMPTY;
+            todo = !fresh &&
+                   !((uint32_t)(prev >> kIdxBits) == tag[j] && src[prev & kIdx] == kb[j]);
+          }
+          if (probes[j] >= Cn) {
+            ovf_set(&s_ovf);
+            continue;
+          }
+        }
+        atomicAdd(&tc[pos[j]], 1u);
+        if (track && fresh && atomicAdd(&s_nd, 1u) + 1 >= limit) ovf_set(&s_ovf);
+      }
+    }
+    __syncthreads();
+    if (ovf_get(&s_ovf)) {
+      if (threadIdx.x == 0) {
+        d_out[l] = kLeafOverflow;
+        // (st->overflow is raised from the leaf counts by the output-offset scan)
+        if (ovf_list) ovf_list[atomicAdd(&st->n_ovf, 1ull)] = (uint32_t)l;
+      }
+      __syncthreads();
+      continue;
+    }
+    if (n > 0xFFFFFFFFull) {
+      // 32-bit counts may have wrapped: they then sum to less than the records
+      if (threadIdx.x == 0) s_sum = 0;
+      __syncthreads();
+      unsigned long long part = 0;
+      for (uint32_t i = threadIdx.x; i < Cn; i += TB) part += tc[i];
+      atomicAdd(&s_sum, part);
+      __syncthreads();
+      if (threadIdx.x == 0 && s_sum != n) s_cov = 1;
+    }
+    const uint32_t d = leaf_sort_write<K, TB, CMAX / TB, kWideGroupShift>(
+        reinterpret_cast<K*>(raw), tc, aux, wsum, &s_max, Cn, keybits, (int)lf.bits, dst, tmp_cnt,
+        lf.begin, TableW<K>{slot, tc, src});
+    if (threadIdx.x == 0) {
+      d_out[l] = d;
+      if (s_cov) atomicOr(&st->count_overflow, 1u);
+      my_records += n;
+      my_distinct += d;
+    }
+    __syncthreads();
+  }
+  if (list && threadIdx.x == 0 && my_records) {
+    atomicAdd(&acc[0], my_records);
+    atomicAdd(&acc[1], my_distinct);
+  }
+}
+
+template <int TB, int CMAX, int R, bool FULL_FIRST>
+__global__ void __launch_bounds__(TB)
+__attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? 4 : 1)))
+k_leaf_countw128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_cnt,
+                 const Leaf* __restrict__ leaves, DevState* __restrict__ st,
+                 uint32_t* __restrict__ d_out, int slots_log2, const uint32_t* __restrict__ list,
+                 const unsigned long long* __restrict__ n_list, uint32_t* __restrict__ ovf_list,
+                 unsigned long long* __restrict__ acc, uint64_t small_max) {
+  leaf_countw_body<u128, TB, CMAX, R>(keybits, bufA, bufB, tmp_cnt, leaves, st, d_out, slots_log2,
+                                      list, n_list, ovf_list, acc, small_max);
+}
+
+template <int TB, int CMAX, int R, bool FULL_FIRST>
+__global__ void __launch_bounds__(TB)
+__attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? 4 : 1)))
+k_leaf_countw256(int keybits, u256* bufA, u256* bufB, uint32_t* __restrict__ tmp_cnt,
+                 const Leaf* __restrict__ leaves, DevState* __restrict__ st,
+                 uint32_t* __restrict__ d_out, int slots_log2, const uint32_t* __restrict__ list,
+                 const unsigned long long* __restrict__ n_list, uint32_t* __restrict__ ovf_list,
+                 unsigned long long* __restrict__ acc, uint64_t small_max) {
+  leaf_countw_body<u256, TB, CMAX, R>(keybits, bufA, bufB, tmp_cnt, leaves, st, d_out, slots_log2,
+                                      list, n_list, ovf_list, acc, small_max);
 }
 
 // ---------------------------------------------------------------- sort-based leaf count
@@ -2425,10 +2629,12 @@ constexpr int kLeafCmax64 = 4096;
 // LDS with the epilogue's counters: one 1,024-thread workgroup per CU)
 constexpr int kRescueTB = 1024;
 constexpr int kRescueCmax64 = 8192;
-constexpr int kRescueSlotsLog2 = 13;
+// the same for wider keys: 4,096 slots (152 KiB for four-word keys)
+constexpr int kRescueCmaxW = 4096;
+inline int second_slots_log2(int words) { return words == 1 ? 13 : 12; }
 constexpr unsigned kRescueGrid = 256;
 constexpr int kLeafCmax128 = 2048;
-constexpr int kLeafCmax256 = 2048;  // 44 bytes a slot: key, 64-bit count, sort aux
+constexpr int kLeafCmax256 = 2048;
 constexpr unsigned kPersistentGrid = 1024;  // blocks of the persistent kernels
 constexpr int kSmallCmax64 = 1024;  // one-wave leaf kernel: slots of its private table
 constexpr int kSmallCmax128 = 512;
@@ -2612,7 +2818,7 @@ static LeafLists leaf_lists(int words, uint64_t max_leaves, uint32_t* d_out, uin
   const bool one_wave = mode != 1 && words != 4 && max_leaves > kFewLeaves;
   // leaves of more than 8 first tables of records go straight to the second
   // count (where it runs: launch_leaf_second)
-  const bool second = words == 1 && mode != 1 && slots_log2 < kRescueSlotsLog2 && ovf_list;
+  const bool second = mode != 1 && slots_log2 < second_slots_log2(words) && ovf_list;
   return LeafLists{one_wave ? small_leaf_max(words) : 0, 8ull << slots_log2, large_list,
                    second ? ovf_list : nullptr, one_wave ? nullptr : d_out};
 }
@@ -2713,10 +2919,12 @@ hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uin
   }
   if (q.d_zero) return hipGetLastError();  // every non-empty leaf is in a list
   const unsigned gsmall = persistent(max_leaves, kSmallGrid);
-#define KC_SMALLW(HI, FF)                                                                        \
-  hipLaunchKernelGGL((k_leaf_countw<u128, 64, kSmallCmax128, 8, HI, FF>), dim3(gsmall), dim3(64), \
-                     0, s, keybits, (u128*)bufA, (u128*)bufB, tmp_cnt, leaves, st, d_out,        \
-                     __builtin_ctz(kSmallCmax128), (const uint32_t*)nullptr, small_max)
+#define KC_SMALLW(KRN, FF)                                                                        \
+  hipLaunchKernelGGL((KRN<64, kSmallCmax128, 8, FF>), dim3(gsmall), dim3(64), 0, s, keybits,       \
+                     (u128*)bufA, (u128*)bufB, tmp_cnt, leaves, st, d_out,                        \
+                     __builtin_ctz(kSmallCmax128), (const uint32_t*)nullptr,                      \
+                     (const unsigned long long*)nullptr, (uint32_t*)nullptr, &st->large_records,  \
+                     small_max)
 #define KC_SMALL64(FF, MG)                                                                       \
   hipLaunchKernelGGL((k_leaf_count64<64, kSmallCmax64, 8, FF, MG>), dim3(gsmall), dim3(64), 0, s, \
                      keybits, (uint64_t*)bufA, (uint64_t*)bufB, tmp_cnt, leaves, st, d_out,      \
@@ -2725,9 +2933,9 @@ hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uin
                      small_max)
   if (wide) {
     if (keybits <= 126) {
-      if (refine) KC_SMALLW(true, true); else KC_SMALLW(true, false);
+      if (refine) KC_SMALLW(k_leaf_count128, true); else KC_SMALLW(k_leaf_count128, false);
     } else {
-      if (refine) KC_SMALLW(false, true); else KC_SMALLW(false, false);
+      if (refine) KC_SMALLW(k_leaf_countw128, true); else KC_SMALLW(k_leaf_countw128, false);
     }
   } else {
     if (merged) {
@@ -2764,29 +2972,26 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                          large_list);
     return hipGetLastError();
   }
-#define KC_LARGEW(KT, CM, HI, FF)                                                               \
-  hipLaunchKernelGGL((k_leaf_countw<KT, kLeafTB, CM, 4, HI, FF>), dim3(glarge), dim3(kLeafTB), 0, \
-                     s, keybits, (KT*)bufA, (KT*)bufB, tmp_cnt, leaves, st, d_out, slots_log2,   \
-                     large_list, small_max)
-  // one-word keys: the leaves whose table overflows are listed for
-  // launch_leaf_second
-  uint32_t* const second = words == 1 && slots_log2 < kRescueSlotsLog2 ? ovf_list : nullptr;
+#define KC_LARGEW(KRN, KT, CM, R, FF)                                                             \
+  hipLaunchKernelGGL((KRN<kLeafTB, CM, R, FF>), dim3(glarge), dim3(kLeafTB), 0, s, keybits,        \
+                     (KT*)bufA, (KT*)bufB, tmp_cnt, leaves, st, d_out, slots_log2, large_list,    \
+                     &st->n_large, second, &st->large_records, small_max)
+  // the leaves whose table overflows are listed for launch_leaf_second
+  uint32_t* const second = slots_log2 < second_slots_log2(words) ? ovf_list : nullptr;
 #define KC_LARGE64(FF, MG)                                                                      \
   hipLaunchKernelGGL((k_leaf_count64<kLeafTB, kLeafCmax64, 4, FF, MG>), dim3(glarge),            \
                      dim3(kLeafTB), 0, s, keybits, (uint64_t*)bufA, (uint64_t*)bufB, tmp_cnt,    \
                      leaves, st, d_out, slots_log2, large_list, &st->n_large, second,            \
                      &st->large_records, small_max)
   if (words == 4) {
-    if (refine) KC_LARGEW(u256, kLeafCmax256, false, true);
-    else KC_LARGEW(u256, kLeafCmax256, false, false);
+    if (refine) KC_LARGEW(k_leaf_countw256, u256, kLeafCmax256, 2, true);
+    else KC_LARGEW(k_leaf_countw256, u256, kLeafCmax256, 2, false);
+  } else if (wide && keybits <= 126) {
+    if (refine) KC_LARGEW(k_leaf_count128, u128, kLeafCmax128, 4, true);
+    else KC_LARGEW(k_leaf_count128, u128, kLeafCmax128, 4, false);
   } else if (wide) {
-    if (keybits <= 126) {
-      if (refine) KC_LARGEW(u128, kLeafCmax128, true, true);
-      else KC_LARGEW(u128, kLeafCmax128, true, false);
-    } else {
-      if (refine) KC_LARGEW(u128, kLeafCmax128, false, true);
-      else KC_LARGEW(u128, kLeafCmax128, false, false);
-    }
+    if (refine) KC_LARGEW(k_leaf_countw128, u128, kLeafCmax128, 4, true);
+    else KC_LARGEW(k_leaf_countw128, u128, kLeafCmax128, 4, false);
   } else {
     if (merged) {
       if (refine) KC_LARGE64(true, true); else KC_LARGE64(false, true);
@@ -2802,12 +3007,24 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
 hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                               const Leaf* leaves, DevState* st, uint32_t* d_out, int slots_log2,
                               const uint32_t* ovf_list, hipStream_t s, int mode, bool merged) {
-  if (words != 1 || mode == 1 || slots_log2 >= kRescueSlotsLog2 || !ovf_list) return hipSuccess;
+  if (mode == 1 || slots_log2 >= second_slots_log2(words) || !ovf_list) return hipSuccess;
   // the leaves whose table overflowed are counted again at once by a
   // workgroup per CU with a table twice as large (a leaf overflows because of
   // its distinct keys: clusters of keys that share a long prefix, the
   // erroneous and diverged copies of frequent k-mers, which a split on the
   // next key bits barely thins out)
+#define KC_SECONDW(KRN, KT, R)                                                                    \
+  hipLaunchKernelGGL((KRN<kRescueTB, kRescueCmaxW, R, true>), dim3(kRescueGrid), dim3(kRescueTB),  \
+                     0, s, keybits, (KT*)bufA, (KT*)bufB, tmp_cnt, leaves, st, d_out,             \
+                     slots_log2 + 1, ovf_list, &st->n_ovf, (uint32_t*)nullptr,                    \
+                     &st->second_records, (uint64_t)0)
+  if (words != 1) {
+    if (words == 4) KC_SECONDW(k_leaf_countw256, u256, 1);
+    else if (keybits <= 126) KC_SECONDW(k_leaf_count128, u128, 2);
+    else KC_SECONDW(k_leaf_countw128, u128, 2);
+    return hipGetLastError();
+  }
+#undef KC_SECONDW
   if (merged)
     hipLaunchKernelGGL((k_leaf_count64<kRescueTB, kRescueCmax64, 4, true, true>),
                        dim3(kRescueGrid), dim3(kRescueTB), 0, s, keybits, (uint64_t*)bufA,

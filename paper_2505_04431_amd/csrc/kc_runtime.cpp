@@ -933,13 +933,17 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   // 1,000,000 reads at k = 31 / 21: 2.76 / 2.71 ms per call against 3.05 /
   // 3.00 ms at three quarters of a table, no overflow; the per-leaf work of
   // clearing, compacting and sorting the table is spread over more records).
-  // Wider keys, mostly distinct: three quarters of the largest table (1.5
-  // tables overflowed 122 leaves at k = 55 and 8,896 at k = 100: 5.35 and
-  // 59.1 ms against 4.68 and 8.4 ms). The sort-based leaves (mode 1) sort
+  // Two-word keys: one table (60 MB of 10 kbp reads at k = 55: 2.32 ms per call
+  // against 2.40 at three quarters and 2.69 at 1.25 tables). Four-word keys,
+  // mostly distinct: three quarters (1,000,000 reads at k = 100: 6.4 ms
+  // against 7.3 at one table). The sort-based leaves (mode 1) sort
   // all their records in LDS, so they keep three quarters of a table too
   // (1.5 tables: 39 ms against 12 ms on the 1,000,000 reads).
   const bool big = words == 1 && o.mode != 1;
-  T = o.leaf_target > 0 ? (uint64_t)o.leaf_target : (big ? (C * 3) / 2 : (C * 3) / 4);
+  T = o.leaf_target > 0 ? (uint64_t)o.leaf_target
+      : big                ? (C * 3) / 2
+      : words == 2 && o.mode != 1 ? C
+                           : (C * 3) / 4;
   H = o.leaf_attempt > 0 ? (uint64_t)o.leaf_attempt : (C * 7) / 8;
 }
 
