@@ -2635,7 +2635,14 @@ inline int second_slots_log2(int words) { return words == 1 ? 13 : 12; }
 constexpr unsigned kRescueGrid = 256;
 constexpr int kLeafCmax128 = 2048;
 constexpr int kLeafCmax256 = 2048;
-constexpr unsigned kPersistentGrid = 1024;  // blocks of the persistent kernels
+// Workgroups of the block-wide leaf kernels and the split scatter, each taking
+// every kManyGrid-th leaf or item. Many more than fit the chip (768 and 256):
+// the hardware hands them out as workgroups finish, which evens out leaves of
+// unequal cost, and there is no last round that fills a third of the chip (1,024
+// workgroups of which 768 are resident: large leaves of 20,000,000 reads 14.3
+// ms, so 10.7; 768: 12.1; 4,096: 11.2; 65,536: 10.8. Split scatter of
+// 1,000,000 reads, 7,300 items on 2,048 workgroups: 0.51 ms, so 0.41).
+constexpr unsigned kManyGrid = 16384;
 constexpr int kSmallCmax64 = 1024;  // one-wave leaf kernel: slots of its private table
 constexpr int kSmallCmax128 = 512;
 constexpr unsigned kSmallGrid = 256 * 20;
@@ -2867,7 +2874,7 @@ hipError_t launch_split_scatter(int words, const void* src, void* dst, const Spl
                                 const DevState* st, uint64_t max_items, const SplitBin* bins,
                                 unsigned long long* cursor, int records_per_thread,
                                 int merge_cshift, int ncls, uint64_t cls_stride, hipStream_t s) {
-  const unsigned grid = persistent(max_items, 2048);
+  const unsigned grid = persistent(max_items, kManyGrid);
   if (merge_cshift) {
     // one cursor per leaf: its final value is the leaf's end
     if (words != 1 || records_per_thread != 16 || ncls != 1) return hipErrorInvalidValue;
@@ -2956,7 +2963,10 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                              bool merged) {
   const bool wide = words == 2;
   const uint64_t small_max = small_leaf_max(words);
-  const unsigned glarge = persistent(max_leaves, kPersistentGrid);
+  // (max_leaves is a bound, two to four times the leaves: fewer workgroups for
+  // inputs of few, or most start only to end, in the way of other streams' work)
+  const unsigned glarge = persistent(
+      max_leaves, (unsigned)std::min<uint64_t>(std::max<uint64_t>(max_leaves / 4, 1024), kManyGrid));
   if (mode == 1) {
     if (words == 4)
       hipLaunchKernelGGL((k_leaf_sort<u256, kLeafTB, kSortMax256>), dim3(glarge), dim3(kLeafTB),
