@@ -188,8 +188,8 @@ hipError_t launch_leaf_ends(Leaf* leaves, const unsigned long long* cursor, cons
 // in large_list, which holds max_leaves entries) to 512-thread workgroups.
 // mode 1: every non-empty leaf's records are sorted in LDS and run-length
 // accumulated (the launch_leaf_small call then only lists the leaves).
-// refine: the leaves are parts of overflowed leaves (first table full size;
-// the launches are separate kernel instantiations, so profiles tell them apart).
+// refine: the leaves are parts of overflowed leaves (the launches are separate
+// kernel instantiations, so profiles tell them apart).
 // merged: leaves may hold pre-aggregated records (one-word keys).
 // ovf_list (max_leaves entries, or nullptr): in mode 0 the leaves whose table
 // overflows are listed there, for launch_leaf_second.

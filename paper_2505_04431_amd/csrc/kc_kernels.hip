@@ -1529,9 +1529,8 @@ template <typename K> struct TableK {
 
 // 64-bit keys: EMPTY (all ones) is never a canonical key for k <= 32, so a
 // slot is claimed by a 64-bit CAS of the key word itself; the count is then
-// added with an atomic add. FULL_FIRST: the first table is the full one (the
-// parts of a leaf that overflowed are rich in distinct keys: a half table
-// would mostly fill up and be retried).
+// added with an atomic add. REFINED only names the launches that count the
+// parts of overflowed leaves apart.
 // MERGED: some leaves may hold pre-aggregated records (Leaf::cshift); the
 // plain instantiation has no decoding in its insert loop.
 // list != nullptr: the leaves listed there, *n_list of them (large ones, or
@@ -1540,7 +1539,7 @@ template <typename K> struct TableK {
 // leaf of at most small_max records. ovf_list != nullptr: the leaves whose
 // table overflows are also appended there (count in st->n_ovf) for a second
 // launch with a larger table.
-template <int TB, int CMAX, int R, bool FULL_FIRST, bool MERGED>
+template <int TB, int CMAX, int R, bool REFINED, bool MERGED>
 __global__ void __launch_bounds__(TB)
 __attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? kLeafOccWaves : 1)))
 k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
@@ -1576,19 +1575,19 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     if (!list && n > small_max) continue;
     const uint64_t* src = lf.buf ? bufB : bufA;
     uint64_t* dst = lf.buf ? bufA : bufB;
-    // First try a table sized for half the records being distinct; if it
-    // fills up, count the leaf again with a table large enough for all.
-    // With few leaves the chip is not full and a leaf's chain of latencies
-    // counts, not its work: one table then, with room to spare.
+    // A table for all records being distinct (a first try with half of that,
+    // counted again if it filled up, saves clearing and compacting slots but
+    // lengthens the probe chains: large leaves of 1,000,000 reads at k = 31 0.74
+    // against 0.68 ms, sized by the share of distinct records 1.01 ms). With few
+    // leaves the chip is not full and a leaf's chain of latencies counts, not
+    // its work: room to spare then.
     const bool few = list && count <= kFewLeaves;
-    const uint32_t Cfull = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
-    uint32_t Cn = FULL_FIRST || few ? Cfull : leaf_slots<TB, CMAX>(n / 2, cmax_rt);
+    const uint32_t Cn = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
     // pre-aggregated records: (count - 1) in bits [cshift, 64), the shard above
     const uint32_t cshift = MERGED ? lf.cshift : 0u;
     const uint64_t low = cshift ? (1ull << cshift) - 1 : ~0ull;
     const uint64_t top = cshift ? (uint64_t)lf.shard << cshift : 0ull;
     unsigned long long my_windows = 0;  // this thread's share of the leaf's windows
-    for (;;) {
     const uint32_t cmask = Cn - 1;
     const int slot_bits = 31 - __builtin_clz(Cn);
     for (uint32_t i = threadIdx.x; i < Cn; i += TB) {
@@ -1604,12 +1603,10 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     __syncthreads();
     const uint32_t limit = Cn - (Cn >> 3);
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
-    // a half table is given up at the first probe chain as long as chains get
-    // near its limit, not only after a whole batch of records: in the full
-    // half table that a batch can leave, chains run to its whole length (256
-    // leaves of 312 records by one wave each: 119 us, capped 59 us)
-    const uint32_t max_probes = Cn < Cfull ? 64u : Cn;
-    my_windows = 0;
+    // new keys are counted per wave and batch, not one by one (a shared counter
+    // takes its lanes one after the other), so a batch may fill the table past
+    // its limit: a probe chain that only such a table has ends the attempt
+    const uint32_t max_probes = track ? min(Cn, 512u) : Cn;
     // records are loaded R per thread before inserting, so that the loads of a
     // batch are in flight together instead of one round trip per insert. The
     // probe loop has a single exit flag (always-CAS: a CAS on a slot holding
@@ -1629,7 +1626,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
       // the sum over the R records of the slowest lane's probes (records past
       // the leaf's end, EMPTY, come last)
       unsigned long long key = EMPTY;
-      uint32_t cnt = 1, pos = 0, probes = 0;
+      uint32_t cnt = 1, pos = 0, probes = 0, claims = 0;
       int j = 0;
       auto take = [&](unsigned long long x) {
         key = x;
@@ -1651,7 +1648,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
         const bool hit = (prev == EMPTY) | (prev == key);
         if (hit) {
           atomicAdd(&tc[pos], cnt);
-          if (track && prev == EMPTY && atomicAdd(&s_nd, 1u) + 1 >= limit) ovf_set(&s_ovf);
+          claims += prev == EMPTY ? 1u : 0u;
           ++j;
           unsigned long long nx = EMPTY;
 #pragma unroll
@@ -1665,15 +1662,13 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
           if (!todo) ovf_set(&s_ovf);  // table full: the leaf overflows
         }
       }
+      if (track) {
+        for (int off = 32; off > 0; off >>= 1) claims += __shfl_xor(claims, off);
+        if ((threadIdx.x & 63) == 0 && claims && atomicAdd(&s_nd, claims) + claims >= limit)
+          ovf_set(&s_ovf);
+      }
     }
     __syncthreads();
-    if (ovf_get(&s_ovf) && Cn < Cfull) {
-      Cn = Cfull;
-      __syncthreads();
-      continue;  // retry this leaf with the full table
-    }
-    break;
-    }
     if (ovf_get(&s_ovf)) {
       if (threadIdx.x == 0) {
         d_out[l] = kLeafOverflow;
@@ -1751,7 +1746,7 @@ template <typename K> struct Hash2 {
 // compares the low word. list, n_list, ovf_list and acc as for one-word keys.
 // (By a 32-bit tag and the keys compared after a barrier: 1.11 against 0.95 ms
 // for the large leaves of 60 MB of 10 kbp reads at k = 55.)
-template <int TB, int CMAX, int R, bool FULL_FIRST>
+template <int TB, int CMAX, int R, bool REFINED>
 __global__ void __launch_bounds__(TB)
 __attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? kLeafOccWaves : 1)))
 k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_cnt,
@@ -1904,9 +1899,9 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
 // large leaves 6.96 -> 2.8 ms (keys in the slots, claimed through a lock in the
 // count word, one workgroup per CU; a bound is the latency of a leaf's chain of
 // steps: about 1,100 records, 0.9 of them distinct).
-// Two tables as for one-word keys: a leaf whose table overflows is listed for a
+// As for one-word keys, a leaf whose table overflows is listed for a
 // second launch with one twice as large (ovf_list, n_list, acc as there).
-// FULL_FIRST only names the launches that count refined parts apart.
+// REFINED only names the launches that count refined parts apart.
 constexpr int kWideGroupShift = 2;  // Cn/4 groups in the epilogue's counting sort
 
 // Their tables for the epilogue: the slot's record holds the key, read once for
@@ -2081,7 +2076,7 @@ __device__ __forceinline__ void leaf_countw_body(
   }
 }
 
-template <int TB, int CMAX, int R, bool FULL_FIRST>
+template <int TB, int CMAX, int R, bool REFINED>
 __global__ void __launch_bounds__(TB)
 __attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? 4 : 1)))
 k_leaf_countw128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_cnt,
@@ -2093,7 +2088,7 @@ k_leaf_countw128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp
                                       list, n_list, ovf_list, acc, small_max);
 }
 
-template <int TB, int CMAX, int R, bool FULL_FIRST>
+template <int TB, int CMAX, int R, bool REFINED>
 __global__ void __launch_bounds__(TB)
 __attribute__((amdgpu_waves_per_eu(TB == kLeafOccTB ? 4 : 1)))
 k_leaf_countw256(int keybits, u256* bufA, u256* bufB, uint32_t* __restrict__ tmp_cnt,
