@@ -357,9 +357,9 @@ void kc_pred_free(kc_predictor* pred);
  *   not overlap the inputs; *n_out receives the number of pairs. KC_E_OVERFLOW
  *   if a sum exceeds 2^32-1. Lets inputs larger than device memory be counted
  *   in pieces whose results are merged. Synchronous on stream.
- * The temporaries of kc_spectrum (8 bytes a bin), kc_merge_counts (24 bytes per 2,048 / words pairs of na +
- * nb) and kc_filter_min_count sit in one device buffer per host thread, part of the
- * thread's scratch arena: it grows stream-ordered from the library pool as
+ * The temporaries of kc_spectrum (8 bytes a bin), kc_merge_counts (24 bytes per
+ * 1,792 pairs of na + nb, or fewer of wider keys) and kc_filter_min_count sit in
+ * one device buffer per host thread, part of the thread's scratch arena: it grows stream-ordered from the library pool as
  * needed and is kept between calls (kc_release_scratch frees it).
  * All return KC_OK, KC_E_INVAL, KC_E_NOMEM or KC_E_DEVICE (and as stated). */
 int kc_spectrum(const uint32_t* counts, uint64_t n, uint32_t max_count, uint64_t* host_hist,
@@ -394,8 +394,9 @@ enum { KC_FASTX_AUTO = 0, KC_FASTQ = 1, KC_FASTA = 2 };
  * the outputs are too small, nothing written to them; KC_E_INVAL for a FASTQ
  * text whose line count is not a multiple of four or whose header / separator
  * lines do not start with '@' / '+' (kc_last_error names the line), or a FASTA
- * text not starting with '>'. Synchronous on stream; uses a small device
- * allocation on the stream (stream-ordered). */
+ * text not starting with '>'. Synchronous on stream; its
+ * temporaries (40 bytes per 16 KiB of text) sit in the thread's buffer as
+ * those of kc_merge_counts do. */
 int kc_parse_fastx(const uint8_t* text, uint64_t n_bytes, int format, uint8_t* out_reads,
                    uint64_t reads_capacity, uint64_t* out_offsets, uint64_t max_records,
                    uint64_t* n_records, uint64_t* n_bases, int* format_out, void* stream);

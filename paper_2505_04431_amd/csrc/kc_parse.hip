@@ -3,15 +3,21 @@
 // The paper leaves input parsing out of its measurements (Section VI); this
 // lets a file's bytes be copied to the device as they are and counted there.
 //
-// Three passes over the text, each HBM-bound (tiles of 16 KiB, 16 bytes per
-// thread and round, loads of whole aligned 16-byte chunks):
-//   1. per tile: newlines, FASTA header starts, start of the last line;
-//      one-block scan over the tiles (sums and a running maximum);
-//   2. per tile: bytes kept (sequence-line bytes other than CR/LF) and the
-//      FASTQ layout check; scan;
-//   3. kept bytes written in order, staged in LDS so that each tile's output
-//      (one contiguous run) is written with consecutive stores, and one
-//      offset per record.
+// Two passes over the text (tiles of 16 KiB, 16 bytes per thread and round,
+// loads of whole aligned 16-byte chunks):
+//   1. per tile: newlines, FASTA header starts, start of the last line, and how
+//      many bytes it keeps (sequence-line bytes other than CR/LF) for every
+//      state in which a line may enter it: which of a record's four lines is
+//      open (FASTQ), or whether a header is (FASTA). Scans over the tiles then
+//      give each tile its state, kept bytes and output offset;
+//   2. kept bytes written in order, straight from the registers (a chunk's kept
+//      bytes are one run in all but a few chunks), one offset per record, and
+//      the FASTQ layout check.
+// Nothing between the passes needs the host: the range without line ends at
+// either end, the format and the outputs' room are looked at on the device,
+// and one synchronization reads the results. 320 MB of FASTQ: 515 -> 314 us
+// (a pass of its own for the kept bytes read the text a third time, 139 us,
+// and three synchronizations took 90 us).
 // Every position a kernel reads is inside [lo, hi) of the trimmed text.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -109,22 +115,25 @@ __device__ __forceinline__ Ld load16(const uint8_t* __restrict__ B, uint64_t pos
   return Ld{make_uint4((uint32_t)w0, (uint32_t)(w0 >> 32), (uint32_t)w1, (uint32_t)(w1 >> 32)), m};
 }
 
-// 4-bit mask of the zero bytes of x (bit i: byte i). (x & 0x7F..) + 0x7F..
-// sets a byte's top bit when its low seven bits are not all zero, without
-// carries between bytes; OR-ing x adds its own top bit; the complement keeps
-// 0x80 exactly in the zero bytes. The multiply by 2^0 + 2^7 + 2^14 + 2^21
-// moves the four flags (bits 0, 8, 16, 24 after the shift) to bits 21..24;
-// no two partial products share a bit position.
-__device__ __forceinline__ uint32_t zero_bytes4(uint32_t x) {
-  const uint32_t t = ~(((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu);
-  return (((t >> 7) * 0x00204081u) >> 21) & 0xFu;
+// x's bytes as 0xFF where not zero, 0x7F where zero: (x & 0x7F..) + 0x7F.. sets
+// a byte's top bit when its low seven bits are not all zero, without carries
+// between bytes; OR-ing x adds its own top bit.
+__device__ __forceinline__ uint32_t mark_zero(uint32_t x) {
+  return ((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x | 0x7F7F7F7Fu;
 }
 
-// Bit j set where byte j equals ch.
+// Bit j set where byte j equals ch. The marks' top bits are gathered by dot
+// products with the bit weights: bytes of 127 + 128 * (not equal) times 1, 2,
+// .. 128 sum to 127 * 255 + 128 * (mask of the bytes not equal). (Both passes
+// are bound by this arithmetic: five instructions a word, thirteen with a
+// multiply that gathers four bits.)
 __device__ __forceinline__ uint32_t eq_mask(const uint4& v, uint32_t ch) {
-  const uint32_t c4 = ch * 0x01010101u;
-  return zero_bytes4(v.x ^ c4) | zero_bytes4(v.y ^ c4) << 4 | zero_bytes4(v.z ^ c4) << 8 |
-         zero_bytes4(v.w ^ c4) << 12;
+  const uint32_t c4 = ch * 0x01010101u, lo = 0x08040201u, hi = 0x80402010u, base = 0u - 127u * 255u;
+  const uint32_t a = __builtin_amdgcn_udot4(
+      mark_zero(v.x ^ c4), lo, __builtin_amdgcn_udot4(mark_zero(v.y ^ c4), hi, base, false), false);
+  const uint32_t b = __builtin_amdgcn_udot4(
+      mark_zero(v.z ^ c4), lo, __builtin_amdgcn_udot4(mark_zero(v.w ^ c4), hi, base, false), false);
+  return (a >> 7 | b << 1) ^ 0xFFFFu;
 }
 
 // The tile's four chunks of this thread (round r: tile bytes
@@ -155,44 +164,156 @@ __device__ __forceinline__ uint32_t last_start(uint32_t nlm, int r) {
   return nlm ? (uint32_t)((r * kTB + threadIdx.x) * kChunk) + (32u - __clz(nlm)) : 0u;
 }
 
-__global__ void __launch_bounds__(kTB) k_fx_lines(const uint8_t* __restrict__ B, uint64_t lo,
-                                                  uint64_t hi, int fasta, ull* __restrict__ t_nl,
-                                                  ull* __restrict__ t_hd, ull* __restrict__ t_ls) {
+// What the passes find out, on the device and for the host.
+struct Info {
+  uint64_t lo, hi;      // the text without line ends at its ends, positions in B
+  uint32_t fasta, first;  // format taken; the first byte
+  uint32_t missing;     // 1, 2: nothing but line ends in the first, last kPeek bytes
+  uint32_t pad;
+  ull newlines, headers, keep, err;  // err: first malformed FASTQ line, ~0 if none
+};
+
+constexpr uint64_t kPeek = 4096;
+
+// One block: [lo, hi), the first byte and the format, if the first and last
+// kPeek bytes each hold a byte that is not CR/LF (else the host looks further).
+__global__ void __launch_bounds__(kTB) k_fx_ends(const uint8_t* __restrict__ text, uint64_t n,
+                                                 uint64_t a0, int format, Info* info) {
+  __shared__ uint32_t s_head, s_tail;
+  if (threadIdx.x == 0) {
+    s_head = ~0u;
+    s_tail = 0;
+  }
+  __syncthreads();
+  const uint32_t nh = (uint32_t)(n < kPeek ? n : kPeek);
+  uint32_t head = ~0u, tail = 0;
+  for (uint32_t i = threadIdx.x; i < nh; i += kTB) {
+    const uint8_t x = text[i], y = text[n - nh + i];
+    if (x != '\n' && x != '\r' && head == ~0u) head = i;
+    if (y != '\n' && y != '\r') tail = i + 1;
+  }
+  if (head != ~0u) atomicMin(&s_head, head);
+  if (tail) atomicMax(&s_tail, tail);
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  Info r = {};
+  r.missing = n > nh ? (s_head == ~0u ? 1u : 0u) | (s_tail == 0 ? 2u : 0u) : 0u;
+  const uint64_t s0 = s_head == ~0u ? n : s_head;
+  r.lo = a0 + s0;
+  r.hi = s_tail == 0 ? r.lo : a0 + n - nh + s_tail;
+  if (r.missing) r.hi = r.lo;  // the passes that follow see no text
+  r.first = s0 < n ? text[s0] : 0;
+  r.fasta = format == KC_FASTA || (format == KC_FASTX_AUTO && r.first == '>');
+  r.err = ~0ull;
+  *info = r;
+}
+
+// A tile's kept bytes by the state at its start, 16 bits each. FASTQ: field q
+// = bytes of the tile's lines q, q + 4, ... (line 0 is the one open at its
+// start), so the lines with index 1 mod 4 are field (1 - first line) mod 4.
+// FASTA: field 0 = bytes before the first newline (kept unless a header is
+// open), field 1 = kept bytes after it.
+__global__ void __launch_bounds__(kTB) k_fx_lines(const uint8_t* __restrict__ B,
+                                                  const Info* __restrict__ info,
+                                                  ull* __restrict__ t_nl, ull* __restrict__ t_hd,
+                                                  ull* __restrict__ t_ls,
+                                                  ull* __restrict__ t_cls) {
   __shared__ ull sh[kTB / 64];
+  const uint64_t lo = info->lo, hi = info->hi;
+  const uint32_t fasta = info->fasta;
   const uint64_t tile0 = (uint64_t)blockIdx.x * kTile;
   const Chunks c = load_tile(B, tile0, lo, hi);
-  uint32_t nl = 0, hd = 0, ls = 0;
+  ull nl4 = 0;
+  uint32_t hd = 0, ls = 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
-    nl += __popc(c.nl[r]);
+    nl4 |= (ull)__popc(c.nl[r]) << (16 * r);
     const uint32_t s = last_start(c.nl[r], r);
     ls = s > ls ? s : ls;
-    if (fasta && c.m[r]) {
+  }
+  ull tot_nl4;
+  const ull ex_nl4 = block_exscan(nl4, Plus(), sh, &tot_nl4);
+  ull ex_ls4 = 0, tot_ls4 = 0;
+  if (fasta) {
+    ull ls4 = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) ls4 |= (ull)last_start(c.nl[r], r) << (16 * r);
+    ex_ls4 = block_exscan(ls4, Max4(), sh, &tot_ls4);
+  }
+  ull cls = 0;
+  uint32_t nl_before = 0, ls_before = 0;
+#pragma unroll
+  for (int r = 0; r < kRounds; ++r) {
+    uint32_t line = nl_before + field(ex_nl4, r);  // of the chunk's first byte, in the tile
+    nl_before += field(tot_nl4, r);
+    // where that line starts, in the tile (0: before it)
+    const uint32_t ls0 = ls_before > field(ex_ls4, r) ? ls_before : field(ex_ls4, r);
+    ls_before = ls_before > field(tot_ls4, r) ? ls_before : field(tot_ls4, r);
+    if (!c.m[r]) continue;
+    const uint32_t body = c.m[r] & ~c.nl[r] & ~eq_mask(c.v[r], '\r');
+    uint32_t hdm = 0;
+    bool header = false;
+    if (fasta) {
       // header starts: '>' at a line start (after a newline, or at lo)
       const uint64_t pos = tile0 + ((uint64_t)r * kTB + threadIdx.x) * kChunk;
       uint32_t starts = (c.nl[r] << 1) & 0xFFFFu;
       if (pos > lo) starts |= B[pos - 1] == '\n' ? 1u : 0u;
       else starts |= 1u << (uint32_t)(lo - pos);
-      hd += __popc(starts & eq_mask(c.v[r], '>') & c.m[r]);
+      hdm = starts & eq_mask(c.v[r], '>') & c.m[r];
+      hd += __popc(hdm);
+      header = line && B[tile0 + ls0] == '>';
+    }
+    uint32_t from = 0;
+    for (uint32_t rest = c.nl[r];;) {
+      const uint32_t to = rest ? (uint32_t)__ffs(rest) : kChunk;  // one past the newline
+      const uint32_t bytes = __popc(body & ((1u << to) - 1) & ~((1u << from) - 1));
+      if (fasta) {
+        if (line == 0) cls += bytes;
+        else if (!header) cls += (ull)bytes << 16;
+      } else {
+        cls += (ull)bytes << (16 * (line & 3));
+      }
+      if (!rest) break;
+      ++line;
+      from = to;
+      header = to < kChunk && (hdm >> to & 1);
+      rest &= rest - 1;
     }
   }
-  ull tot;
-  block_exscan(nl, Plus(), sh, &tot);
-  if (threadIdx.x == 0) t_nl[blockIdx.x] = tot;
-  if (fasta) {
-    block_exscan(hd, Plus(), sh, &tot);
-    if (threadIdx.x == 0) t_hd[blockIdx.x] = tot;
-  } else if (threadIdx.x == 0) {
-    t_hd[blockIdx.x] = 0;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    cls += __shfl_xor(cls, off);
+    hd += __shfl_xor(hd, off);
+    const uint32_t o = __shfl_xor(ls, off);
+    ls = o > ls ? o : ls;
   }
-  block_exscan(ls, Max(), sh, &tot);
-  if (threadIdx.x == 0) t_ls[blockIdx.x] = tot ? tile0 + tot : 0;
+  __shared__ ull s_cls[kTB / 64];
+  __shared__ uint32_t s_hd[kTB / 64], s_ls[kTB / 64];
+  if ((threadIdx.x & 63) == 0) {
+    s_cls[threadIdx.x >> 6] = cls;
+    s_hd[threadIdx.x >> 6] = hd;
+    s_ls[threadIdx.x >> 6] = ls;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kTB / 64; ++w) {
+      cls += s_cls[w];
+      hd += s_hd[w];
+      ls = s_ls[w] > ls ? s_ls[w] : ls;
+    }
+    ull nl = 0;
+    for (int r = 0; r < kRounds; ++r) nl += field(tot_nl4, r);
+    t_nl[blockIdx.x] = nl;
+    t_hd[blockIdx.x] = hd;
+    t_ls[blockIdx.x] = ls ? tile0 + ls : 0;
+    t_cls[blockIdx.x] = cls;
+  }
 }
 
 // Tile scans in two levels. Level 1 (many blocks): each group of 1024
 // consecutive tiles is scanned in place (exclusive, from 0) and its total
 // written to g[group]. Level 2 (one block): the group totals are scanned
-// (exclusive, from init); g[n_groups] = the reduction of everything. A tile's
+// (exclusive; a maximum from lo); g[n_groups] = the reduction of everything. A tile's
 // exclusive prefix is then op(g[tile >> 10], t[tile]). Up to three arrays
 // per launch; is_max selects the running maximum instead of the sum.
 constexpr int kScanGroup = 1024;
@@ -200,7 +321,6 @@ constexpr int kScanGroup = 1024;
 struct ScanArrays {
   ull* t[3];
   ull* g[3];
-  ull init[3];
   int is_max[3];
   int n;
 };
@@ -218,10 +338,11 @@ __global__ void __launch_bounds__(kScanGroup) k_fx_scan_groups(ScanArrays s, uin
   }
 }
 
-__global__ void __launch_bounds__(kScanGroup) k_fx_scan_top(ScanArrays s, uint64_t ng) {
+__global__ void __launch_bounds__(kScanGroup) k_fx_scan_top(ScanArrays s, uint64_t ng,
+                                                            const Info* __restrict__ info) {
   __shared__ ull sh[kScanGroup / 64];
   for (int a = 0; a < s.n; ++a) {
-    ull carry = s.init[a];
+    ull carry = s.is_max[a] ? info->lo : 0;  // the first line starts at lo
     for (uint64_t base = 0; base < ng; base += kScanGroup) {
       const uint64_t j = base + threadIdx.x;
       const ull v = j < ng ? s.g[a][j] : 0;
@@ -241,67 +362,136 @@ __global__ void __launch_bounds__(kScanGroup) k_fx_scan_top(ScanArrays s, uint64
   }
 }
 
-// Passes 2 (kWrite = false: kept bytes per tile into t_keep, FASTQ layout
-// check into err_line) and 3 (kWrite: t_keep holds each tile's output offset;
-// kept bytes and record offsets written). The per-round prefixes of the
-// tile's chunks come from one block scan each, the four rounds packed in
-// 16-bit fields (a round holds at most 4096 bytes).
-template <bool kWrite>
-__global__ void __launch_bounds__(kTB) k_fx_seq(const uint8_t* __restrict__ B, uint64_t lo,
-                                                uint64_t hi, int fasta,
-                                                const ull* __restrict__ t_nl,
-                                                const ull* __restrict__ t_hd,
-                                                const ull* __restrict__ t_ls,
-                                                const ull* __restrict__ g_nl,
-                                                const ull* __restrict__ g_hd,
-                                                const ull* __restrict__ g_ls,
-                                                ull* __restrict__ t_keep,
-                                                const ull* __restrict__ g_keep,
-                                                ull* __restrict__ err_line,
-                                                uint8_t* __restrict__ out_reads,
-                                                uint64_t* __restrict__ out_offsets) {
+// Kept bytes of each tile from its classes and the state at its start, scanned
+// within groups of kScanGroup tiles like the arrays above.
+__global__ void __launch_bounds__(kScanGroup) k_fx_keep_groups(
+    const uint8_t* __restrict__ B, const Info* __restrict__ info, const ull* __restrict__ t_nl,
+    const ull* __restrict__ t_ls, const ull* __restrict__ g_nl, const ull* __restrict__ g_ls,
+    const ull* __restrict__ t_cls, ull* __restrict__ t_keep, ull* __restrict__ g_keep,
+    uint64_t nt) {
+  __shared__ ull sh[kScanGroup / 64];
+  const uint64_t i = (uint64_t)blockIdx.x * kScanGroup + threadIdx.x;
+  ull v = 0;
+  if (i < nt && info->lo < info->hi) {
+    const ull cls = t_cls[i];
+    if (info->fasta) {
+      const ull ls = g_ls[blockIdx.x] > t_ls[i] ? g_ls[blockIdx.x] : t_ls[i];
+      v = field(cls, 1) + (B[ls] == '>' ? 0 : field(cls, 0));
+    } else {
+      const uint32_t line = (uint32_t)(g_nl[blockIdx.x] + t_nl[i]);
+      v = field(cls, (1u - line) & 3u);
+    }
+  }
+  ull total;
+  const ull ex = block_exscan<Plus, kScanGroup>(v, Plus(), sh, &total);
+  if (i < nt) t_keep[i] = ex;
+  if (threadIdx.x == 0) g_keep[blockIdx.x] = total;
+}
+
+// The L low bytes of v to p, any alignment.
+__device__ __forceinline__ void store_bytes(uint8_t* p, unsigned __int128 v, uint32_t L) {
+  if (L == kChunk) {
+    __builtin_memcpy(p, &v, 16);
+    return;
+  }
+  ull w = (ull)v;
+  if (L & 8) {
+    __builtin_memcpy(p, &w, 8);
+    w = (ull)(v >> 64);
+    p += 8;
+  }
+  uint32_t x = (uint32_t)w;
+  if (L & 4) {
+    __builtin_memcpy(p, &x, 4);
+    x = (uint32_t)(w >> 32);
+    p += 4;
+  }
+  if (L & 2) {
+    p[0] = (uint8_t)x;
+    p[1] = (uint8_t)(x >> 8);
+    x >>= 16;
+    p += 2;
+  }
+  if (L & 1) *p = (uint8_t)x;
+}
+
+// Pass 2: kept bytes and record offsets written, FASTQ layout checked. The
+// per-round prefixes of the tile's chunks come from one block scan each, the
+// four rounds packed in 16-bit fields (a round holds at most 4096 bytes).
+// Nothing is written unless the outputs have room for all of it and the text
+// can be of the format; out_offsets[records] is written by the last block.
+__global__ void __launch_bounds__(kTB) k_fx_write(const uint8_t* __restrict__ B, Info* info,
+                                                  const ull* __restrict__ t_nl,
+                                                  const ull* __restrict__ t_hd,
+                                                  const ull* __restrict__ t_ls,
+                                                  const ull* __restrict__ g_nl,
+                                                  const ull* __restrict__ g_hd,
+                                                  const ull* __restrict__ g_ls,
+                                                  const ull* __restrict__ t_keep,
+                                                  const ull* __restrict__ g_keep,
+                                                  uint8_t* __restrict__ out_reads,
+                                                  uint64_t reads_capacity,
+                                                  uint64_t* __restrict__ out_offsets,
+                                                  uint64_t max_records, uint64_t ng) {
   __shared__ ull sh[kTB / 64];
-  __shared__ uint8_t stage[kWrite ? kTile : 1];
+  const uint64_t lo = info->lo, hi = info->hi;
+  if (lo >= hi) return;
+  const uint32_t fasta = info->fasta;
+  const ull lines = g_nl[ng] + 1, keep_all = g_keep[ng];
+  const ull records = fasta ? g_hd[ng] : lines / 4;
+  const bool fits = (fasta ? info->first == '>' : lines % 4 == 0) && records <= max_records;
+  const bool store = fits && keep_all <= reads_capacity && (out_reads || !keep_all);
+  if (!fits) return;
+  if (store && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out_offsets[records] = keep_all;
   const uint64_t tile0 = (uint64_t)blockIdx.x * kTile;
   const Chunks c = load_tile(B, tile0, lo, hi);
   const uint64_t grp = blockIdx.x / kScanGroup;
   const ull c_nl = g_nl[grp] + t_nl[blockIdx.x];
-  const ull c_ls = g_ls[grp] > t_ls[blockIdx.x] ? g_ls[grp] : t_ls[blockIdx.x];
-
-  ull nl4 = 0, ls4 = 0;
+  ull nl4 = 0;
 #pragma unroll
-  for (int r = 0; r < kRounds; ++r) {
-    nl4 |= (ull)__popc(c.nl[r]) << (16 * r);
-    ls4 |= (ull)last_start(c.nl[r], r) << (16 * r);
-  }
-  ull tot_nl4, tot_ls4;
+  for (int r = 0; r < kRounds; ++r) nl4 |= (ull)__popc(c.nl[r]) << (16 * r);
+  ull tot_nl4;
   const ull ex_nl4 = block_exscan(nl4, Plus(), sh, &tot_nl4);
-  const ull ex_ls4 = block_exscan(ls4, Max4(), sh, &tot_ls4);
+  // FASTA: where the line open at each chunk's first byte starts
+  ull ex_ls4 = 0, tot_ls4 = 0, c_ls = 0;
+  if (fasta) {
+    c_ls = g_ls[grp] > t_ls[blockIdx.x] ? g_ls[grp] : t_ls[blockIdx.x];
+    ull ls4 = 0;
+#pragma unroll
+    for (int r = 0; r < kRounds; ++r) ls4 |= (ull)last_start(c.nl[r], r) << (16 * r);
+    ex_ls4 = block_exscan(ls4, Max4(), sh, &tot_ls4);
+  }
 
-  // per chunk: line index and line start at its first byte, line-start and
-  // kept masks
+  // per chunk: line index at its first byte, line-start (FASTA: header-start)
+  // and kept masks
   uint32_t keep[kRounds], starts[kRounds];
-  ull line0[kRounds];
+  uint32_t line0[kRounds];  // relative to c_nl
   uint32_t nl_before = 0, ls_before = 0;  // earlier rounds of this tile
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
     const uint64_t pos = tile0 + ((uint64_t)r * kTB + threadIdx.x) * kChunk;
-    const ull L = c_nl + nl_before + field(ex_nl4, r);
+    line0[r] = nl_before + field(ex_nl4, r);
     const uint32_t lsl = ls_before > field(ex_ls4, r) ? ls_before : field(ex_ls4, r);
-    const ull ls0 = lsl ? tile0 + lsl : c_ls;  // <= pos, except lo inside the first chunk
     nl_before += field(tot_nl4, r);
     ls_before = ls_before > field(tot_ls4, r) ? ls_before : field(tot_ls4, r);
     const uint32_t m = c.m[r], nlm = c.nl[r];
+    keep[r] = starts[r] = 0;
+    // the byte before the chunk: from the neighbour lane (its last byte is not
+    // a newline where it lies before lo), or from memory
+    uint32_t before = __shfl_up(nlm >> (kChunk - 1), 1u, 64);
+    if (!m) continue;
+    if ((threadIdx.x & 63) == 0) before = pos > lo && B[pos - 1] == '\n' ? 1u : 0u;
     uint32_t st = (nlm << 1) & 0xFFFFu;
-    if (ls0 >= pos && ls0 < pos + kChunk) st |= 1u << (uint32_t)(ls0 - pos);
+    if (pos > lo) st |= before;
+    else st |= 1u << (uint32_t)(lo - pos);
     st &= m;
-    const uint32_t crm = eq_mask(c.v[r], '\r');
     uint32_t k = 0;
     if (fasta) {
       // segments between line starts; a segment is kept unless its line is
       // a header
+      const ull ls0 = lsl ? tile0 + lsl : c_ls;
       const uint32_t hdm = st & eq_mask(c.v[r], '>');
-      bool hh = m && ls0 < pos && B[ls0] == '>';
+      bool hh = ls0 < pos && B[ls0] == '>';
       uint32_t from = 0;
       for (uint32_t rest = st;;) {
         const uint32_t to = rest ? (uint32_t)__ffs(rest) - 1 : kChunk;  // next line start
@@ -314,7 +504,7 @@ __global__ void __launch_bounds__(kTB) k_fx_seq(const uint8_t* __restrict__ B, u
       starts[r] = hdm;
     } else {
       // segments ending at newlines; lines 4i + 1 are kept
-      uint32_t l = (uint32_t)L, from = 0;
+      uint32_t l = (uint32_t)c_nl + line0[r], from = 0;
       for (uint32_t rest = nlm;;) {
         const uint32_t to = rest ? (uint32_t)__ffs(rest) : kChunk;  // one past the newline
         if ((l & 3) == 1) k |= ((1u << to) - 1) & ~((1u << from) - 1);
@@ -323,35 +513,26 @@ __global__ void __launch_bounds__(kTB) k_fx_seq(const uint8_t* __restrict__ B, u
         from = to;
         rest &= rest - 1;
       }
-      if (!kWrite) {
-        // layout check at line starts: '@' on header lines, '+' on separators
-        for (uint32_t s = st; s;) {
-          const int j = __ffs(s) - 1;
-          s &= s - 1;
-          const ull lj = L + __popc(nlm & ((1u << j) - 1));
-          const uint32_t b = byte_of(c.v[r], j);
-          if (((lj & 3) == 0 && b != '@') || ((lj & 3) == 2 && b != '+')) atomicMin(err_line, lj);
-        }
+      // layout check at line starts: '@' on header lines, '+' on separators
+      for (uint32_t s = st; s;) {
+        const int j = __ffs(s) - 1;
+        s &= s - 1;
+        const ull lj = c_nl + line0[r] + __popc(nlm & ((1u << j) - 1));
+        const uint32_t b = byte_of(c.v[r], j);
+        if (((lj & 3) == 0 && b != '@') || ((lj & 3) == 2 && b != '+')) atomicMin(&info->err, lj);
       }
       starts[r] = st;
     }
-    keep[r] = k & m & ~nlm & ~crm;
-    line0[r] = L;
+    if (k) k &= m & ~nlm & ~eq_mask(c.v[r], '\r');
+    keep[r] = k;
   }
+  if (!store) return;
 
   ull kp4 = 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) kp4 |= (ull)__popc(keep[r]) << (16 * r);
   ull tot_kp4;
   const ull ex_kp4 = block_exscan(kp4, Plus(), sh, &tot_kp4);
-  uint32_t tile_keep = 0;
-#pragma unroll
-  for (int r = 0; r < kRounds; ++r) tile_keep += field(tot_kp4, r);
-  if (!kWrite) {
-    if (threadIdx.x == 0) t_keep[blockIdx.x] = tile_keep;
-    return;
-  }
-
   const ull out0 = g_keep[grp] + t_keep[blockIdx.x];
   ull hd_ex4 = 0, tot_hd4 = 0;
   if (fasta) {
@@ -363,7 +544,7 @@ __global__ void __launch_bounds__(kTB) k_fx_seq(const uint8_t* __restrict__ B, u
   uint32_t kp_before = 0, hd_before = 0;
 #pragma unroll
   for (int r = 0; r < kRounds; ++r) {
-    uint32_t at = kp_before + field(ex_kp4, r);  // tile-local output position
+    const ull at = out0 + kp_before + field(ex_kp4, r);  // output position of the chunk
     kp_before += field(tot_kp4, r);
     const uint32_t km = keep[r];
     // record offsets: FASTA header starts; FASTQ starts of sequence lines
@@ -372,31 +553,41 @@ __global__ void __launch_bounds__(kTB) k_fx_seq(const uint8_t* __restrict__ B, u
       for (uint32_t s = starts[r]; s;) {
         const int j = __ffs(s) - 1;
         s &= s - 1;
-        out_offsets[h++] = out0 + at + __popc(km & ((1u << j) - 1));
+        out_offsets[h++] = at + __popc(km & ((1u << j) - 1));
       }
       hd_before += field(tot_hd4, r);
     } else {
       for (uint32_t s = starts[r]; s;) {
         const int j = __ffs(s) - 1;
         s &= s - 1;
-        const ull lj = line0[r] + __popc(c.nl[r] & ((1u << j) - 1));
-        if ((lj & 3) == 1) out_offsets[lj >> 2] = out0 + at + __popc(km & ((1u << j) - 1));
+        const ull lj = c_nl + line0[r] + __popc(c.nl[r] & ((1u << j) - 1));
+        if ((lj & 3) == 1) out_offsets[lj >> 2] = at + __popc(km & ((1u << j) - 1));
       }
     }
-#pragma unroll
-    for (int j = 0; j < kChunk; ++j)
-      if (km >> j & 1) stage[at++] = (uint8_t)byte_of(c.v[r], j);
+    // the kept bytes, a run at a time
+    uint8_t* o = out_reads + at;
+    const unsigned __int128 v =
+        ((unsigned __int128)((ull)c.v[r].w << 32 | c.v[r].z) << 64) | ((ull)c.v[r].y << 32 | c.v[r].x);
+    for (uint32_t rest = km; rest;) {
+      const int from = __ffs(rest) - 1;
+      const uint32_t L = __ffs(~(rest >> from)) - 1;  // (bits 16.. of rest are 0)
+      store_bytes(o, v >> (8 * from), L);
+      o += L;
+      rest &= ~(((1u << L) - 1) << from);
+    }
   }
-  __syncthreads();
-  for (uint32_t i = threadIdx.x; i < tile_keep; i += kTB) out_reads[out0 + i] = stage[i];
 }
 
-__global__ void k_fx_fill(ull* p, ull v) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *p = v;
-}
-
-__global__ void k_fx_last(uint64_t* out_offsets, uint64_t n_records, const ull* total) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) out_offsets[n_records] = *total;
+// The results, to the host.
+__global__ void k_fx_publish(const Info* __restrict__ info, const ull* __restrict__ g_nl,
+                             const ull* __restrict__ g_hd, const ull* __restrict__ g_keep,
+                             uint64_t ng, Info* pub) {
+  if (threadIdx.x != 0) return;
+  Info r = *info;
+  r.newlines = g_nl[ng];
+  r.headers = g_hd[ng];
+  r.keep = g_keep[ng];
+  *pub = r;
 }
 
 struct Fail {
@@ -417,8 +608,6 @@ int bad(const std::string& msg) {
 }
 
 bool is_eol(uint8_t b) { return b == '\n' || b == '\r'; }
-
-constexpr uint64_t kPeek = 4096;
 
 // First position in [lo, hi) whose byte is not CR/LF, scanning forward
 // (dir > 0), or last such position + 1 scanning backward; hi / lo if none.
@@ -446,42 +635,17 @@ uint64_t trim(const uint8_t* text, uint64_t lo, uint64_t hi, int dir, hipStream_
   return lo;
 }
 
-// Trimmed range [*s0, *e0) and its first byte, with one round trip when the
-// text's first and last kPeek bytes each hold a byte that is not CR/LF.
-void trim_both(const uint8_t* text, uint64_t n, hipStream_t st, uint64_t* s0, uint64_t* e0,
-               uint8_t* first) {
-  uint8_t head[kPeek], tail[kPeek];
-  const uint64_t nh = n < kPeek ? n : kPeek;
-  chk(hipMemcpyAsync(head, text, nh, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-  chk(hipMemcpyAsync(tail, text + n - nh, nh, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-  chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-  uint64_t s = nh;
-  for (uint64_t i = 0; i < nh; ++i)
-    if (!is_eol(head[i])) {
-      s = i;
-      break;
-    }
-  if (s == nh) s = trim(text, nh, n, 1, st);
-  if (s >= n) {
-    *s0 = *e0 = n;
-    return;
+// Device temporaries and host-visible words of the calling thread, kept
+// between calls.
+void* scratch(size_t bytes, hipStream_t st) {
+  std::string err;
+  int code = KC_E_NOMEM;
+  void* p = kc::thread_scratch(bytes, st, &err, &code);
+  if (!p) {
+    kc::set_last_error(err);
+    throw Fail{code};
   }
-  uint64_t e = 0;
-  for (uint64_t i = nh; i > 0; --i)
-    if (!is_eol(tail[i - 1])) {
-      e = n - nh + i;
-      break;
-    }
-  // a tail of line ends only lies after s (s holds a byte that is not CR/LF)
-  if (e == 0) e = trim(text, s, n - nh, -1, st);
-  *s0 = s;
-  *e0 = e > s ? e : s + 1;  // s holds a byte that is not CR/LF
-  if (s < nh) {
-    *first = head[s];
-  } else {
-    chk(hipMemcpyAsync(first, text + s, 1, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-  }
+  return p;
 }
 
 }  // namespace
@@ -499,124 +663,116 @@ extern "C" int kc_parse_fastx(const uint8_t* text, uint64_t n_bytes, int format,
   if (n_bytes && !text) return bad("text is NULL");
   if (!out_offsets) return bad("out_offsets is NULL");
   const hipStream_t st = (hipStream_t)stream;
-  void* d = nullptr;
   try {
-    uint64_t s0 = 0, e0 = 0;
-    uint8_t first = 0;
-    if (n_bytes) trim_both(text, n_bytes, st, &s0, &e0, &first);
-    if (s0 >= e0) {  // nothing but line ends: no records
+    if (!n_bytes) {
+      const uint64_t zero = 0;
+      chk(hipMemcpyAsync(out_offsets, &zero, 8, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
+      chk(hipStreamSynchronize(st), "hipStreamSynchronize");
+      return KC_OK;
+    }
+    // positions relative to the 16-byte aligned base B; the text is [a, a + n)
+    const uint64_t a = (uint64_t)(uintptr_t)text & 15u;
+    const uint8_t* B = text - a;
+    const uint64_t nt = (a + n_bytes + kTile - 1) / kTile;
+    if (nt > 0x7fffffffull) return bad("text too large");
+    const uint64_t ng = (nt + kScanGroup - 1) / kScanGroup;
+    ull* t_nl = (ull*)scratch((5 * nt + 4 * (ng + 1)) * sizeof(ull) + sizeof(Info), st);
+    ull* t_hd = t_nl + nt;
+    ull* t_ls = t_hd + nt;
+    ull* t_cls = t_ls + nt;
+    ull* t_keep = t_cls + nt;
+    ull* g_nl = t_keep + nt;
+    ull* g_hd = g_nl + (ng + 1);
+    ull* g_ls = g_hd + (ng + 1);
+    ull* g_keep = g_ls + (ng + 1);
+    Info* info = (Info*)(g_keep + (ng + 1));
+    std::string err;
+    int code = KC_E_NOMEM;
+    void* pub_dev = nullptr;
+    Info* const pub = (Info*)kc::thread_pinned(sizeof(Info), &pub_dev, &err, &code);
+    if (!pub) {
+      kc::set_last_error(err);
+      return code;
+    }
+    ScanArrays sa3 = {{t_nl, t_hd, t_ls}, {g_nl, g_hd, g_ls}, {0, 0, 1}, 3};
+    ScanArrays sa1 = {{t_keep, nullptr, nullptr}, {g_keep, nullptr, nullptr}, {0, 0, 0}, 1};
+    const auto passes = [&] {
+      hipLaunchKernelGGL(k_fx_lines, dim3((unsigned)nt), dim3(kTB), 0, st, B, info, t_nl, t_hd,
+                         t_ls, t_cls);
+      hipLaunchKernelGGL(k_fx_scan_groups, dim3((unsigned)ng), dim3(kScanGroup), 0, st, sa3, nt);
+      hipLaunchKernelGGL(k_fx_scan_top, dim3(1), dim3(kScanGroup), 0, st, sa3, ng, info);
+      hipLaunchKernelGGL(k_fx_keep_groups, dim3((unsigned)ng), dim3(kScanGroup), 0, st, B, info,
+                         t_nl, t_ls, g_nl, g_ls, t_cls, t_keep, g_keep, nt);
+      hipLaunchKernelGGL(k_fx_scan_top, dim3(1), dim3(kScanGroup), 0, st, sa1, ng, info);
+      hipLaunchKernelGGL(k_fx_write, dim3((unsigned)nt), dim3(kTB), 0, st, B, info, t_nl, t_hd,
+                         t_ls, g_nl, g_hd, g_ls, t_keep, g_keep, out_reads, reads_capacity,
+                         out_offsets, max_records, ng);
+      hipLaunchKernelGGL(k_fx_publish, dim3(1), dim3(64), 0, st, info, g_nl, g_hd, g_keep, ng,
+                         (Info*)pub_dev);
+      chk(hipGetLastError(), "parse launch");
+      chk(hipStreamSynchronize(st), "hipStreamSynchronize");
+    };
+    hipLaunchKernelGGL(k_fx_ends, dim3(1), dim3(kTB), 0, st, text, n_bytes, a, format, info);
+    passes();
+    if (pub->missing) {
+      // more than kPeek line ends at an end of the text: the host looks past them
+      const uint64_t s0 = trim(text, 0, n_bytes, 1, st);
+      const uint64_t e0 = s0 < n_bytes ? trim(text, s0, n_bytes, -1, st) : s0;
+      if (s0 < e0) {
+        Info in = *pub;
+        in.lo = a + s0;
+        in.hi = a + e0;
+        in.missing = 0;
+        in.err = ~0ull;
+        uint8_t first = 0;
+        chk(hipMemcpyAsync(&first, text + s0, 1, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
+        chk(hipStreamSynchronize(st), "hipStreamSynchronize");
+        in.first = first;
+        in.fasta = format == KC_FASTA || (format == KC_FASTX_AUTO && first == '>');
+        chk(hipMemcpyAsync(info, &in, sizeof(in), hipMemcpyHostToDevice, st), "hipMemcpyAsync");
+        passes();
+      }
+    }
+    const Info r = *pub;
+    if (r.lo >= r.hi) {  // nothing but line ends: no records
       const uint64_t zero = 0;
       chk(hipMemcpyAsync(out_offsets, &zero, 8, hipMemcpyHostToDevice, st), "hipMemcpyAsync");
       chk(hipStreamSynchronize(st), "hipStreamSynchronize");
       return KC_OK;
     }
     if (format == KC_FASTX_AUTO) {
-      if (first == '@') format = KC_FASTQ;
-      else if (first == '>') format = KC_FASTA;
+      if (r.first == '@') format = KC_FASTQ;
+      else if (r.first == '>') format = KC_FASTA;
       else return bad("the text starts with neither '@' (FASTQ) nor '>' (FASTA)");
     }
     if (format_out) *format_out = format;
-    if (format == KC_FASTA && first != '>') return bad("FASTA text does not start with '>'");
-    const int fasta = format == KC_FASTA;
-
-    // positions relative to the 16-byte aligned base B; the text is [lo, hi)
-    const uint64_t a = (uint64_t)(uintptr_t)(text + s0) & 15u;
-    const uint8_t* B = text + s0 - a;
-    const uint64_t lo = a, hi = a + (e0 - s0);
-    const uint64_t nt = (hi + kTile - 1) / kTile;
-    if (nt > 0x7fffffffull) return bad("text too large");
-    const uint64_t ng = (nt + kScanGroup - 1) / kScanGroup;
-    chk(hipMallocAsync(&d, (4 * nt + 4 * (ng + 1) + 1) * sizeof(ull), st), "hipMallocAsync");
-    ull* t_nl = (ull*)d;
-    ull* t_hd = t_nl + nt;
-    ull* t_ls = t_hd + nt;
-    ull* t_keep = t_ls + nt;
-    ull* g_nl = t_keep + nt;
-    ull* g_hd = g_nl + (ng + 1);
-    ull* g_ls = g_hd + (ng + 1);
-    ull* g_keep = g_ls + (ng + 1);
-    ull* err = g_keep + (ng + 1);
-    ScanArrays sa3 = {{t_nl, t_hd, t_ls}, {g_nl, g_hd, g_ls}, {0, 0, (ull)lo}, {0, 0, 1}, 3};
-    ScanArrays sa1 = {{t_keep, nullptr, nullptr}, {g_keep, nullptr, nullptr}, {0, 0, 0},
-                      {0, 0, 0}, 1};
-    hipLaunchKernelGGL(k_fx_fill, dim3(1), dim3(64), 0, st, err, ~0ull);
-    hipLaunchKernelGGL(k_fx_lines, dim3((unsigned)nt), dim3(kTB), 0, st, B, lo, hi, fasta, t_nl,
-                       t_hd, t_ls);
-    hipLaunchKernelGGL(k_fx_scan_groups, dim3((unsigned)ng), dim3(kScanGroup), 0, st, sa3, nt);
-    hipLaunchKernelGGL(k_fx_scan_top, dim3(1), dim3(kScanGroup), 0, st, sa3, ng);
-    chk(hipGetLastError(), "parse launch");
-    ull tot[2] = {0, 0};
-    chk(hipMemcpyAsync(&tot[0], g_nl + ng, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    chk(hipMemcpyAsync(&tot[1], g_hd + ng, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-    const uint64_t lines = tot[0] + 1;  // the trimmed text does not end with a newline
-    if (!fasta && lines % 4) {
-      chk(hipFreeAsync(d, st), "hipFreeAsync");
-      d = nullptr;
+    if (format == KC_FASTA && r.first != '>') return bad("FASTA text does not start with '>'");
+    const uint64_t lines = r.newlines + 1;  // the trimmed text does not end with a newline
+    if (!r.fasta && lines % 4)
       return bad("FASTQ text has " + std::to_string(lines) +
                  " lines, not a whole number of 4-line records");
-    }
-    const uint64_t R = fasta ? tot[1] : lines / 4;
+    const uint64_t R = r.fasta ? r.headers : lines / 4;
     *n_records = R;
     if (R > max_records) {
-      chk(hipFreeAsync(d, st), "hipFreeAsync");
-      d = nullptr;
-      chk(hipStreamSynchronize(st), "hipStreamSynchronize");
       kc::set_last_error("out_offsets has room for " + std::to_string(max_records) +
                          " records, the text holds " + std::to_string(R));
       return KC_E_CAPACITY;
     }
-    hipLaunchKernelGGL(k_fx_seq<false>, dim3((unsigned)nt), dim3(kTB), 0, st, B, lo, hi, fasta,
-                       t_nl, t_hd, t_ls, g_nl, g_hd, g_ls, t_keep, g_keep, err, nullptr, nullptr);
-    hipLaunchKernelGGL(k_fx_scan_groups, dim3((unsigned)ng), dim3(kScanGroup), 0, st, sa1, nt);
-    hipLaunchKernelGGL(k_fx_scan_top, dim3(1), dim3(kScanGroup), 0, st, sa1, ng);
-    chk(hipGetLastError(), "parse launch");
-    // the kept bytes are at most hi - lo: with that much room the write pass
-    // follows at once and the checks are read after it
-    const bool room = out_reads && reads_capacity >= hi - lo;
-    ull res[2] = {0, ~0ull};  // kept bytes, first malformed FASTQ line (none: all ones)
-    if (!room) {
-      chk(hipMemcpyAsync(&res[0], g_keep + ng, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-      chk(hipMemcpyAsync(&res[1], err, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-      chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-      if (res[1] == ~0ull && res[0] > reads_capacity) {
-        *n_bases = res[0];
-        chk(hipFreeAsync(d, st), "hipFreeAsync");
-        d = nullptr;
-        chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-        kc::set_last_error("out_reads has room for " + std::to_string(reads_capacity) +
-                           " bytes, the sequences hold " + std::to_string(res[0]));
-        return KC_E_CAPACITY;
-      }
-      if (res[1] == ~0ull && res[0] && !out_reads) {
-        chk(hipFreeAsync(d, st), "hipFreeAsync");
-        d = nullptr;
-        return bad("out_reads is NULL");
-      }
-    }
-    if (res[1] == ~0ull) {
-      hipLaunchKernelGGL(k_fx_seq<true>, dim3((unsigned)nt), dim3(kTB), 0, st, B, lo, hi, fasta,
-                         t_nl, t_hd, t_ls, g_nl, g_hd, g_ls, t_keep, g_keep, err, out_reads,
-                         out_offsets);
-      hipLaunchKernelGGL(k_fx_last, dim3(1), dim3(64), 0, st, out_offsets, R, g_keep + ng);
-      chk(hipGetLastError(), "parse launch");
-    }
-    if (room) {
-      chk(hipMemcpyAsync(&res[0], g_keep + ng, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-      chk(hipMemcpyAsync(&res[1], err, 8, hipMemcpyDeviceToHost, st), "hipMemcpyAsync");
-    }
-    chk(hipFreeAsync(d, st), "hipFreeAsync");
-    d = nullptr;
-    chk(hipStreamSynchronize(st), "hipStreamSynchronize");
-    if (res[1] != ~0ull) {
+    if (r.err != ~0ull) {
       *n_records = 0;
-      const uint64_t l = res[1];
+      const uint64_t l = r.err;
       return bad("FASTQ line " + std::to_string(l) + " (counting from 0) should start with '" +
                  ((l & 3) == 0 ? "@" : "+") + "'");
     }
-    *n_bases = res[0];
+    if (r.keep > reads_capacity) {
+      *n_bases = r.keep;
+      kc::set_last_error("out_reads has room for " + std::to_string(reads_capacity) +
+                         " bytes, the sequences hold " + std::to_string(r.keep));
+      return KC_E_CAPACITY;
+    }
+    if (r.keep && !out_reads) return bad("out_reads is NULL");
+    *n_bases = r.keep;
   } catch (const Fail& f) {
-    if (d) (void)hipFreeAsync(d, st);
     return f.code;
   }
   return KC_OK;
