@@ -520,6 +520,38 @@ __device__ __forceinline__ uint32_t shard_of(const K& key, int keybits, int shar
   return (uint32_t)(key >> (keybits - shard_bits));
 }
 
+// Sets of a batch that the bytes [g0, g1) lie in: lo to hi; any: one of them is
+// in the class being counted. The same for a whole workgroup, so that its
+// threads search between lo and hi only (mostly one set), and tiles of other
+// classes' sets are passed over.
+struct SetRange {
+  uint32_t lo, hi;
+  bool any;
+};
+__device__ __forceinline__ SetRange sets_of(const BatchSets& bs, uint64_t g0, uint64_t g1) {
+  uint32_t lo = 0, hi = bs.n_sets - 1;  // last set whose first byte is <= g0
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (bs.set_byte_off[mid] <= g0) lo = mid; else hi = mid - 1;
+  }
+  SetRange r{lo, lo, bs.set_local[lo] != kNoSet};
+  while (r.hi + 1 < bs.n_sets && bs.set_byte_off[r.hi + 1] < g1) {
+    ++r.hi;
+    r.any |= bs.set_local[r.hi] != kNoSet;
+  }
+  return r;
+}
+
+// Set of byte g among those of r.
+__device__ __forceinline__ uint32_t set_of(const BatchSets& bs, const SetRange& r, uint64_t g) {
+  uint32_t lo = r.lo, hi = r.hi;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (bs.set_byte_off[mid] <= g) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 // Keys of a thread's S window starts. Plain counting: the canonical k-mer. In
 // a batch of read sets, the key of a window is (set id within its k-class <<
 // 2k) | canonical k-mer, so that sorting keys sorts by set, then k-mer; windows
@@ -527,7 +559,7 @@ __device__ __forceinline__ uint32_t shard_of(const K& key, int keybits, int shar
 template <typename K, typename Kc, int S, bool BATCH>
 __device__ __forceinline__ uint32_t window_keys(const uint64_t* __restrict__ packed, uint64_t g,
                                                 int k, uint32_t vm, const BatchSets& bs,
-                                                K (&key)[S]) {
+                                                const SetRange& range, K (&key)[S]) {
   Kc c[S];
   if constexpr (Key<Kc>::kWords == 4) {
     const uint64_t w = g >> 5;
@@ -545,12 +577,7 @@ __device__ __forceinline__ uint32_t window_keys(const uint64_t* __restrict__ pac
     for (int i = 0; i < S; ++i) key[i] = (K)c[i];
     return vm;
   } else {
-  uint32_t lo = 0, hi = bs.n_sets - 1;  // last set whose first byte is <= g
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (bs.set_byte_off[mid] <= g) lo = mid; else hi = mid - 1;
-  }
-  uint32_t set = lo;
+  uint32_t set = set_of(bs, range, g);
 #pragma unroll
   for (int i = 0; i < S; ++i) {
     if (!(vm & (1u << i))) continue;
@@ -591,38 +618,56 @@ __global__ void __launch_bounds__(TB) k_window_hist(const uint64_t* __restrict__
   const int nb = 1 << shard_bits;
   for (int i = threadIdx.x; i < nb; i += TB) sh[i] = 0;
   __syncthreads();
-  for (uint64_t g = w_begin + ((uint64_t)blockIdx.x * TB + threadIdx.x) * S; g < w_end;
-       g += (uint64_t)gridDim.x * TB * S) {
+  // Only the shard is needed: set id bits (batch), then kb bits of the canonical
+  // k-mer, whose top bits are the smaller of the top bits of fwd and of rc (if
+  // those are equal, so are both keys' top bits). The top 10 bits of fwd are
+  // its first 5 bases, those of rc the complements of its last 5 bases, last
+  // first: whole keys are not built, whatever their width (four words: 0.50 ->
+  // KC_H1 ms on 1,000,000 reads).
+  const int kb = BATCH ? shard_bits - (keybits - 2 * k) : shard_bits;
+  const bool ends = S <= 8 && k >= 5 && kb >= 0 && kb <= 10;
+  for (uint64_t unit = w_begin + (uint64_t)blockIdx.x * TB * S; unit < w_end;
+       unit += (uint64_t)gridDim.x * TB * S) {
+    SetRange range{0, 0, true};
+    if constexpr (BATCH) {
+      range = sets_of(bs, unit, min(w_end, unit + (uint64_t)TB * S));
+      if (!range.any) continue;
+    }
+    const uint64_t g = unit + (uint64_t)threadIdx.x * S;
+    if (g >= w_end) continue;
     uint32_t vm = valid_starts<S>(valid, g);
     if (!vm) continue;
-    if constexpr (!BATCH && std::is_same<Kc, uint64_t>::value && S <= 8) {
-      if (k >= 5) {
-        // only the shard is needed: the top bits of min(fwd, rc) are the
-        // smaller of the top bits of fwd and of rc (if those are equal, so
-        // are both keys' top bits). The top 10 bits of fwd are its first 5
-        // bases, those of rc the complements of its last 5 bases, last first.
-        const uint64_t w0 = g >> 5;
-        const uint64_t p0 = packed[w0], p1 = packed[w0 + 1];
-        const int s0 = (int)(g & 31);
-        const uint32_t head = bits24(p0, p1, 2 * s0);            // bases g .. g+11
-        const uint32_t tail = bits24(p0, p1, 2 * (s0 + k - 5));  // bases g+k-5 .. g+k+6
-        // the 12 head bases in reverse order (each base's 2-bit code kept):
-        // reverse all bits, then swap the two bits of every base
-        const uint32_t hb = __builtin_bitreverse32(head) >> 8;
-        const uint32_t hr = ((hb >> 1) & 0x555555u) | ((hb & 0x555555u) << 1);
+    if (ends) {
+      const uint64_t w0 = g >> 5, wt = (g + k - 5) >> 5;
+      const uint64_t p0 = packed[w0], p1 = packed[w0 + 1];
+      const uint32_t head = bits24(p0, p1, 2 * (int)(g & 31));  // bases g .. g+11
+      const uint32_t tail = Key<Kc>::kWords == 1                // bases g+k-5 .. g+k+6
+                                ? bits24(p0, p1, 2 * ((int)(g & 31) + k - 5))
+                                : bits24(packed[wt], packed[wt + 1], 2 * (int)((g + k - 5) & 31));
+      // the 12 head bases in reverse order (each base's 2-bit code kept):
+      // reverse all bits, then swap the two bits of every base
+      const uint32_t hb = __builtin_bitreverse32(head) >> 8;
+      const uint32_t hr = ((hb >> 1) & 0x555555u) | ((hb & 0x555555u) << 1);
+      uint32_t set = BATCH ? set_of(bs, range, g) : 0u;
 #pragma unroll
-        for (int i = 0; i < S; ++i) {
-          if (!(vm & (1u << i))) continue;
-          // bases g+i .. g+i+4, the first most significant
-          const uint32_t f = (hr >> (2 * (7 - i))) & 0x3FFu;
-          const uint32_t r = ((tail >> (2 * i)) & 0x3FFu) ^ 0x3FFu;
-          atomicAdd(&sh[min(f, r) >> (10 - shard_bits)], 1u);
+      for (int i = 0; i < S; ++i) {
+        if (!(vm & (1u << i))) continue;
+        uint32_t at = 0;
+        if constexpr (BATCH) {
+          while (set < range.hi && g + i >= bs.set_byte_off[set + 1]) ++set;
+          const uint32_t loc = bs.set_local[set];
+          if (loc == kNoSet) continue;
+          at = loc << kb;
         }
-        continue;
+        // bases g+i .. g+i+4, the first most significant
+        const uint32_t f = (hr >> (2 * (7 - i))) & 0x3FFu;
+        const uint32_t r = ((tail >> (2 * i)) & 0x3FFu) ^ 0x3FFu;
+        atomicAdd(&sh[at + (min(f, r) >> (10 - kb))], 1u);
       }
+      continue;
     }
     K keys[S];
-    vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, keys);
+    vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, range, keys);
 #pragma unroll
     for (int i = 0; i < S; ++i)
       if (vm & (1u << i)) atomicAdd(&sh[shard_of(keys[i], keybits, shard_bits)], 1u);
@@ -659,6 +704,11 @@ __device__ __forceinline__ void window_scatter_body(const uint64_t* __restrict__
     // turn) then write adjacent runs, whose shared 64-byte segments meet in
     // that XCD's L2 instead of going to memory in halves
     unsigned long long* const cls_cursor = cursor + (tile % kXcds) * (uint64_t)nb;
+    SetRange range{0, 0, true};
+    if constexpr (BATCH) {
+      range = sets_of(bs, (t_begin + tile * TB) * S, min(t_end, t_begin + (tile + 1) * TB) * S);
+      if (!range.any) continue;
+    }
     for (int i = threadIdx.x; i < nb; i += TB) loff[i] = 0;
     __syncthreads();
     const uint64_t t = t_begin + tile * TB + threadIdx.x;
@@ -667,7 +717,7 @@ __device__ __forceinline__ void window_scatter_body(const uint64_t* __restrict__
     K key[S];
     uint32_t rank[S];  // (the shard is recomputed from the key: fewer live registers)
     if (vm) {
-      vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, key);
+      vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, range, key);
 #pragma unroll
       for (int i = 0; i < S; ++i)
         if (vm & (1u << i)) rank[i] = atomicAdd(&loff[shard_of(key[i], keybits, shard_bits)], 1u);
