@@ -623,7 +623,7 @@ __global__ void __launch_bounds__(TB) k_window_hist(const uint64_t* __restrict__
   // those are equal, so are both keys' top bits). The top 10 bits of fwd are
   // its first 5 bases, those of rc the complements of its last 5 bases, last
   // first: whole keys are not built, whatever their width (four words: 0.50 ->
-  // KC_H1 ms on 1,000,000 reads).
+  // 0.08 ms on 1,000,000 reads).
   const int kb = BATCH ? shard_bits - (keybits - 2 * k) : shard_bits;
   const bool ends = S <= 8 && k >= 5 && kb >= 0 && kb <= 10;
   for (uint64_t unit = w_begin + (uint64_t)blockIdx.x * TB * S; unit < w_end;
@@ -2662,10 +2662,17 @@ __global__ void __launch_bounds__(256) k_check(const uint64_t* __restrict__ keys
 constexpr int kHistTB = 256;
 constexpr unsigned kHistGrid = 2048;  // a multiple of kXcds times the units of a tile (1 to 8)
 constexpr int kScatterTB64 = 1024;
-constexpr int kScatterTB128 = 512;
+constexpr int kScatterTB128 = 1024;
 constexpr int kSplitTB64 = 1024;
 constexpr int kSplitTB128 = 512;
-constexpr int kScatterTB256 = 256;  // 256-bit keys: LDS staging of 64 KiB per tile
+// Wider keys: LDS staging of 64 KiB per tile, two tiles per CU; four window
+// starts per thread, so that these make 16 and 32 waves (eight starts, half as
+// many waves: 1,000,000 reads at k = 100 1.16 ms, so 1.06)
+constexpr int kScatterTB256 = 512;
+constexpr int kScatterS256 = 4, kScatterS128 = 4;
+inline int scatter_starts(int words, int starts_per_thread) {
+  return words == 4 ? kScatterS256 : words == 2 ? kScatterS128 : starts_per_thread == 16 ? 16 : kWinStarts;
+}
 constexpr int kSplitTB256 = 256;
 constexpr int kSplitR = 8;
 constexpr int kLeafTB = 512;
@@ -2772,7 +2779,7 @@ hipError_t launch_window_hist(int words, const uint64_t* packed, const uint64_t*
                               int keybits, int shard_bits, const BatchSets* batch,
                               unsigned long long* hist, int starts_per_thread, hipStream_t s) {
   // the owner scatter's tiles (see launch_window_scatter)
-  const int S = words == 1 && starts_per_thread == 16 ? 16 : kWinStarts;
+  const int S = scatter_starts(words, starts_per_thread);
   const int TBs = words == 4 ? kScatterTB256 : words == 2 ? kScatterTB128 : kScatterTB64;
   const uint64_t w_begin = byte_begin / S * S;
   const uint64_t w_end = (byte_end + S - 1) / S * S;
@@ -2819,21 +2826,24 @@ hipError_t launch_window_scatter(int words, const uint64_t* packed, const uint64
 #undef ARG0
     return hipGetLastError();
   }
-  const uint64_t t_begin = byte_begin / kWinStarts;
-  const uint64_t t_end = (byte_end + kWinStarts - 1) / kWinStarts;
+  const int S = scatter_starts(words, starts_per_thread);
+  const uint64_t t_begin = byte_begin / S;
+  const uint64_t t_end = (byte_end + S - 1) / S;
   const BatchSets bs = batch ? *batch : BatchSets{nullptr, nullptr, 0};
 #define ARG0 cursor
   if (words == 4) {
     if (batch) return hipErrorInvalidValue;
     const unsigned grid = grid_for(t_end - t_begin, kScatterTB256, 1u << 20);
 #define ARG1 (u256*)out
-    KC_WINDOW_LAUNCH(k_window_scatter, u256, u256, kScatterTB256, false, grid);
+    KC_WINDOW_LAUNCH_S(k_window_scatter, u256, u256, kScatterS256, kScatterTB256, false, grid);
 #undef ARG1
   } else if (words == 2) {
     const unsigned grid = grid_for(t_end - t_begin, kScatterTB128, 1u << 20);
 #define ARG1 (u128*)out
-    if (batch) KC_WINDOW_LAUNCH(k_window_scatter, u128, uint64_t, kScatterTB128, true, grid);
-    else KC_WINDOW_LAUNCH(k_window_scatter, u128, u128, kScatterTB128, false, grid);
+    if (batch)
+      KC_WINDOW_LAUNCH_S(k_window_scatter, u128, uint64_t, kScatterS128, kScatterTB128, true, grid);
+    else
+      KC_WINDOW_LAUNCH_S(k_window_scatter, u128, u128, kScatterS128, kScatterTB128, false, grid);
 #undef ARG1
   } else {
     const unsigned grid = grid_for(t_end - t_begin, kScatterTB64, 1u << 20);
