@@ -2441,40 +2441,49 @@ __global__ void __launch_bounds__(256) k_concat(const K* __restrict__ bufA,
     const Leaf lf = leaves[l];
     const K* src = lf.buf ? bufA : bufB;  // sorted pairs sit in the other buffer
     const unsigned long long base = out_off[l];
-    // U pairs per lane per step, all loaded before any is stored (more bytes
-    // in flight per wave)
-    constexpr uint32_t U = Key<K>::kWords == 4 ? 1 : 4;
     const uint64_t lim = base >= cap ? 0 : min((uint64_t)n, cap - base);
-    for (uint32_t i0 = 0; i0 < lim; i0 += 64 * U) {
-      K key[U];
-      uint32_t cnt[U];
+    // U words per lane and step, all loaded before any is stored (more bytes
+    // in flight per wave). Keys are copied word by word, whatever their width
+    // (their words lie in memory as the output has them): a lane that stores a
+    // four-word key's words touches 32 bytes in four stores of a quarter each
+    // (1,000,000 reads at k = 100 0.73 -> 0.66 ms, at k = 31 0.202 -> 0.183).
+    constexpr uint32_t U = 4;
+    const uint64_t* const ks = (const uint64_t*)(src + lf.begin);
+    uint64_t* const kd = out_keys + base * Key<K>::kWords;
+    const uint64_t words = lim * Key<K>::kWords;
+    const uint32_t* const cs = tmp_cnt + lf.begin;
+    uint32_t* const cd = out_counts + base;
+    for (uint64_t i0 = lane; i0 < words; i0 += 64 * U) {
+      uint64_t x[U];
+      uint32_t c[U];
+      const bool both = Key<K>::kWords == 1;
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t i = i0 + u * 64 + lane;
-        if (i < lim) {
-          key[u] = src[lf.begin + i];
-          cnt[u] = tmp_cnt[lf.begin + i];
+        const uint64_t i = i0 + u * 64;
+        if (i < words) {
+          x[u] = ks[i];
+          if (both) c[u] = cs[i];
         }
       }
 #pragma unroll
       for (uint32_t u = 0; u < U; ++u) {
-        const uint32_t i = i0 + u * 64 + lane;
-        if (i >= lim) break;
-        const uint64_t o = base + i;
-        if constexpr (Key<K>::kWords == 4) {
-          out_keys[4 * o] = (uint64_t)key[u].lo;
-          out_keys[4 * o + 1] = (uint64_t)(key[u].lo >> 64);
-          out_keys[4 * o + 2] = (uint64_t)key[u].hi;
-          out_keys[4 * o + 3] = (uint64_t)(key[u].hi >> 64);
-        } else if constexpr (Key<K>::kWords == 2) {
-          out_keys[2 * o] = (uint64_t)key[u];
-          out_keys[2 * o + 1] = (uint64_t)((u128)key[u] >> 64);
-        } else {
-          out_keys[o] = (uint64_t)key[u];
+        const uint64_t i = i0 + u * 64;
+        if (i < words) {
+          kd[i] = x[u];
+          if (both) cd[i] = c[u];
         }
-        out_counts[o] = cnt[u];
       }
     }
+    if constexpr (Key<K>::kWords > 1)
+      for (uint64_t i0 = lane; i0 < lim; i0 += 64 * U) {
+        uint32_t c[U];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+          if (i0 + u * 64 < lim) c[u] = cs[i0 + u * 64];
+#pragma unroll
+        for (uint32_t u = 0; u < U; ++u)
+          if (i0 + u * 64 < lim) cd[i0 + u * 64] = c[u];
+      }
   }
 }
 
