@@ -108,6 +108,12 @@ hipError_t launch_valid_mask(int words, const uint64_t* inv, const uint64_t* end
                              uint64_t byte_begin, uint64_t byte_end, int k, uint64_t* valid,
                              const ZeroRanges& z, hipStream_t s);
 
+// launch_pack and launch_valid_mask of the n_bytes bytes of a plain call in one
+// pass, without the two masks in memory (valid holds nchunks words).
+hipError_t launch_front(int words, const uint8_t* src, uint64_t n_bytes, const uint64_t* offsets,
+                        uint64_t n_reads, uint64_t off0, int k, uint64_t* packed, uint64_t* valid,
+                        uint64_t nchunks, const ZeroRanges& z, hipStream_t s);
+
 // Window kernels over the bytes [byte_begin, byte_end) of the packed stream,
 // with the valid-start mask of launch_valid_mask for the same range and k.
 // keybits = 2k (plain) or 2k + set id bits (batch: batch != nullptr).

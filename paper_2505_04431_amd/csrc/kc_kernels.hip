@@ -305,65 +305,77 @@ __global__ void k_fill_u64(unsigned long long* p, uint64_t n, unsigned long long
 
 // ---------------------------------------------------------------- pack
 
-__device__ __forceinline__ uint32_t base_code(uint32_t b) { return ((b >> 1) ^ (b >> 2)) & 3u; }
 // Top bit of each byte of v set iff that byte is not zero (no carry between bytes).
 __device__ __forceinline__ uint32_t nonzero_bytes(uint32_t v) {
   return (((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) & 0x80808080u;
 }
-__device__ __forceinline__ bool base_valid(uint32_t b) {
-  uint32_t u = b | 0x20u;
-  return u == 'a' || u == 'c' || u == 'g' || u == 't';
+// Four bytes w at once (SWAR), bases j .. j+3 of a chunk: the 2-bit code of each
+// byte from its bits 1 and 2, then the four 2-bit codes gathered into 8 bits of p; a byte is invalid iff its
+// lowercase form differs from each of a, c, g, t (nonzero_bytes sets a byte's top
+// bit iff the byte is not 0), the four top bits gathered into 4 bits of iv by one
+// multiply.
+__device__ __forceinline__ void pack4(uint32_t w, int j, uint64_t (&p)[2], uint64_t& iv) {
+  const uint32_t c = ((w >> 1) ^ (w >> 2)) & 0x03030303u;
+  const uint32_t t = c | (c >> 6);
+  p[j >> 5] |= (uint64_t)((t & 0xFu) | ((t >> 12) & 0xF0u)) << (2 * (j & 31));
+  const uint32_t l = w | 0x20202020u;
+  const uint32_t bad = nonzero_bytes(l ^ 0x61616161u) & nonzero_bytes(l ^ 0x63636363u) &
+                       nonzero_bytes(l ^ 0x67676767u) & nonzero_bytes(l ^ 0x74747474u);
+  iv |= (uint64_t)(((bad & 0x80808080u) * 0x00204081u) >> 28) << j;
+}
+
+// Bases [64c, 64c + 64) of the n bytes at src, at any alignment: two packed
+// words and the invalid mask. Bytes from n on are invalid, their codes 0. Off a
+// 16-byte boundary the aligned words that hold a byte of src are loaded, all
+// before any is used (byte loads, each waited for, took 7.4 us of a small input).
+__device__ __forceinline__ void pack_chunk(const uint8_t* __restrict__ src, uint64_t n, uint64_t c,
+                                           uint64_t (&p)[2], uint64_t& iv) {
+  const uint64_t g0 = c * 64;
+  p[0] = p[1] = 0;
+  iv = 0;
+  if (g0 >= n) {
+    iv = ~0ull;
+    return;
+  }
+  const uint8_t* const q = src + g0;
+  if (((uintptr_t)q & 15) == 0 && g0 + 64 <= n) {
+    const uint4* const v = (const uint4*)q;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint4 x = v[i];
+      pack4(x.x, i * 16, p, iv);
+      pack4(x.y, i * 16 + 4, p, iv);
+      pack4(x.z, i * 16 + 8, p, iv);
+      pack4(x.w, i * 16 + 12, p, iv);
+    }
+    return;
+  }
+  const uint32_t sh = (uint32_t)((uintptr_t)q & 3);
+  const uint32_t* const a = (const uint32_t*)(q - sh);
+  const uint32_t left = (uint32_t)min((uint64_t)64, n - g0), end = left + sh;  // bytes from a
+  uint32_t w[17];
+#pragma unroll
+  for (int i = 0; i < 17; ++i) w[i] = 4u * i < end ? a[i] : 0u;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    pack4((uint32_t)((((uint64_t)w[i + 1] << 32) | w[i]) >> (8 * sh)), 4 * i, p, iv);
+  if (left < 64) {
+    iv |= ~0ull << left;
+    p[1] &= left > 32 ? (1ull << (2 * (left - 32))) - 1 : 0ull;
+    p[0] &= left >= 32 ? ~0ull : (1ull << (2 * left)) - 1;
+  }
 }
 
 // Thread c packs bytes [64c, 64c+64): two packed words, one invalid-mask word
 // and one end-mask word (bit j set iff byte 64c+j is the last byte of a read).
 __global__ void __launch_bounds__(256) k_pack(const uint8_t* __restrict__ src, uint64_t n_bytes,
-                                              const uint64_t* __restrict__ offsets,
-                                              uint64_t n_reads, uint64_t off0,
                                               uint64_t* __restrict__ packed,
                                               uint64_t* __restrict__ inv,
-                                              uint64_t* __restrict__ endm, uint64_t nchunks,
-                                              int aligned) {
+                                              uint64_t* __restrict__ endm, uint64_t nchunks) {
   const uint64_t c = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= nchunks) return;
-  const uint64_t g0 = c * 64;
-  uint64_t p[2] = {0, 0};
-  uint64_t iv = 0;
-  if (aligned && g0 + 64 <= n_bytes) {
-    const uint4* q = reinterpret_cast<const uint4*>(src + g0);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      uint4 x = q[v];
-      uint32_t w[4] = {x.x, x.y, x.z, x.w};
-#pragma unroll
-      for (int d = 0; d < 4; ++d) {
-        // four bytes at once (SWAR): base_code of each byte, then the four
-        // 2-bit codes gathered into 8 bits; a byte is invalid iff its
-        // lowercase form differs from each of a, c, g, t (nonzero_bytes sets
-        // a byte's top bit iff the byte is not 0), the four top bits gathered
-        // into 4 bits by one multiply
-        const int j = v * 16 + d * 4;
-        const uint32_t c = ((w[d] >> 1) ^ (w[d] >> 2)) & 0x03030303u;
-        const uint32_t t = c | (c >> 6);
-        p[j >> 5] |= (uint64_t)((t & 0xFu) | ((t >> 12) & 0xF0u)) << (2 * (j & 31));
-        const uint32_t l = w[d] | 0x20202020u;
-        const uint32_t bad = nonzero_bytes(l ^ 0x61616161u) & nonzero_bytes(l ^ 0x63636363u) &
-                             nonzero_bytes(l ^ 0x67676767u) & nonzero_bytes(l ^ 0x74747474u);
-        iv |= (uint64_t)(((bad & 0x80808080u) * 0x00204081u) >> 28) << j;
-      }
-    }
-  } else {
-    for (int j = 0; j < 64; ++j) {
-      const uint64_t g = g0 + j;
-      if (g < n_bytes) {
-        const uint32_t b = src[g];
-        p[j >> 5] |= (uint64_t)base_code(b) << (2 * (j & 31));
-        if (!base_valid(b)) iv |= 1ull << j;
-      } else {
-        iv |= 1ull << j;
-      }
-    }
-  }
+  uint64_t p[2], iv;
+  pack_chunk(src, n_bytes, c, p, iv);
   packed[2 * c] = p[0];
   packed[2 * c + 1] = p[1];
   inv[c] = iv;
@@ -448,6 +460,122 @@ __global__ void __launch_bounds__(256) k_valid_mask(const uint64_t* __restrict__
     bad = (uint64_t)b;
   }
   valid[w] = ~bad;
+}
+
+// Chunks after a window's first that it may reach into: it starts at bit 63 at
+// the latest and is up to 128 (WIDE) or 64 bases long.
+template <bool WIDE> constexpr int kFrontHalo = WIDE ? 2 : 1;
+
+// First r in [lo, hi) with off[r + 1] > x, or hi; by a whole wave, 64 places a
+// step. guess: about where it lies.
+__device__ __forceinline__ uint64_t wave_first_end(const uint64_t* __restrict__ off, uint64_t lo,
+                                                   uint64_t hi, uint64_t x, uint64_t guess) {
+  const uint64_t lane = threadIdx.x & 63;
+  if (hi - lo > 64) {  // 64 places about the guess: reads of like lengths are found between two
+    uint64_t i = guess + 64 * lane;
+    i = i < lo + 2048 ? lo : i - 2048;
+    i = min(i, hi - 1);
+    const int below = __popcll(__ballot(off[i + 1] <= x));
+    const uint64_t last = __shfl(i, below ? below - 1 : 0), first = __shfl(i, below & 63);
+    if (below) lo = last + 1;
+    if (below < 64) hi = first;
+  }
+  while (lo < hi) {
+    const uint64_t step = (hi - lo + 63) / 64;
+    const uint64_t i = lo + lane * step;
+    const uint64_t below = (uint64_t)__popcll(__ballot(i < hi && off[i + 1] <= x));
+    hi = min(hi, lo + below * step);
+    if (below) lo += (below - 1) * step + 1;
+  }
+  return lo;
+}
+
+// Input of a plain call in one pass: packed bases and the valid-start mask for
+// k, and the counters of the pipeline cleared. A workgroup takes 256 chunks of
+// 64 bytes, a thread each, and keeps the invalid and read-end masks in LDS; the
+// last HALO chunks (those a window of k reaches into) are the next workgroup's
+// first. The read ends among its bytes are a range of the offsets, found by
+// one wave and set by all threads. Bound by reading the input (large) and by
+// the number of launches (small): apart, the three kernels wrote and read the
+// two masks (3/8 of a byte a base) and set the ends by an atomic each in
+// memory: 20,000,000 reads 1.33 -> 0.85 ms (3.5 TB/s of bases), 1,000,000 reads
+// 83 -> 60 us, 667 reads 11.8 -> 6.3 us and two launches less (whole call 101 ->
+// 94 us).
+template <bool WIDE>
+__global__ void __launch_bounds__(256) k_front(const uint8_t* __restrict__ src, uint64_t n_bytes,
+                                               const uint64_t* __restrict__ offsets,
+                                               uint64_t n_reads, uint64_t off0, int k,
+                                               uint64_t* __restrict__ packed,
+                                               uint64_t* __restrict__ valid, uint64_t nchunks,
+                                               ZeroRanges z) {
+  constexpr int HALO = kFrontHalo<WIDE>;
+  __shared__ uint64_t s_inv[256];
+  __shared__ __align__(8) uint32_t s_end[512];  // two words a chunk
+  __shared__ uint64_t s_r;
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int r = 0; r < ZeroRanges::kN; ++r)
+    for (uint64_t i = (uint64_t)blockIdx.x * 256 + t; i < z.n[r]; i += (uint64_t)gridDim.x * 256)
+      z.p[r][i] = 0;
+  const uint64_t c0 = (uint64_t)blockIdx.x * (256 - HALO), c = c0 + t;
+  if (c0 >= nchunks) return;  // a workgroup that only clears
+  s_end[t] = s_end[t + 256] = 0;
+  uint64_t p[2], iv;
+  pack_chunk(src, n_bytes, c, p, iv);
+  s_inv[t] = iv;
+  // ends e with x0 < e <= x1 are those of bases of these chunks
+  const uint64_t x0 = off0 + min(n_bytes, c0 * 64), x1 = off0 + min(n_bytes, (c0 + 256) * 64);
+  auto first_end = [&](uint64_t lo, uint64_t x) {
+    if (t < 64) {
+      const uint64_t r = wave_first_end(
+          offsets, lo, n_reads, x, (uint64_t)((double)(x - off0) / (double)n_bytes * (double)n_reads));
+      if (t == 0) s_r = r;
+    }
+    __syncthreads();
+    return s_r;
+  };
+  constexpr int U = 4;
+  for (uint64_t r = first_end(0, x0); r < n_reads;) {
+    uint64_t e[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint64_t i = r + u * 256 + t;
+      e[u] = i < n_reads ? offsets[i + 1] : ~0ull;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (e[u] <= x1) {  // (an empty read's end is that of an earlier one too, or <= x0)
+        const uint32_t b = (uint32_t)(e[u] - 1 - off0 - c0 * 64);
+        atomicOr(&s_end[b >> 5], 1u << (b & 31));
+      }
+    // done if the last one looked at is past these chunks; many empty reads
+    // with one end are passed over
+    const uint64_t last = r + U * 256;
+    if (last > n_reads) break;
+    const uint64_t el = offsets[last];
+    if (el > x1) break;
+    const bool same = offsets[r + 1] == el;
+    r = last;
+    if (same) {
+      __syncthreads();  // s_r was read by all
+      r = first_end(r, el);
+    }
+  }
+  __syncthreads();
+  if (t >= 256 - HALO || c >= nchunks) return;
+  *(ulonglong2*)(packed + 2 * c) = ulonglong2{p[0], p[1]};
+  const uint64_t* const s_e = (const uint64_t*)s_end;
+  uint64_t bad;
+  if constexpr (WIDE) {
+    u256 b = smear256(u256(((u128)s_inv[t + 1] << 64) | s_inv[t], (u128)s_inv[t + 2]), k);
+    if (k > 1) b |= smear256(u256(((u128)s_e[t + 1] << 64) | s_e[t], (u128)s_e[t + 2]), k - 1);
+    bad = (uint64_t)b;
+  } else {
+    u128 b = smear(((u128)s_inv[t + 1] << 64) | s_inv[t], k);
+    if (k > 1) b |= smear(((u128)s_e[t + 1] << 64) | s_e[t], k - 1);
+    bad = (uint64_t)b;
+  }
+  valid[c] = ~bad;
 }
 
 // Valid starts among the S window starts g .. g+S-1 (g a multiple of S, S
@@ -2740,13 +2868,28 @@ hipError_t launch_fill_u64(unsigned long long* p, uint64_t n, unsigned long long
 hipError_t launch_pack(const uint8_t* src, uint64_t n_bytes, const uint64_t* offsets,
                        uint64_t n_reads, uint64_t off0, uint64_t* packed, uint64_t* inv,
                        uint64_t* endm, uint64_t nchunks, hipStream_t s) {
-  const int aligned = ((uintptr_t)src & 15) == 0;
   const unsigned grid = (unsigned)((nchunks + 255) / 256);
-  hipLaunchKernelGGL(k_pack, dim3(grid), dim3(256), 0, s, src, n_bytes, offsets, n_reads, off0,
-                     packed, inv, endm, nchunks, aligned);
+  hipLaunchKernelGGL(k_pack, dim3(grid), dim3(256), 0, s, src, n_bytes, packed, inv, endm, nchunks);
   if (n_reads)
     hipLaunchKernelGGL(k_read_ends, dim3((unsigned)((n_reads + 255) / 256)), dim3(256), 0, s,
                        offsets, n_reads, off0, (unsigned long long*)endm);
+  return hipGetLastError();
+}
+
+hipError_t launch_front(int words, const uint8_t* src, uint64_t n_bytes, const uint64_t* offsets,
+                        uint64_t n_reads, uint64_t off0, int k, uint64_t* packed, uint64_t* valid,
+                        uint64_t nchunks, const ZeroRanges& z, hipStream_t s) {
+  uint64_t zeros = 0;
+  for (uint64_t n : z.n) zeros += n;
+  const uint64_t per = 256 - (words == 4 ? kFrontHalo<true> : kFrontHalo<false>);
+  const unsigned grid = (unsigned)std::max<uint64_t>(
+      (nchunks + per - 1) / per, std::min<uint64_t>((zeros + 1023) / 1024, 1024));
+  if (words == 4)
+    hipLaunchKernelGGL(k_front<true>, dim3(grid), dim3(256), 0, s, src, n_bytes, offsets, n_reads,
+                       off0, k, packed, valid, nchunks, z);
+  else
+    hipLaunchKernelGGL(k_front<false>, dim3(grid), dim3(256), 0, s, src, n_bytes, offsets,
+                       n_reads, off0, k, packed, valid, nchunks, z);
   return hipGetLastError();
 }
 

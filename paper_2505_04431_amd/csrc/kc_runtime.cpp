@@ -814,8 +814,6 @@ template <class F>
 void plain_needs(const Pipe& p, F&& f) {
   const uint64_t nchunks = packed_chunks(p.byte_end);
   f(&Ctx::packed, nchunks * 16, "packed bases");
-  f(&Ctx::inv, nchunks * 8, "invalid mask");
-  f(&Ctx::endm, nchunks * 8, "end mask");
   f(&Ctx::valid, nchunks * 8, "valid-start mask");
   f(&Ctx::state, sizeof(kc::DevState), "device state");
   f(&Ctx::order, (size_t)(1ull << p.sb) * 4, "owner order");
@@ -830,21 +828,29 @@ struct PipeOut {
   uint32_t* set;  // batch form only
   uint64_t cap;
   bool concat = true;  // false: stop after the output offsets
-  bool zero_state = false;      // the pipeline clears its state first
+  bool front = false;           // packed, masked and the counters cleared by launch_front
   kc::DevState* pub = nullptr;  // device-visible host memory that receives the state
 };
 
+// Item classes of the split scatter (one when a leaf's end is its cursor's last value).
+int split_classes(const Pipe& p) { return p.merge_cshift ? 1 : kc::kXcds; }
+
+// The counters that a pipeline run starts with, to be cleared before it.
+kc::ZeroRanges pipeline_zeros(const Ctx& c, const Pipe& p, kc::DevState* dstate) {
+  return {{(unsigned long long*)c.hist.p, (unsigned long long*)c.subhist.p,
+           (unsigned long long*)dstate},
+          {(1ull + kc::kXcds) << p.sb, p.max_leaves * split_classes(p),
+           dstate ? sizeof(kc::DevState) / 8 : 0}};
+}
+
 void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, const PipeOut& out,
                       hipStream_t st) {
-  // item classes of the split scatter (one when a leaf's end is its cursor's last value)
-  const int ncls = p.merge_cshift ? 1 : kc::kXcds;
-  const kc::ZeroRanges z = {
-      {(unsigned long long*)c.hist.p, (unsigned long long*)c.subhist.p, (unsigned long long*)dstate},
-      {(1ull + kc::kXcds) << p.sb, p.max_leaves * ncls,
-       out.zero_state ? sizeof(kc::DevState) / 8 : 0}};
-  hipchk(kc::launch_valid_mask(p.words, (uint64_t*)c.inv.p, (uint64_t*)c.endm.p, p.byte_begin,
-                               p.byte_end, p.k, (uint64_t*)c.valid.p, z, st),
-         "valid mask launch");
+  const int ncls = split_classes(p);
+  if (!out.front)  // (a plain call's launch_front has done this)
+    hipchk(kc::launch_valid_mask(p.words, (uint64_t*)c.inv.p, (uint64_t*)c.endm.p, p.byte_begin,
+                                 p.byte_end, p.k, (uint64_t*)c.valid.p,
+                                 pipeline_zeros(c, p, nullptr), st),
+           "valid mask launch");
   hipchk(kc::launch_window_hist(p.words, (uint64_t*)c.packed.p, (uint64_t*)c.valid.p,
                                 p.byte_begin, p.byte_end, p.k, p.keybits,
                                 p.sb, p.batch, (unsigned long long*)c.hist.p, p.scatter_s, st),
@@ -1084,12 +1090,13 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
   kc::DevState* dstate = (kc::DevState*)c.state.p;
 
   tm.mark(ST_NONE);
-  hipchk(kc::launch_pack(reads + off0, q.N, offsets, n_reads, off0, (uint64_t*)c.packed.p,
-                         (uint64_t*)c.inv.p, (uint64_t*)c.endm.p, nchunks, st),
+  hipchk(kc::launch_front(p.words, reads + off0, q.N, offsets, n_reads, off0, k,
+                          (uint64_t*)c.packed.p, (uint64_t*)c.valid.p, nchunks,
+                          pipeline_zeros(c, p, dstate), st),
          "pack launch");
   tm.mark(ST_PACK);
   PipeOut po{out_keys, out_counts, nullptr, cap, !oa};
-  po.zero_state = true;
+  po.front = true;
   po.pub = h_dev ? (kc::DevState*)((char*)h_dev + kInfoBytes) : nullptr;
   enqueue_pipeline(c, p, dstate, tm, po, st);
   q.concat_leaves = p.max_leaves;
