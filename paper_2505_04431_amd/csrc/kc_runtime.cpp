@@ -972,10 +972,13 @@ Pipe plain_pipe(uint64_t n_bytes, int k, int P, const kc_options& o) {
   uint64_t C = 0;
   table_params(o, p.words, p.slots_log2, C, p.T, p.H);
   p.sb = shard_bits_for(o, P, n_bytes, p.T, p.keybits);
-  // two-word keys: one more shard bit shortens the split's runs more than it
-  // lengthens the owner scatter's (measured: 4.67 against 4.77 ms at k = 55,
-  // 1,000,000 reads of 150 bp)
-  if (p.words == 2 && o.shard_bits <= 0) p.sb = std::min(std::max(p.sb, 9), kc::max_shard_bits());
+  // two-word keys of larger inputs: one more shard bit shortens the split's runs
+  // more than it lengthens the owner scatter's (k = 55, 150 MB of 150 bp reads
+  // 4.12 against 4.17 ms, 60 MB of 10 kbp reads 2.19 against 2.21; below, the
+  // plans of twice the shards cost more: 4 MB 225 against 211 us, 0.1 MB 108
+  // against 97)
+  if (p.words == 2 && o.shard_bits <= 0 && n_bytes >= (48u << 20))
+    p.sb = std::min(std::max(p.sb, 9), kc::max_shard_bits());
   p.byte_begin = 0;
   p.byte_end = n_bytes;
   p.rec_bound = n_bytes;  // byte count: an upper bound of the window count
