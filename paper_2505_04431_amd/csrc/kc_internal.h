@@ -68,6 +68,9 @@ struct ZeroRanges {
 struct LeafLists {
   uint64_t small_max, huge_min;
   uint32_t *large, *huge, *d_zero;
+  bool on;        // classify them
+  bool one_wave;  // leaves of up to small_max records go to the one-wave kernel
+  bool direct;    // no list of large leaves: the block-wide kernel takes them all
 };
 
 // Read sets of a batch, for the window kernels: set_byte_off[s] is the first
@@ -199,7 +202,8 @@ hipError_t launch_leaf_ends(Leaf* leaves, const unsigned long long* cursor, cons
 // merged: leaves may hold pre-aggregated records (one-word keys).
 // ovf_list (max_leaves entries, or nullptr): in mode 0 the leaves whose table
 // overflows are listed there, for launch_leaf_second.
-// With few leaves (max_leaves) none is small: all go to the block-wide kernel.
+// With few leaves (max_leaves) none is small: all go to the block-wide kernel,
+// which then takes them from the leaf table, not from large_list.
 // launch_leaf_small also classifies the leaves unless launch_plan_leaves has
 // (classified): large ones into large_list;
 // in mode 0 with ovf_list (and the second count running,
@@ -221,8 +225,9 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
 // st->overflow from the leaf counts). A no-op where launch_leaf_large lists
 // nothing.
 hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
-                              const Leaf* leaves, DevState* st, uint32_t* d_out, int slots_log2,
-                              const uint32_t* ovf_list, hipStream_t s, int mode, bool merged);
+                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
+                              uint32_t* d_out, int slots_log2, const uint32_t* ovf_list,
+                              hipStream_t s, int mode, bool refine, bool merged);
 uint64_t small_leaf_max(int words);
 
 // Exclusive scan of leaf counts into output offsets; st->D = total. bsum
@@ -252,10 +257,13 @@ hipError_t launch_splice(const Leaf* leaves, const uint32_t* d, uint64_t n,
 // st->overflow is set: the host refines the overflowed leaves first and
 // launches it again (the concat of a batch class likewise: the class is
 // recounted set by set).
+// With concat_plans_out(max_leaves) and out_off nullptr, launch_plan_out's part
+// (st->D, st->overflow, the state to pub) is done in this launch too.
+bool concat_plans_out(uint64_t max_leaves);
 hipError_t launch_concat(int words, const void* bufA, const void* bufB, const uint32_t* tmp_cnt,
                          const Leaf* leaves, const uint32_t* d, const unsigned long long* out_off,
-                         const DevState* st, uint64_t max_leaves, uint64_t cap,
-                         uint64_t* out_keys, uint32_t* out_counts, hipStream_t s);
+                         DevState* st, uint64_t max_leaves, uint64_t cap, uint64_t* out_keys,
+                         uint32_t* out_counts, hipStream_t s, DevState* pub = nullptr);
 
 // Batch helpers: class concat (k-mer, count, set id within the class), set
 // bounds in a class output, global set offsets and the final gather.

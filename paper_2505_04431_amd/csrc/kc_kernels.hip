@@ -1019,6 +1019,8 @@ __global__ void k_plan_items(const unsigned long long* __restrict__ hist,
 // records, the others 4,600), and the first count would read part of them
 // before giving up. d_zero != nullptr (no one-wave kernel follows): the counts
 // of empty leaves are set to 0 there.
+// (direct: the block-wide kernel takes all others straight from the leaf table,
+// see leaf_lists.)
 // Called by all threads of a workgroup of up to 1,024; sh holds 2 * 17 words.
 // One atomic per list and workgroup: one per wave, on one word, took 130 us for
 // the 2^20 leaves of 20,000,000 reads at 12 ns each (the whole kernel now 21 us).
@@ -1027,7 +1029,7 @@ __device__ __forceinline__ void classify_leaves(bool has, uint32_t i, uint64_t l
                                                 uint32_t* sh, unsigned long long* base) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
   const bool to_huge = has && q.huge && len > q.huge_min;
-  const bool big = has && !to_huge && len > q.small_max;
+  const bool big = has && !to_huge && !q.direct && len > q.small_max;
   if (q.d_zero && has && len == 0) q.d_zero[i] = 0;
   const unsigned long long m = __ballot(big), mh = __ballot(to_huge);
   if (lane == 0) {
@@ -1067,7 +1069,7 @@ __global__ void k_classify_leaves(const Leaf* __restrict__ leaves, DevState* __r
 }
 
 // Leaf table (key order) and sub-bin cursors: block c handles shard c. With
-// q.large the leaves are classified here as well (not where pre-aggregation
+// q.on the leaves are classified here as well (not where pre-aggregation
 // still shortens them).
 __global__ void __launch_bounds__(kPlanTB) k_plan_leaves(
     const unsigned long long* __restrict__ hist, const unsigned long long* __restrict__ sbegin,
@@ -1083,7 +1085,7 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_leaves(
   const SplitBin b = bins[c];
   if (b.nbits == 0) {
     if (threadIdx.x == 0) leaves[b.hist_off] = Leaf{sbegin[c], sbegin[c] + h, 0u, (uint32_t)shard_bits};
-    if (q.large) classify_leaves(threadIdx.x == 0, (uint32_t)b.hist_off, h, st, q, sh, base);
+    if (q.on) classify_leaves(threadIdx.x == 0, (uint32_t)b.hist_off, h, st, q, sh, base);
     return;
   }
   const uint32_t nsub = 1u << b.nbits;  // <= kPlanTB
@@ -1104,7 +1106,7 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_leaves(
       at += subhist[x * cls_stride + b.hist_off + j];
     }
   }
-  if (q.large) classify_leaves(j < nsub, (uint32_t)(b.hist_off + j), n, st, q, sh, base);
+  if (q.on) classify_leaves(j < nsub, (uint32_t)(b.hist_off + j), n, st, q, sh, base);
 }
 
 // ---------------------------------------------------------------- refinement support
@@ -1759,7 +1761,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     // against 0.68 ms, sized by the share of distinct records 1.01 ms). With few
     // leaves the chip is not full and a leaf's chain of latencies counts, not
     // its work: room to spare then.
-    const bool few = list && count <= kFewLeaves;
+    const bool few = TB != 64 && count <= kFewLeaves;
     const uint32_t Cn = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
     // pre-aggregated records: (count - 1) in bits [cshift, 64), the shard above
     const uint32_t cshift = MERGED ? lf.cshift : 0u;
@@ -1887,7 +1889,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
   }
   // one update of the shared totals per workgroup (not per leaf: same-address
   // atomics from every workgroup would serialise)
-  if (list && threadIdx.x == 0 && my_records) {
+  if (TB != 64 && threadIdx.x == 0 && my_records) {
     atomicAdd(&acc[0], my_records);
     atomicAdd(&acc[1], my_distinct);
   }
@@ -1953,7 +1955,7 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
     if (!list && n > small_max) continue;
     const u128* src = lf.buf ? bufB : bufA;
     u128* dst = lf.buf ? bufA : bufB;
-    const bool few = list && count <= kFewLeaves;
+    const bool few = TB != 64 && count <= kFewLeaves;
     const uint32_t Cn = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
     const uint32_t cmask = Cn - 1;
     const int slot_bits = 31 - __builtin_clz(Cn);
@@ -2058,7 +2060,7 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
     }
     __syncthreads();
   }
-  if (list && threadIdx.x == 0 && my_records) {
+  if (TB != 64 && threadIdx.x == 0 && my_records) {
     atomicAdd(&acc[0], my_records);
     atomicAdd(&acc[1], my_distinct);
   }
@@ -2135,7 +2137,7 @@ __device__ __forceinline__ void leaf_countw_body(
     if (!list && n > small_max) continue;
     const K* __restrict__ src = (lf.buf ? bufB : bufA) + lf.begin;
     K* const dst = lf.buf ? bufA : bufB;
-    const bool few = list && count <= kFewLeaves;
+    const bool few = TB != 64 && count <= kFewLeaves;
     const uint32_t Cn = leaf_slots<TB, CMAX>(few ? n + n / 2 : n, cmax_rt);
     const uint32_t cmask = Cn - 1;
     const int slot_bits = 31 - __builtin_clz(Cn);
@@ -2248,7 +2250,7 @@ __device__ __forceinline__ void leaf_countw_body(
     }
     __syncthreads();
   }
-  if (list && threadIdx.x == 0 && my_records) {
+  if (TB != 64 && threadIdx.x == 0 && my_records) {
     atomicAdd(&acc[0], my_records);
     atomicAdd(&acc[1], my_distinct);
   }
@@ -2545,21 +2547,87 @@ __global__ void __launch_bounds__(TB) k_leaf_radix64(int keybits, uint64_t* bufA
 
 // ---------------------------------------------------------------- concat + check
 
-template <typename K>
+// Output offsets within the concat: the leaf counts of up to kFewLeaves leaves
+// are summed by every workgroup for itself (4 loads a thread in flight, from
+// L2) instead of by a launch before it, which took 7 us and the gap of a launch
+// (5 us) for as many leaves: this launch 4.5 instead of 6.0 us for 667 reads,
+// 7.7 instead of 13.2 for 40,001 trimmed ones. Returns the output place of leaf l0, the workgroup's
+// first; ovf: a leaf overflowed. The first workgroup leaves the totals in st
+// and copies the state to pub.
+__device__ __forceinline__ unsigned long long leaf_prefix(const uint32_t* __restrict__ d,
+                                                          uint32_t n, uint32_t l0, DevState* st,
+                                                          DevState* pub, bool& ovf) {
+  __shared__ unsigned long long s_below[4], s_all[4];
+  __shared__ uint32_t s_ovf;
+  if (threadIdx.x == 0) s_ovf = 0;
+  __syncthreads();
+  unsigned long long below = 0, all = 0;
+  bool o = false;
+  constexpr uint32_t U = 4;
+  for (uint32_t i0 = threadIdx.x; i0 < n; i0 += 256 * U) {
+    uint32_t v[U];
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) v[u] = i0 + u * 256 < n ? d[i0 + u * 256] : 0u;
+#pragma unroll
+    for (uint32_t u = 0; u < U; ++u) {
+      o |= v[u] == kLeafOverflow;
+      if (v[u] == kLeafOverflow) v[u] = 0;
+      all += v[u];
+      if (i0 + u * 256 < l0) below += v[u];
+    }
+  }
+  for (int m = 32; m > 0; m >>= 1) {
+    below += __shfl_xor(below, m);
+    all += __shfl_xor(all, m);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    s_below[threadIdx.x >> 6] = below;
+    s_all[threadIdx.x >> 6] = all;
+  }
+  if (o) atomicOr(&s_ovf, 1u);
+  __syncthreads();
+  ovf = s_ovf != 0;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) {
+      if (ovf) atomicOr(&st->overflow, 1u);
+      __hip_atomic_store(&st->D, s_all[0] + s_all[1] + s_all[2] + s_all[3], __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
+      __threadfence();
+    }
+    __syncthreads();
+    publish_state(st, pub);
+  }
+  return s_below[0] + s_below[1] + s_below[2] + s_below[3];
+}
+
+// OFFS: the output offsets are in out_off; else each workgroup takes four leaves
+// and finds them itself (leaf_prefix).
+template <typename K, bool OFFS>
 __global__ void __launch_bounds__(256) k_concat(const K* __restrict__ bufA,
                                                 const K* __restrict__ bufB,
                                                 const uint32_t* __restrict__ tmp_cnt,
                                                 const Leaf* __restrict__ leaves,
                                                 const uint32_t* __restrict__ d,
                                                 const unsigned long long* __restrict__ out_off,
-                                                const DevState* __restrict__ st, uint64_t cap,
+                                                DevState* st, uint64_t cap,
                                                 uint64_t* __restrict__ out_keys,
-                                                uint32_t* __restrict__ out_counts) {
+                                                uint32_t* __restrict__ out_counts,
+                                                DevState* pub) {
   // a leaf overflowed: the host refines it and concatenates afterwards, so
   // this launch (enqueued before the host could know) has nothing to do
-  if (st->overflow) return;
-  // one wave per leaf, many leaves in flight per CU
   const unsigned long long n_leaves = st->n_leaves;
+  unsigned long long first = 0;
+  if constexpr (OFFS) {
+    if (st->overflow) return;
+  } else {
+    if (blockIdx.x && blockIdx.x * 4ull >= n_leaves) return;
+    bool ovf;
+    first = leaf_prefix(d, (uint32_t)n_leaves, blockIdx.x * 4, st, pub, ovf);
+    if (ovf) return;
+    for (uint32_t l = blockIdx.x * 4; l < blockIdx.x * 4 + (threadIdx.x >> 6) && l < n_leaves; ++l)
+      first += d[l];
+  }
+  // one wave per leaf, many leaves in flight per CU
   const unsigned lane = threadIdx.x & 63;
   const unsigned long long nw = (unsigned long long)gridDim.x * 4;
   for (unsigned long long l = (unsigned long long)blockIdx.x * 4 + (threadIdx.x >> 6); l < n_leaves;
@@ -2568,7 +2636,7 @@ __global__ void __launch_bounds__(256) k_concat(const K* __restrict__ bufA,
     if (n == 0 || n == kLeafOverflow) continue;
     const Leaf lf = leaves[l];
     const K* src = lf.buf ? bufA : bufB;  // sorted pairs sit in the other buffer
-    const unsigned long long base = out_off[l];
+    const unsigned long long base = OFFS ? out_off[l] : first;
     const uint64_t lim = base >= cap ? 0 : min((uint64_t)n, cap - base);
     // U words per lane and step, all loaded before any is stored (more bytes
     // in flight per wave). Keys are copied word by word, whatever their width
@@ -3026,15 +3094,31 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
   return hipGetLastError();
 }
 
+// Inputs of one-word keys with up to kTinyLeaves leaves: the second count's table
+// for all of them from the start. There is a CU for each, or nearly, so a
+// workgroup that fills one takes no longer (13.0 against 12.7 us for 667 reads),
+// and the second launch, mostly with nothing to do, goes (4 to 5 us).
+constexpr uint64_t kTinyLeaves = 3 * kRescueGrid;
+static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode, bool refine,
+                        bool merged) {
+  return words == 1 && mode != 1 && !refine && !merged && max_leaves <= kTinyLeaves &&
+         (1 << slots_log2) == kLeafCmax64;
+}
+
 // Which leaves go where (see classify_leaves).
 static LeafLists leaf_lists(int words, uint64_t max_leaves, uint32_t* d_out, uint32_t* large_list,
-                            uint32_t* ovf_list, int slots_log2, int mode) {
+                            uint32_t* ovf_list, int slots_log2, int mode, bool tiny) {
   const bool one_wave = mode != 1 && words != 4 && max_leaves > kFewLeaves;
+  // few leaves: the block-wide kernel goes through the leaf table itself, empty
+  // leaves too, with no list between (one word that 256 planning workgroups
+  // count up, and a load more per leaf)
+  const bool direct = mode != 1 && max_leaves <= kFewLeaves;
   // leaves of more than 8 first tables of records go straight to the second
   // count (where it runs: launch_leaf_second)
-  const bool second = mode != 1 && slots_log2 < second_slots_log2(words) && ovf_list;
+  const bool second = mode != 1 && !tiny && slots_log2 < second_slots_log2(words) && ovf_list;
   return LeafLists{one_wave ? small_leaf_max(words) : 0, 8ull << slots_log2, large_list,
-                   second ? ovf_list : nullptr, one_wave ? nullptr : d_out};
+                   second ? ovf_list : nullptr, one_wave || direct ? nullptr : d_out,
+                   true, one_wave, direct};
 }
 
 hipError_t launch_plan_leaves(int words, const unsigned long long* hist,
@@ -3046,7 +3130,8 @@ hipError_t launch_plan_leaves(int words, const unsigned long long* hist,
                               int slots_log2, int mode, hipStream_t s) {
   LeafLists q{};
   if (!merge_cshift)
-    q = leaf_lists(words, max_leaves, d_out, large_list, ovf_list, slots_log2, mode);
+    q = leaf_lists(words, max_leaves, d_out, large_list, ovf_list, slots_log2, mode,
+                   tiny_leaves(words, max_leaves, slots_log2, mode, false, false));
   hipLaunchKernelGGL(k_plan_leaves, dim3(1u << shard_bits), dim3(kPlanTB), 0, s, hist, sbegin,
                      bins, shard_bits, subhist, leaves, cursor, merge_cshift, ncls, cls_stride, st,
                      q);
@@ -3123,7 +3208,9 @@ hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uin
                              int slots_log2, hipStream_t s, int mode, bool refine, bool merged,
                              bool classified) {
   const bool wide = words == 2;
-  const LeafLists q = leaf_lists(words, max_leaves, d_out, large_list, ovf_list, slots_log2, mode);
+  const LeafLists q =
+      leaf_lists(words, max_leaves, d_out, large_list, ovf_list, slots_log2, mode,
+                 tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged));
   const uint64_t small_max = q.small_max;
   if (!classified) {
     // n_large and n_ovf
@@ -3131,7 +3218,7 @@ hipError_t launch_leaf_small(int words, int keybits, void* bufA, void* bufB, uin
     hipLaunchKernelGGL(k_classify_leaves, dim3(grid_for(max_leaves, 256, 2048)), dim3(256), 0, s,
                        leaves, st, q);
   }
-  if (q.d_zero) return hipGetLastError();  // every non-empty leaf is in a list
+  if (!q.one_wave) return hipGetLastError();  // the block-wide kernel takes every leaf
   const unsigned gsmall = persistent(max_leaves, kSmallGrid);
 #define KC_SMALLW(KRN, FF)                                                                        \
   hipLaunchKernelGGL((KRN<64, kSmallCmax128, 8, FF>), dim3(gsmall), dim3(64), 0, s, keybits,       \
@@ -3169,7 +3256,6 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                              uint32_t* ovf_list, hipStream_t s, int mode, bool refine,
                              bool merged) {
   const bool wide = words == 2;
-  const uint64_t small_max = small_leaf_max(words);
   // (max_leaves is a bound, two to four times the leaves: fewer workgroups for
   // inputs of few, or most start only to end, in the way of other streams' work)
   const unsigned glarge = persistent(
@@ -3189,16 +3275,28 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                          large_list);
     return hipGetLastError();
   }
-#define KC_LARGEW(KRN, KT, CM, R, FF)                                                             \
-  hipLaunchKernelGGL((KRN<kLeafTB, CM, R, FF>), dim3(glarge), dim3(kLeafTB), 0, s, keybits,        \
-                     (KT*)bufA, (KT*)bufB, tmp_cnt, leaves, st, d_out, slots_log2, large_list,    \
-                     &st->n_large, second, &st->large_records, small_max)
   // the leaves whose table overflows are listed for launch_leaf_second
   uint32_t* const second = slots_log2 < second_slots_log2(words) ? ovf_list : nullptr;
+  // few leaves: from the leaf table, but for those planned for the second count
+  const bool direct = max_leaves <= kFewLeaves;
+  const uint64_t small_max = second ? 8ull << slots_log2 : ~0ull;  // (without a list)
+  const uint32_t* const list = direct ? nullptr : large_list;
+  if (tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged)) {
+    hipLaunchKernelGGL((k_leaf_count64<kRescueTB, kRescueCmax64, 4, true, false>), dim3(glarge),
+                       dim3(kRescueTB), 0, s, keybits, (uint64_t*)bufA, (uint64_t*)bufB, tmp_cnt,
+                       leaves, st, d_out, slots_log2 + 1, (const uint32_t*)nullptr,
+                       (const unsigned long long*)nullptr, (uint32_t*)nullptr,
+                       &st->large_records, ~0ull);
+    return hipGetLastError();
+  }
+#define KC_LARGEW(KRN, KT, CM, R, FF)                                                             \
+  hipLaunchKernelGGL((KRN<kLeafTB, CM, R, FF>), dim3(glarge), dim3(kLeafTB), 0, s, keybits,        \
+                     (KT*)bufA, (KT*)bufB, tmp_cnt, leaves, st, d_out, slots_log2, list,          \
+                     &st->n_large, second, &st->large_records, small_max)
 #define KC_LARGE64(FF, MG)                                                                      \
   hipLaunchKernelGGL((k_leaf_count64<kLeafTB, kLeafCmax64, 4, FF, MG>), dim3(glarge),            \
                      dim3(kLeafTB), 0, s, keybits, (uint64_t*)bufA, (uint64_t*)bufB, tmp_cnt,    \
-                     leaves, st, d_out, slots_log2, large_list, &st->n_large, second,            \
+                     leaves, st, d_out, slots_log2, list, &st->n_large, second,                  \
                      &st->large_records, small_max)
   if (words == 4) {
     if (refine) KC_LARGEW(k_leaf_countw256, u256, kLeafCmax256, 2, true);
@@ -3222,9 +3320,12 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
 }
 
 hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
-                              const Leaf* leaves, DevState* st, uint32_t* d_out, int slots_log2,
-                              const uint32_t* ovf_list, hipStream_t s, int mode, bool merged) {
-  if (mode == 1 || slots_log2 >= second_slots_log2(words) || !ovf_list) return hipSuccess;
+                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
+                              uint32_t* d_out, int slots_log2, const uint32_t* ovf_list,
+                              hipStream_t s, int mode, bool refine, bool merged) {
+  if (mode == 1 || slots_log2 >= second_slots_log2(words) || !ovf_list ||
+      tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged))
+    return hipSuccess;
   // the leaves whose table overflowed are counted again at once by a
   // workgroup per CU with a table twice as large (a leaf overflows because of
   // its distinct keys: clusters of keys that share a long prefix, the
@@ -3304,23 +3405,28 @@ hipError_t launch_plan_out(const uint32_t* d, DevState* st, unsigned long long* 
   return hipGetLastError();
 }
 
+bool concat_plans_out(uint64_t max_leaves) { return max_leaves <= kFewLeaves; }
+
 hipError_t launch_concat(int words, const void* bufA, const void* bufB, const uint32_t* tmp_cnt,
                          const Leaf* leaves, const uint32_t* d, const unsigned long long* out_off,
-                         const DevState* st, uint64_t max_leaves, uint64_t cap,
-                         uint64_t* out_keys, uint32_t* out_counts, hipStream_t s) {
+                         DevState* st, uint64_t max_leaves, uint64_t cap, uint64_t* out_keys,
+                         uint32_t* out_counts, hipStream_t s, DevState* pub) {
   const unsigned grid = persistent((max_leaves + 3) / 4, 16384);
-  if (words == 4)
-    hipLaunchKernelGGL(k_concat<u256>, dim3(grid), dim3(256), 0, s, (const u256*)bufA,
-                       (const u256*)bufB, tmp_cnt, leaves, d, out_off, st, cap, out_keys,
-                       out_counts);
-  else if (words == 2)
-    hipLaunchKernelGGL(k_concat<u128>, dim3(grid), dim3(256), 0, s, (const u128*)bufA,
-                       (const u128*)bufB, tmp_cnt, leaves, d, out_off, st, cap, out_keys,
-                       out_counts);
-  else
-    hipLaunchKernelGGL(k_concat<uint64_t>, dim3(grid), dim3(256), 0, s, (const uint64_t*)bufA,
-                       (const uint64_t*)bufB, tmp_cnt, leaves, d, out_off, st, cap, out_keys,
-                       out_counts);
+#define KC_CONCAT(K, OFFS)                                                                       \
+  hipLaunchKernelGGL((k_concat<K, OFFS>), dim3(grid), dim3(256), 0, s, (const K*)bufA,           \
+                     (const K*)bufB, tmp_cnt, leaves, d, out_off, st, cap, out_keys, out_counts, pub)
+  if (out_off) {
+    if (words == 4) KC_CONCAT(u256, true);
+    else if (words == 2) KC_CONCAT(u128, true);
+    else KC_CONCAT(uint64_t, true);
+  } else {
+    // a workgroup for every four leaves
+    if (!concat_plans_out(max_leaves)) return hipErrorInvalidValue;
+    if (words == 4) KC_CONCAT(u256, false);
+    else if (words == 2) KC_CONCAT(u128, false);
+    else KC_CONCAT(uint64_t, false);
+  }
+#undef KC_CONCAT
   return hipGetLastError();
 }
 

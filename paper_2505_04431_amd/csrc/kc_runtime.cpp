@@ -649,8 +649,9 @@ void refine_overflowed(Ctx& c, Call& q, kc_stats& S, Timer& tm, uint64_t nl0,
                                  q.o.mode, true, q.merged),
            "leaf count launch");
     hipchk(kc::launch_leaf_second(q.words, q.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
-                                  (kc::Leaf*)c.aleaves.p, dst_state, (uint32_t*)c.adcnt.p,
-                                  q.slots_log2, (uint32_t*)c.aovfl.p, st, q.o.mode, q.merged),
+                                  (kc::Leaf*)c.aleaves.p, dst_state, na, (uint32_t*)c.adcnt.p,
+                                  q.slots_log2, (uint32_t*)c.aovfl.p, st, q.o.mode, true,
+                                  q.merged),
            "leaf count launch");
     tm.mark(ST_REFINE);
     uint32_t* hd = (uint32_t*)host_stage(c, na * 4 + 64);
@@ -903,13 +904,17 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
          "leaf count launch");
   tm.mark(ST_LEAF);
   hipchk(kc::launch_leaf_second(p.words, p.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
-                                (kc::Leaf*)c.leaves.p, dstate, (uint32_t*)c.dcnt.p, p.slots_log2,
-                                (uint32_t*)c.ovfl.p, st, p.mode, p.merge_cshift != 0),
+                                (kc::Leaf*)c.leaves.p, dstate, p.max_leaves, (uint32_t*)c.dcnt.p,
+                                p.slots_log2, (uint32_t*)c.ovfl.p, st, p.mode, false,
+                                p.merge_cshift != 0),
          "leaf count launch");
   tm.mark(ST_LEAF_SECOND);
-  hipchk(kc::launch_plan_out((uint32_t*)c.dcnt.p, dstate, (unsigned long long*)c.bsum.p,
-                             p.max_leaves, (unsigned long long*)c.outoff.p, st, out.pub),
-         "plan_out launch");
+  // few leaves: the concat finds the output offsets itself
+  const bool plan_in_concat = out.concat && !out.set && kc::concat_plans_out(p.max_leaves);
+  if (!plan_in_concat)
+    hipchk(kc::launch_plan_out((uint32_t*)c.dcnt.p, dstate, (unsigned long long*)c.bsum.p,
+                               p.max_leaves, (unsigned long long*)c.outoff.p, st, out.pub),
+           "plan_out launch");
   tm.mark(ST_OUT);
   if (!out.concat) return;
   if (out.set)
@@ -921,8 +926,8 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
   else
     hipchk(kc::launch_concat(p.words, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                              (kc::Leaf*)c.leaves.p, (uint32_t*)c.dcnt.p,
-                             (unsigned long long*)c.outoff.p, dstate, p.max_leaves, out.cap,
-                             out.keys, out.counts, st),
+                             plan_in_concat ? nullptr : (unsigned long long*)c.outoff.p, dstate,
+                             p.max_leaves, out.cap, out.keys, out.counts, st, out.pub),
            "concat launch");
   tm.mark(ST_CONCAT);
 }

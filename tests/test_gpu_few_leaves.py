@@ -6,6 +6,7 @@ import numpy as np
 import pytest
 
 import oracle
+import paper_2505_04431_amd as kc
 import synth
 from gpu_util import assert_same, gpu_count
 
@@ -26,7 +27,7 @@ def reads():
 @pytest.mark.parametrize("leaf_target", [14, 15, 16, 60, 66, 67, 68, 4000])
 def test_leaf_numbers(reads, k, leaf_target):
     r, o = reads
-    n = 2 * int(o[-1]) // leaf_target + 2 * (512 if k == 55 else 256) + 1
+    n = 2 * int(o[-1]) // leaf_target + 2 * 256 + 1
     assert n > 4096 or leaf_target > 60
     got = gpu_count(r, o, k, P=3, leaf_target=leaf_target, leaf_attempt=leaf_target, check=1)
     assert_same(got, oracle.count(r, o, k), "k %d, at most %d leaves" % (k, n))
@@ -38,3 +39,18 @@ def test_few_reads(n):
     r, o = synth.reads(g, n, 101, err_rate=0.01, seed=n)
     for k in (1, 21, 32, 40, 90):
         assert_same(gpu_count(r, o, k, P=2), oracle.count(r, o, k), "%d reads, k %d" % (n, k))
+
+
+@pytest.mark.parametrize("k", [5, 21, 31, 55, 100])
+@pytest.mark.parametrize("leaf_target", [930, 940, 945, 960, 3_000, 200_000])
+def test_tiny_inputs(reads, k, leaf_target):
+    """Up to 768 leaves of one-word keys are counted with the larger table at
+    once; leaves of more distinct keys than that holds are refined."""
+    r, o = reads
+    want = oracle.count(r, o, k)
+    for sb in (0, 1, 3):
+        got = gpu_count(r, o, k, P=2, shard_bits=sb, leaf_target=leaf_target,
+                        leaf_attempt=leaf_target, check=1)
+        assert_same(got, want, "k %d, %d shard bits" % (k, sb))
+        if sb == 1 and leaf_target == 200_000 and k == 31:
+            assert kc.last_stats()["n_overflow"] > 0
