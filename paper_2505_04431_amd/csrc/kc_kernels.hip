@@ -758,7 +758,9 @@ __global__ void __launch_bounds__(TB) k_window_hist(const uint64_t* __restrict__
        unit += (uint64_t)gridDim.x * TB * S) {
     SetRange range{0, 0, true};
     if constexpr (BATCH) {
-      range = sets_of(bs, unit, min(w_end, unit + (uint64_t)TB * S));
+      // (to the unit's end: a thread's S starts may pass w_end, which is rounded to
+      // the scatter's starts per thread, and those there belong to the next set)
+      range = sets_of(bs, unit, unit + (uint64_t)TB * S);
       if (!range.any) continue;
     }
     const uint64_t g = unit + (uint64_t)threadIdx.x * S;
