@@ -77,10 +77,16 @@ struct LeafLists {
 // byte of set s relative to the packed stream (n_sets + 1 entries), and
 // set_local[s] its id within the k-class being counted (kNoSet if the set
 // belongs to another class).
+// cut: keys of up to 74 bits as one-word records, their low 64 bits. What is cut
+// off is part of the shard (shard_bits >= set id bits, keybits - shard_bits <=
+// 64): a shard's records agree in it, so they are split, counted and sorted by
+// the bits kept, and the set id is the shard's top bits. No record is all ones:
+// the low 2k bits are a canonical k-mer, which never is.
 struct BatchSets {
   const unsigned long long* set_byte_off;
   const uint32_t* set_local;
   uint32_t n_sets;
+  bool cut;
 };
 constexpr uint32_t kNoSet = 0xFFFFFFFFu;
 
@@ -270,8 +276,9 @@ hipError_t launch_concat(int words, const void* bufA, const void* bufB, const ui
 hipError_t launch_concat_batch(int words, const void* bufA, const void* bufB,
                                const uint32_t* tmp_cnt, const Leaf* leaves, const uint32_t* d,
                                const unsigned long long* out_off, const DevState* st,
-                               uint64_t max_leaves, uint64_t cap, int k, uint64_t* out_keys,
-                               uint32_t* out_counts, uint32_t* out_set, hipStream_t s);
+                               uint64_t max_leaves, uint64_t cap, int k, int cut_kb,
+                               uint64_t* out_keys, uint32_t* out_counts, uint32_t* out_set,
+                               hipStream_t s);
 hipError_t launch_set_bounds(const uint32_t* set, const DevState* st, uint64_t max_pairs,
                              uint32_t n_local, unsigned long long* start, hipStream_t s);
 hipError_t launch_batch_offsets(const uint32_t* set_class, const uint32_t* set_local,

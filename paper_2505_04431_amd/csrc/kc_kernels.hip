@@ -684,10 +684,13 @@ __device__ __forceinline__ uint32_t set_of(const BatchSets& bs, const SetRange& 
 // a batch of read sets, the key of a window is (set id within its k-class <<
 // 2k) | canonical k-mer, so that sorting keys sorts by set, then k-mer; windows
 // of sets outside the class are dropped from vm. Returns the updated vm.
-template <typename K, typename Kc, int S, bool BATCH>
+// Cut keys (CUT, one word, see BatchSets): the key's low 64 bits, and in
+// shard[] its top set_bits + kb bits.
+template <typename K, typename Kc, int S, bool BATCH, bool CUT>
 __device__ __forceinline__ uint32_t window_keys(const uint64_t* __restrict__ packed, uint64_t g,
                                                 int k, uint32_t vm, const BatchSets& bs,
-                                                const SetRange& range, K (&key)[S]) {
+                                                const SetRange& range, K (&key)[S], int kb,
+                                                uint32_t (&shard)[CUT ? S : 1]) {
   Kc c[S];
   if constexpr (Key<Kc>::kWords == 4) {
     const uint64_t w = g >> 5;
@@ -714,6 +717,7 @@ __device__ __forceinline__ uint32_t window_keys(const uint64_t* __restrict__ pac
     if (loc == kNoSet) vm &= ~(1u << i);
     // (a class of one k = 32 set has no set-id bits: no shift by the key width)
     else key[i] = (2 * k < (int)(8 * sizeof(K)) ? ((K)loc << (2 * k)) : (K)0) | (K)c[i];
+    if constexpr (CUT) shard[i] = (loc << kb) | (uint32_t)((c[i] >> 1) >> (2 * k - 1 - kb));
   }
   return vm;
   }
@@ -797,7 +801,8 @@ __global__ void __launch_bounds__(TB) k_window_hist(const uint64_t* __restrict__
       continue;
     }
     K keys[S];
-    vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, range, keys);
+    uint32_t none[1];
+    vm = window_keys<K, Kc, S, BATCH, false>(packed, g, k, vm, bs, range, keys, 0, none);
 #pragma unroll
     for (int i = 0; i < S; ++i)
       if (vm & (1u << i)) atomicAdd(&sh[shard_of(keys[i], keybits, shard_bits)], 1u);
@@ -813,7 +818,8 @@ __global__ void __launch_bounds__(TB) k_window_hist(const uint64_t* __restrict__
 // TB*S window starts: the tile's records are ranked per shard in LDS, each
 // shard's run reserves its place in its class's part with one global atomic,
 // and the runs leave LDS as coalesced writes.
-template <typename K, typename Kc, int S, int TB, bool BATCH>
+// CUT (see BatchSets): the shard is not in the record; it is staged beside it.
+template <typename K, typename Kc, int S, int TB, bool BATCH, bool CUT = false>
 __device__ __forceinline__ void window_scatter_body(const uint64_t* __restrict__ packed,
                                                     const uint64_t* __restrict__ valid,
                                                     uint64_t t_begin, uint64_t t_end, int k,
@@ -825,7 +831,9 @@ __device__ __forceinline__ void window_scatter_body(const uint64_t* __restrict__
   __shared__ uint32_t loff[NBMAX];  // per shard: records in the tile, then their run offsets
   __shared__ unsigned long long gbase[NBMAX];
   __shared__ uint32_t wsum[TB / 64];
+  __shared__ uint16_t stage_shard[CUT ? TB * S : 1];
   const int nb = 1 << shard_bits;
+  const int kb = CUT ? shard_bits - (keybits - 2 * k) : 0;
   const uint64_t n_tiles = (t_end - t_begin + TB - 1) / TB;
   for (uint64_t tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
     // tiles of class tile mod kXcds take their runs from their own part of
@@ -846,11 +854,16 @@ __device__ __forceinline__ void window_scatter_body(const uint64_t* __restrict__
     uint32_t vm = t < t_end ? valid_starts<S>(valid, g) : 0u;
     K key[S];
     uint32_t rank[S];  // (the shard is recomputed from the key: fewer live registers)
+    uint32_t cut_shard[CUT ? S : 1];
+    auto shard = [&](int i) {
+      if constexpr (CUT) return cut_shard[i];
+      else return shard_of(key[i], keybits, shard_bits);
+    };
     if (vm) {
-      vm = window_keys<K, Kc, S, BATCH>(packed, g, k, vm, bs, range, key);
+      vm = window_keys<K, Kc, S, BATCH, CUT>(packed, g, k, vm, bs, range, key, kb, cut_shard);
 #pragma unroll
       for (int i = 0; i < S; ++i)
-        if (vm & (1u << i)) rank[i] = atomicAdd(&loff[shard_of(key[i], keybits, shard_bits)], 1u);
+        if (vm & (1u << i)) rank[i] = atomicAdd(&loff[shard(i)], 1u);
     }
     __syncthreads();
     const uint32_t total = block_exscan_inplace<TB>(loff, nb, wsum);
@@ -860,11 +873,17 @@ __device__ __forceinline__ void window_scatter_body(const uint64_t* __restrict__
     }
 #pragma unroll
     for (int i = 0; i < S; ++i)
-      if (vm & (1u << i)) stage[loff[shard_of(key[i], keybits, shard_bits)] + rank[i]] = key[i];
+      if (vm & (1u << i)) {
+        const uint32_t p = loff[shard(i)] + rank[i];
+        stage[p] = key[i];
+        if constexpr (CUT) stage_shard[p] = (uint16_t)shard(i);
+      }
     __syncthreads();
     for (uint32_t j = threadIdx.x; j < total; j += TB) {
       const K kk = stage[j];  // its shard again from the key: cheaper than staging it
-      const uint32_t b = shard_of(kk, keybits, shard_bits);
+      uint32_t b;
+      if constexpr (CUT) b = stage_shard[j];
+      else b = shard_of(kk, keybits, shard_bits);
       out[gbase[b] + (j - loff[b])] = kk;
     }
     __syncthreads();
@@ -880,6 +899,17 @@ __global__ void __launch_bounds__(TB) k_window_scatter(const uint64_t* __restric
                                                        K* __restrict__ out) {
   window_scatter_body<K, Kc, S, TB, BATCH>(packed, valid, t_begin, t_end, k, keybits,
                                            shard_bits, bs, cursor, out);
+}
+
+// Cut keys of a batch.
+template <int S, int TB>
+__global__ void __launch_bounds__(TB)
+k_window_scatter_cut(const uint64_t* __restrict__ packed, const uint64_t* __restrict__ valid,
+                     uint64_t t_begin, uint64_t t_end, int k, int keybits, int shard_bits,
+                     BatchSets bs, unsigned long long* __restrict__ cursor,
+                     uint64_t* __restrict__ out) {
+  window_scatter_body<uint64_t, uint64_t, S, TB, true, true>(packed, valid, t_begin, t_end, k,
+                                                             keybits, shard_bits, bs, cursor, out);
 }
 
 // Plain 64-bit keys: registers capped so that two 1024-thread workgroups
@@ -1086,7 +1116,9 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_leaves(
   if (!h) return;
   const SplitBin b = bins[c];
   if (b.nbits == 0) {
-    if (threadIdx.x == 0) leaves[b.hist_off] = Leaf{sbegin[c], sbegin[c] + h, 0u, (uint32_t)shard_bits};
+    if (threadIdx.x == 0)
+      leaves[b.hist_off] =
+          Leaf{sbegin[c], sbegin[c] + h, 0u, (uint32_t)shard_bits, 0u, (uint32_t)c};
     if (q.on) classify_leaves(threadIdx.x == 0, (uint32_t)b.hist_off, h, st, q, sh, base);
     return;
   }
@@ -2686,13 +2718,14 @@ __global__ void __launch_bounds__(256) k_concat(const K* __restrict__ bufA,
 }
 
 // Batch form of concat: writes the k-mer (low 2k bits) and the set id within
-// the class (the bits above) of every pair, in key order.
+// the class (the bits above) of every pair, in key order. cut_kb >= 0: of cut keys
+// (see BatchSets), whose set id is the leaf's shard without its low cut_kb bits.
 template <typename K>
 __global__ void __launch_bounds__(256) k_concat_batch(
     const K* __restrict__ bufA, const K* __restrict__ bufB, const uint32_t* __restrict__ tmp_cnt,
     const Leaf* __restrict__ leaves, const uint32_t* __restrict__ d,
     const unsigned long long* __restrict__ out_off, const DevState* __restrict__ st, uint64_t cap,
-    int k, uint64_t* __restrict__ out_keys, uint32_t* __restrict__ out_counts,
+    int k, int cut_kb, uint64_t* __restrict__ out_keys, uint32_t* __restrict__ out_counts,
     uint32_t* __restrict__ out_set) {
   if (st->overflow) return;  // the class is recounted set by set
   const unsigned long long n_leaves = st->n_leaves;
@@ -2726,7 +2759,9 @@ __global__ void __launch_bounds__(256) k_concat_batch(
         if (i >= lim) break;
         const uint64_t o = base + i;
         out_keys[o] = (uint64_t)(key[u] & kmask);
-        out_set[o] = has_set_bits ? (uint32_t)(key[u] >> (2 * k)) : 0u;
+        out_set[o] = cut_kb >= 0 ? lf.shard >> cut_kb
+                     : has_set_bits ? (uint32_t)(key[u] >> (2 * k))
+                                    : 0u;
         out_counts[o] = cnt[u];
       }
     }
@@ -2877,6 +2912,10 @@ constexpr int kSplitTB128 = 512;
 // many waves: 1,000,000 reads at k = 100 1.16 ms, so 1.06)
 constexpr int kScatterTB256 = 512;
 constexpr int kScatterS256 = 4, kScatterS128 = 4;
+// cut keys: tiles of 4,096 records and their shards, 52 KB, three workgroups a CU
+// (four starts per thread and 1,024 threads: 512 us against 285 in the batch of 48
+// sets)
+constexpr int kScatterSCut = 8, kScatterTBCut = 512;
 inline int scatter_starts(int words, int starts_per_thread) {
   return words == 4 ? kScatterS256 : words == 2 ? kScatterS128 : starts_per_thread == 16 ? 16 : kWinStarts;
 }
@@ -3001,8 +3040,9 @@ hipError_t launch_window_hist(int words, const uint64_t* packed, const uint64_t*
                               int keybits, int shard_bits, const BatchSets* batch,
                               unsigned long long* hist, int starts_per_thread, hipStream_t s) {
   // the owner scatter's tiles (see launch_window_scatter)
-  const int S = scatter_starts(words, starts_per_thread);
-  const int TBs = words == 4 ? kScatterTB256 : words == 2 ? kScatterTB128 : kScatterTB64;
+  const bool cut = batch && batch->cut;
+  const int S = cut ? kScatterSCut : scatter_starts(words, starts_per_thread);
+  const int TBs = cut ? kScatterTBCut : words == 4 ? kScatterTB256 : words == 2 ? kScatterTB128 : kScatterTB64;
   const uint64_t w_begin = byte_begin / S * S;
   const uint64_t w_end = (byte_end + S - 1) / S * S;
   const uint64_t unit = (uint64_t)kHistTB * kWinStarts;
@@ -3012,7 +3052,7 @@ hipError_t launch_window_hist(int words, const uint64_t* packed, const uint64_t*
   const uint64_t step = (uint64_t)R * kXcds;
   const unsigned grid = (unsigned)std::min<uint64_t>((n_units + step - 1) / step * step, kHistGrid);
   if (grid == 0) return hipSuccess;
-  const BatchSets bs = batch ? *batch : BatchSets{nullptr, nullptr, 0};
+  const BatchSets bs = batch ? *batch : BatchSets{nullptr, nullptr, 0, false};
   const bool wide = words == 2;
   if (batch) {
     if (words == 4) return hipErrorInvalidValue;
@@ -3032,7 +3072,16 @@ hipError_t launch_window_scatter(int words, const uint64_t* packed, const uint64
                                  int k, int keybits, int shard_bits, const BatchSets* batch,
                                  unsigned long long* cursor, void* out, int starts_per_thread,
                                  hipStream_t s) {
-  const BatchSets bs0 = batch ? *batch : BatchSets{nullptr, nullptr, 0};
+  const BatchSets bs0 = batch ? *batch : BatchSets{nullptr, nullptr, 0, false};
+  if (batch && batch->cut) {
+    if (words != 1) return hipErrorInvalidValue;
+    const uint64_t t0 = byte_begin / kScatterSCut;
+    const uint64_t t1 = (byte_end + kScatterSCut - 1) / kScatterSCut;
+    hipLaunchKernelGGL((k_window_scatter_cut<kScatterSCut, kScatterTBCut>),
+                       dim3(grid_for(t1 - t0, kScatterTBCut, 1u << 20)), dim3(kScatterTBCut), 0, s,
+                       packed, valid, t0, t1, k, keybits, shard_bits, bs0, cursor, (uint64_t*)out);
+    return hipGetLastError();
+  }
   if (words == 1 && starts_per_thread == 16) {
     // byte_begin is a multiple of 32 (batch classes) or 0
     constexpr int S = 16;
@@ -3051,7 +3100,7 @@ hipError_t launch_window_scatter(int words, const uint64_t* packed, const uint64
   const int S = scatter_starts(words, starts_per_thread);
   const uint64_t t_begin = byte_begin / S;
   const uint64_t t_end = (byte_end + S - 1) / S;
-  const BatchSets bs = batch ? *batch : BatchSets{nullptr, nullptr, 0};
+  const BatchSets bs = batch ? *batch : BatchSets{nullptr, nullptr, 0, false};
 #define ARG0 cursor
   if (words == 4) {
     if (batch) return hipErrorInvalidValue;
@@ -3452,18 +3501,19 @@ namespace kc {
 hipError_t launch_concat_batch(int words, const void* bufA, const void* bufB,
                                const uint32_t* tmp_cnt, const Leaf* leaves, const uint32_t* d,
                                const unsigned long long* out_off, const DevState* st,
-                               uint64_t max_leaves, uint64_t cap, int k, uint64_t* out_keys,
-                               uint32_t* out_counts, uint32_t* out_set, hipStream_t s) {
+                               uint64_t max_leaves, uint64_t cap, int k, int cut_kb,
+                               uint64_t* out_keys, uint32_t* out_counts, uint32_t* out_set,
+                               hipStream_t s) {
   const unsigned grid = persistent((max_leaves + 3) / 4, 16384);
   if (words == 4) return hipErrorInvalidValue;
   if (words == 2)
     hipLaunchKernelGGL(k_concat_batch<u128>, dim3(grid), dim3(256), 0, s, (const u128*)bufA,
-                       (const u128*)bufB, tmp_cnt, leaves, d, out_off, st, cap, k, out_keys,
+                       (const u128*)bufB, tmp_cnt, leaves, d, out_off, st, cap, k, -1, out_keys,
                        out_counts, out_set);
   else
     hipLaunchKernelGGL(k_concat_batch<uint64_t>, dim3(grid), dim3(256), 0, s,
                        (const uint64_t*)bufA, (const uint64_t*)bufB, tmp_cnt, leaves, d, out_off,
-                       st, cap, k, out_keys, out_counts, out_set);
+                       st, cap, k, cut_kb, out_keys, out_counts, out_set);
   return hipGetLastError();
 }
 

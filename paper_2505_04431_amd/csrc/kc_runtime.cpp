@@ -751,6 +751,7 @@ struct Pipe {
   uint64_t T = 0, H = 0;
   uint64_t max_items = 0, max_leaves = 0;
   const kc::BatchSets* batch = nullptr;   // batch form (composite keys)
+  bool cut = false;                       // of them, one-word records of wider keys (BatchSets)
   int mode = 0;                           // leaf count: 0 hash tables, 1 sort
   int scatter_s = 8, split_r = 8;         // LDS tile shape of the two scatters (one-word keys)
   int merge_cshift = 0;                   // != 0: the split scatter pre-aggregates equal keys
@@ -921,7 +922,8 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
     hipchk(kc::launch_concat_batch(p.words, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                    (kc::Leaf*)c.leaves.p, (uint32_t*)c.dcnt.p,
                                    (unsigned long long*)c.outoff.p, dstate, p.max_leaves, out.cap,
-                                   p.k, out.keys, out.counts, out.set, st),
+                                   p.k, p.cut ? p.sb - (p.keybits - 2 * p.k) : -1, out.keys,
+                                   out.counts, out.set, st),
            "concat launch");
   else
     hipchk(kc::launch_concat(p.words, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
@@ -1420,14 +1422,25 @@ int batch_plan_impl(const uint64_t* host_set_reads, const uint64_t* host_set_byt
       Pipe& p = C.pipe;
       p.k = C.k;
       p.keybits = 2 * C.k + C.set_bits;
-      p.words = p.keybits > 64 ? 2 : 1;
-      uint64_t Cslots;
-      table_params(b->o, p.words, p.slots_log2, Cslots, p.T, p.H);
       p.rec_bound = std::max<uint64_t>(bytes, 1);
-      p.sb = b->o.shard_bits > 0 ? std::min(b->o.shard_bits, kc::max_shard_bits())
-                                 : std::max(shard_bits_for(b->o, P, p.rec_bound, p.T, p.keybits),
-                                            std::min(kc::max_shard_bits(), C.set_bits + 3));
-      p.sb = std::max(1, std::min(p.sb, p.keybits));
+      const auto plan = [&](int words) {
+        uint64_t Cslots;
+        p.words = words;
+        table_params(b->o, words, p.slots_log2, Cslots, p.T, p.H);
+        p.sb = b->o.shard_bits > 0 ? std::min(b->o.shard_bits, kc::max_shard_bits())
+                                   : std::max(shard_bits_for(b->o, P, p.rec_bound, p.T, p.keybits),
+                                              std::min(kc::max_shard_bits(), C.set_bits + 3));
+        p.sb = std::max(1, std::min(p.sb, p.keybits));
+      };
+      plan(1);
+      if (p.keybits > 64) {
+        // one-word records where the shard holds what is cut off: half the bytes
+        // of two-word ones through every step (48 sets, 24 of them of k = 31:
+        // 3.29 -> 2.36 ms, of it the owner scatter 560 -> 285 us, the split 611 ->
+        // 357, the leaves 635 -> 300)
+        p.cut = b->o.mode == 0 && C.set_bits <= p.sb && p.keybits - p.sb <= 64;
+        if (!p.cut) plan(2);
+      }
       p.byte_begin = lo & ~31ull;
       p.byte_end = hi;
       tile_params(b->o, p);
@@ -1472,7 +1485,7 @@ int batch_plan_impl(const uint64_t* host_set_reads, const uint64_t* host_set_byt
     upload_sync(w.class_base_dev.p, cbase.data(), w.cls.size() * 8, st);
     for (kc_batch::Class& C : w.cls) {
       C.bs = kc::BatchSets{(const unsigned long long*)w.byte_off_dev.p,
-                           (const uint32_t*)C.set_local.p, w.ns};
+                           (const uint32_t*)C.set_local.p, w.ns, C.pipe.cut};
       C.pipe.batch = &C.bs;
     }
     max_bytes = std::max(max_bytes, w.nbytes);
