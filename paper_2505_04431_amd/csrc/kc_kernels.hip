@@ -2916,6 +2916,16 @@ constexpr int kScatterS256 = 4, kScatterS128 = 4;
 // (four starts per thread and 1,024 threads: 512 us against 285 in the batch of 48
 // sets)
 constexpr int kScatterSCut = 8, kScatterTBCut = 512;
+// One-word keys of a batch: the same tiles (a batch's kernel keeps too many values
+// live for two workgroups of 1,024 threads a CU: 244 against 193 us in that batch).
+constexpr int kScatterTBBatch64 = 512;
+inline int scatter_threads(int words, bool batch, bool cut, int starts) {
+  return cut          ? kScatterTBCut
+         : words == 4 ? kScatterTB256
+         : words == 2 ? kScatterTB128
+         : batch && starts == kWinStarts ? kScatterTBBatch64
+                                         : kScatterTB64;
+}
 inline int scatter_starts(int words, int starts_per_thread) {
   return words == 4 ? kScatterS256 : words == 2 ? kScatterS128 : starts_per_thread == 16 ? 16 : kWinStarts;
 }
@@ -3042,7 +3052,7 @@ hipError_t launch_window_hist(int words, const uint64_t* packed, const uint64_t*
   // the owner scatter's tiles (see launch_window_scatter)
   const bool cut = batch && batch->cut;
   const int S = cut ? kScatterSCut : scatter_starts(words, starts_per_thread);
-  const int TBs = cut ? kScatterTBCut : words == 4 ? kScatterTB256 : words == 2 ? kScatterTB128 : kScatterTB64;
+  const int TBs = scatter_threads(words, batch != nullptr, cut, S);
   const uint64_t w_begin = byte_begin / S * S;
   const uint64_t w_end = (byte_end + S - 1) / S * S;
   const uint64_t unit = (uint64_t)kHistTB * kWinStarts;
@@ -3119,7 +3129,9 @@ hipError_t launch_window_scatter(int words, const uint64_t* packed, const uint64
   } else {
     const unsigned grid = grid_for(t_end - t_begin, kScatterTB64, 1u << 20);
 #define ARG1 (uint64_t*)out
-    if (batch) KC_WINDOW_LAUNCH(k_window_scatter, uint64_t, uint64_t, kScatterTB64, true, grid);
+    if (batch)
+      KC_WINDOW_LAUNCH(k_window_scatter, uint64_t, uint64_t, kScatterTBBatch64, true,
+                       grid_for(t_end - t_begin, kScatterTBBatch64, 1u << 20));
     else KC_WINDOW_LAUNCH(k_window_scatter64, uint64_t, uint64_t, kScatterTB64, false, grid);
 #undef ARG1
   }
