@@ -156,7 +156,16 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
                               int tile, unsigned long long* sbegin, unsigned long long* cursor,
                               SplitBin* bins, SplitItem* items, unsigned long long* item_off,
                               unsigned long long* subhist, uint64_t max_items, DevState* st,
-                              hipStream_t s);
+                              Leaf* leaves, hipStream_t s);
+
+// Whether an input of one-word keys is small enough to be counted without a
+// split: every shard a leaf (launch_plan_shards lists them in leaves, nullptr
+// elsewhere), whatever its records, counted with the larger table. On average a
+// shard then holds a quarter of that table's slots at most; where one still has
+// more distinct keys than the table, st->overflow is set and the caller counts
+// again with a split.
+bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
+                    int slots_log2);
 
 // Device planning of the leaves (one block): leaf table in key order and the
 // sub-bin cursors of the split shards.

@@ -955,7 +955,7 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_shards(
     unsigned long long* __restrict__ sbegin, unsigned long long* __restrict__ cursor,
     SplitBin* __restrict__ bins, unsigned long long* __restrict__ item_off,
     unsigned long long* __restrict__ subhist, DevState* __restrict__ st,
-    SplitItem* __restrict__ items) {
+    SplitItem* __restrict__ items, Leaf* __restrict__ leaves) {
   __shared__ unsigned long long wsum[kPlanTB / 64];
   __shared__ unsigned long long s_hist[kPlanTB], s_off[kPlanTB + 1], s_begin[kPlanTB];
   const int nb = 1 << shard_bits;  // <= kPlanTB
@@ -1001,14 +1001,18 @@ __global__ void __launch_bounds__(kPlanTB) k_plan_shards(
   if (t < nb) {
     bins[t] = SplitBin{loff, (uint32_t)(keybits - shard_bits - nbits), (uint32_t)nbits};
     item_off[t] = ioff;
-    if (!nbits && h) subhist[loff] = h;  // split shards' counters were cleared before
+    if (leaves) {  // no shard is split (leaf_attempt): a leaf each
+      if (h) leaves[loff] = Leaf{s_begin[t], s_begin[t] + h, 0u, (uint32_t)shard_bits, 0u, (uint32_t)t};
+    } else if (!nbits && h) {
+      subhist[loff] = h;  // split shards' counters were cleared before
+    }
   }
   if (t == 0) {
     item_off[nb] = n_items;
     st->n_items = n_items;
     st->n_leaves = n_leaves;
   }
-  if (!items) return;  // many items: k_plan_items lists them
+  if (!items || leaves) return;  // many items: k_plan_items lists them
   if (t < nb) s_off[t] = ioff;
   if (t == 0) s_off[nb] = n_items;
   __syncthreads();
@@ -3146,11 +3150,12 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
                               int tile, unsigned long long* sbegin, unsigned long long* cursor,
                               SplitBin* bins, SplitItem* items, unsigned long long* item_off,
                               unsigned long long* subhist, uint64_t max_items, DevState* st,
-                              hipStream_t s) {
-  const bool few = max_items <= kFewItems;
+                              Leaf* leaves, hipStream_t s) {
+  if (leaves) leaf_attempt = ~0ull;
+  const bool few = leaves || max_items <= kFewItems;
   hipLaunchKernelGGL(k_plan_shards, dim3(1), dim3(kPlanTB), 0, s, hist, order, shard_bits,
                      keybits, leaf_target, leaf_attempt, tile, sbegin, cursor, bins, item_off,
-                     subhist, st, few ? items : (SplitItem*)nullptr);
+                     subhist, st, few ? items : (SplitItem*)nullptr, leaves);
   if (!few)
     hipLaunchKernelGGL(k_plan_items, dim3(grid_for(max_items, 256, 2048)), dim3(256), 0, s, hist,
                      sbegin, item_off, shard_bits, tile, st, items);
@@ -3166,6 +3171,12 @@ static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode
                         bool merged) {
   return words == 1 && mode != 1 && !refine && !merged && max_leaves <= kTinyLeaves &&
          (1 << slots_log2) == kLeafCmax64;
+}
+
+bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
+                    int slots_log2) {
+  return tiny_leaves(words, max_leaves, slots_log2, 0, false, false) &&
+         rec_bound <= (uint64_t)kRescueCmax64 / 4 << shard_bits;
 }
 
 // Which leaves go where (see classify_leaves).

@@ -756,6 +756,10 @@ struct Pipe {
   int scatter_s = 8, split_r = 8;         // LDS tile shape of the two scatters (one-word keys)
   int merge_cshift = 0;                   // != 0: the split scatter pre-aggregates equal keys
   const int* order = nullptr;             // device, owner-major shard order
+  // every shard is a leaf: three launches less (split histogram, leaf plan and
+  // split scatter; 667 reads of 150 bp
+  // 82 -> 67 us)
+  bool unsplit = false;
 };
 
 // Tile shapes of the scatters from the options (0 = automatic).
@@ -862,7 +866,8 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
                                 kc::split_tile(p.words, p.split_r), (unsigned long long*)c.sbegin.p,
                                 (unsigned long long*)c.cursor.p, (kc::SplitBin*)c.bins.p,
                                 (kc::SplitItem*)c.items.p, (unsigned long long*)c.itemoff.p,
-                                (unsigned long long*)c.subhist.p, p.max_items, dstate, st),
+                                (unsigned long long*)c.subhist.p, p.max_items, dstate,
+                                p.unsplit ? (kc::Leaf*)c.leaves.p : nullptr, st),
          "plan_shards launch");
   hipchk(kc::launch_window_scatter(p.words, (uint64_t*)c.packed.p, (uint64_t*)c.valid.p,
                                    p.byte_begin, p.byte_end, p.k, p.keybits,
@@ -870,23 +875,25 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
                                    p.scatter_s, st),
          "owner scatter launch");
   tm.mark(ST_SCATTER);
-  hipchk(kc::launch_split_hist(p.words, c.bufA.p, (kc::SplitItem*)c.items.p, dstate, p.max_items,
-                               (kc::SplitBin*)c.bins.p, (unsigned long long*)c.subhist.p, ncls,
-                               p.max_leaves, st),
-         "split histogram launch");
-  tm.mark(ST_SPLIT_HIST);
-  hipchk(kc::launch_plan_leaves(p.words, (unsigned long long*)c.hist.p, (unsigned long long*)c.sbegin.p,
-                                (kc::SplitBin*)c.bins.p, p.sb, (unsigned long long*)c.subhist.p,
-                                (kc::Leaf*)c.leaves.p, (unsigned long long*)c.cursor2.p,
-                                p.merge_cshift, ncls, p.max_leaves, dstate, p.max_leaves,
-                                (uint32_t*)c.dcnt.p, (uint32_t*)c.large.p, (uint32_t*)c.ovfl.p,
-                                p.slots_log2, p.mode, st),
-         "plan_leaves launch");
-  hipchk(kc::launch_split_scatter(p.words, c.bufA.p, c.bufB.p, (kc::SplitItem*)c.items.p, dstate,
-                                  p.max_items, (kc::SplitBin*)c.bins.p,
-                                  (unsigned long long*)c.cursor2.p, p.split_r, p.merge_cshift,
-                                  ncls, p.max_leaves, st),
-         "split scatter launch");
+  if (!p.unsplit) {
+    hipchk(kc::launch_split_hist(p.words, c.bufA.p, (kc::SplitItem*)c.items.p, dstate, p.max_items,
+                                 (kc::SplitBin*)c.bins.p, (unsigned long long*)c.subhist.p, ncls,
+                                 p.max_leaves, st),
+           "split histogram launch");
+    tm.mark(ST_SPLIT_HIST);
+    hipchk(kc::launch_plan_leaves(p.words, (unsigned long long*)c.hist.p, (unsigned long long*)c.sbegin.p,
+                                  (kc::SplitBin*)c.bins.p, p.sb, (unsigned long long*)c.subhist.p,
+                                  (kc::Leaf*)c.leaves.p, (unsigned long long*)c.cursor2.p,
+                                  p.merge_cshift, ncls, p.max_leaves, dstate, p.max_leaves,
+                                  (uint32_t*)c.dcnt.p, (uint32_t*)c.large.p, (uint32_t*)c.ovfl.p,
+                                  p.slots_log2, p.mode, st),
+           "plan_leaves launch");
+    hipchk(kc::launch_split_scatter(p.words, c.bufA.p, c.bufB.p, (kc::SplitItem*)c.items.p, dstate,
+                                    p.max_items, (kc::SplitBin*)c.bins.p,
+                                    (unsigned long long*)c.cursor2.p, p.split_r, p.merge_cshift,
+                                    ncls, p.max_leaves, st),
+           "split scatter launch");
+  }
   if (p.merge_cshift)
     hipchk(kc::launch_leaf_ends((kc::Leaf*)c.leaves.p, (unsigned long long*)c.cursor2.p, dstate,
                                 p.max_leaves, st),
@@ -997,6 +1004,10 @@ Pipe plain_pipe(uint64_t n_bytes, int k, int P, const kc_options& o) {
   const int cshift = p.keybits - p.sb;
   if (p.words == 1 && p.split_r == 16 && o.preagg == 1 && cshift <= 60) p.merge_cshift = cshift;
   pipe_bounds(p);
+  // (where the caller leaves the shapes to the library)
+  p.unsplit = o.mode == 0 && !p.merge_cshift && o.shard_bits <= 0 && o.leaf_target <= 0 &&
+              o.leaf_attempt <= 0 && o.table_slots_log2 <= 0 &&
+              kc::counts_unsplit(p.words, p.rec_bound, p.sb, p.max_leaves, p.slots_log2);
   return p;
 }
 
@@ -1099,23 +1110,27 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
   p.order = device_order(c, q, S, st);
   kc::DevState* dstate = (kc::DevState*)c.state.p;
 
-  tm.mark(ST_NONE);
-  hipchk(kc::launch_front(p.words, reads + off0, q.N, offsets, n_reads, off0, k,
-                          (uint64_t*)c.packed.p, (uint64_t*)c.valid.p, nchunks,
-                          pipeline_zeros(c, p, dstate), st),
-         "pack launch");
-  tm.mark(ST_PACK);
   PipeOut po{out_keys, out_counts, nullptr, cap, !oa};
   po.front = true;
   po.pub = h_dev ? (kc::DevState*)((char*)h_dev + kInfoBytes) : nullptr;
-  enqueue_pipeline(c, p, dstate, tm, po, st);
   q.concat_leaves = p.max_leaves;
   kc::DevState ds;  // host sync 2 of 2 (3 with an output allocator)
-  if (po.pub) {
-    hipchk(hipStreamSynchronize(st), "hipStreamSynchronize");
-    std::memcpy(&ds, (const char*)h + kInfoBytes, sizeof(ds));
-  } else {
-    ds = read_state(c, st);
+  for (;;) {
+    tm.mark(ST_NONE);
+    hipchk(kc::launch_front(p.words, reads + off0, q.N, offsets, n_reads, off0, k,
+                            (uint64_t*)c.packed.p, (uint64_t*)c.valid.p, nchunks,
+                            pipeline_zeros(c, p, dstate), st),
+           "pack launch");
+    tm.mark(ST_PACK);
+    enqueue_pipeline(c, p, dstate, tm, po, st);
+    if (po.pub) {
+      hipchk(hipStreamSynchronize(st), "hipStreamSynchronize");
+      std::memcpy(&ds, (const char*)h + kInfoBytes, sizeof(ds));
+    } else {
+      ds = read_state(c, st);
+    }
+    if (!ds.overflow || !p.unsplit) break;
+    p.unsplit = false;  // a shard of very many distinct keys: again, split
   }
   S.n_levels = 1;
   S.n_leaves = ds.n_leaves;
