@@ -161,7 +161,7 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
 // Whether an input of one-word keys is small enough to be counted without a
 // split: every shard a leaf (launch_plan_shards lists them in leaves, nullptr
 // elsewhere), whatever its records, counted with the larger table. On average a
-// shard then holds a quarter of that table's slots at most; where one still has
+// shard then holds an eighth of that table's slots at most; where one still has
 // more distinct keys than the table, st->overflow is set and the caller counts
 // again with a split.
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,

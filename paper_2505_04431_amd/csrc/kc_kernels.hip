@@ -3173,10 +3173,16 @@ static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode
          (1 << slots_log2) == kLeafCmax64;
 }
 
+// (The line: 1,024 bytes a shard, so that the fullest shard of an AT-rich genome,
+// 10% of the windows, overflows only where nearly all of them are distinct, which
+// costs a second pipeline: 100 kB of random reads of 80% AT 83 against 101 us with
+// a split, but 500 kB of them 860 against 600. Random reads of A and T alone, 100
+// kB, 400 against 147 us. Not for wider keys: their table of 4,096 slots fills
+// slowly, 100 kB of 80% AT at k = 55 1,030 against 122 us.)
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
                     int slots_log2) {
   return tiny_leaves(words, max_leaves, slots_log2, 0, false, false) &&
-         rec_bound <= (uint64_t)kRescueCmax64 / 4 << shard_bits;
+         rec_bound <= (uint64_t)kRescueCmax64 / 8 << shard_bits;
 }
 
 // Which leaves go where (see classify_leaves).
