@@ -1598,6 +1598,15 @@ __device__ __forceinline__ uint32_t slot_hash(uint64_t key, int bits) {
   return (f ^ (f >> 15)) * 0x2C1B3C6Du >> (32 - bits);
 }
 
+// Wider keys' tables: probes after which a lane gives its leaf up as overflowed,
+// where the leaf has records enough for that (chains of a table below its limit
+// are far shorter), and it looks every 64 probes whether another lane has. A
+// batch may hold as many new keys as the table has slots, and each of its lanes
+// probed a full table round: 100 overflowing leaves among 30,000 (10 kbp reads, k =
+// 55) took the launch from 0.9 to 1.7 ms, so 1.1; those of 1,000,000 reads at k =
+// 100 3.9 -> 2.7 ms.
+constexpr uint32_t kMaxProbesW = 512;
+
 // Workgroup-scope flag in LDS (a volatile LDS variable would be accessed with
 // flat instructions that also wait for all outstanding global memory operations).
 __device__ __forceinline__ uint32_t ovf_get(uint32_t* f) {
@@ -2009,6 +2018,7 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
     __syncthreads();
     const uint32_t limit = Cn - (Cn >> 3);
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
+    const uint32_t max_probes = track ? min(Cn, kMaxProbesW) : Cn;
     for (uint64_t base = lf.begin; base < lf.end; base += (uint64_t)TB * R) {
       if (ovf_get(&s_ovf)) break;
       u128 kb[R];
@@ -2046,7 +2056,7 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
             // the bound only guards against a hang; giving up marks the leaf
             // overflowed, so it is counted again
             wait = ++spins <= (1u << 22);
-            if (!wait) probes = Cn;
+            if (!wait) probes = max_probes;
           } else if (w[0] == klo) {
             __hip_atomic_fetch_add(&tc[pos], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             hit = true;
@@ -2062,7 +2072,7 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
           if (todo) take(nx);
         } else if (!wait) {
           pos = (pos + 1) & cmask;
-          todo = ++probes < Cn;
+          todo = ++probes < max_probes && ((probes & 63) != 0 || !ovf_get(&s_ovf));
           if (!todo) ovf_set(&s_ovf);
         }
       }
@@ -2191,6 +2201,7 @@ __device__ __forceinline__ void leaf_countw_body(
     __syncthreads();
     const uint32_t limit = Cn - (Cn >> 3);
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
+    const uint32_t max_probes = track ? min(Cn, kMaxProbesW) : Cn;
     for (uint64_t base = 0; base < n; base += (uint64_t)TB * R) {
       if (ovf_get(&s_ovf)) break;
       K kb[R];
@@ -2218,8 +2229,9 @@ __device__ __forceinline__ void leaf_countw_body(
           todo = prev != EMPTY && (uint32_t)(prev >> kIdxBits) != tag[j];
           if (todo) {
             pos[j] = (pos[j] + 1) & cmask;
-            if (++probes[j] >= Cn) {
+            if (++probes[j] >= max_probes || ((probes[j] & 63) == 0 && ovf_get(&s_ovf))) {
               ovf_set(&s_ovf);  // table full: the leaf overflows
+              probes[j] = Cn;
               todo = false;
             }
           }
@@ -2241,7 +2253,10 @@ __device__ __forceinline__ void leaf_countw_body(
           bool todo = true;
           while (todo) {
             pos[j] = (pos[j] + 1) & cmask;
-            if (++probes[j] >= Cn) break;
+            if (++probes[j] >= max_probes || ((probes[j] & 63) == 0 && ovf_get(&s_ovf))) {
+              probes[j] = Cn;
+              break;
+            }
             const unsigned long long prev =
                 atomicCAS(&slot[pos[j]], EMPTY, (unsigned long long)tag[j] << kIdxBits | r);
             fresh = prev == EMPTY;
