@@ -158,12 +158,11 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
                               unsigned long long* subhist, uint64_t max_items, DevState* st,
                               Leaf* leaves, hipStream_t s);
 
-// Whether an input of one-word keys is small enough to be counted without a
-// split: every shard a leaf (launch_plan_shards lists them in leaves, nullptr
-// elsewhere), whatever its records, counted with the larger table. On average a
-// shard then holds an eighth of that table's slots at most; where one still has
-// more distinct keys than the table, st->overflow is set and the caller counts
-// again with a split.
+// Whether an input is small enough to be counted without a split: every shard a
+// leaf (launch_plan_shards lists them in leaves, nullptr elsewhere), whatever its
+// records. On average a shard then holds an eighth of the larger table's slots at
+// most; where one still has more distinct keys than that table, st->overflow is
+// set and the caller counts again with a split.
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
                     int slots_log2);
 
@@ -233,7 +232,7 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
                              uint32_t* d_out, int slots_log2, const uint32_t* large_list,
                              uint32_t* ovf_list, hipStream_t s, int mode, bool refine,
-                             bool merged);
+                             bool merged, bool unsplit);
 // Second count of the leaves launch_leaf_large listed in ovf_list, with a
 // table twice as large (one 1,024-thread workgroup per CU); only what
 // overflows that table too stays marked overflowed (launch_plan_out raises

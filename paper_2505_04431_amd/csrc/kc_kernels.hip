@@ -3188,16 +3188,21 @@ static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode
          (1 << slots_log2) == kLeafCmax64;
 }
 
-// (The line: 1,024 bytes a shard, so that the fullest shard of an AT-rich genome,
-// 10% of the windows, overflows only where nearly all of them are distinct, which
-// costs a second pipeline: 100 kB of random reads of 80% AT 83 against 101 us with
-// a split, but 500 kB of them 860 against 600. Random reads of A and T alone, 100
-// kB, 400 against 147 us. Not for wider keys: their table of 4,096 slots fills
-// slowly, 100 kB of 80% AT at k = 55 1,030 against 122 us.)
+// (The line: an eighth of the larger table, 1,024 bytes a shard for one-word keys
+// and 512 for wider ones, so that the fullest shard of an AT-rich genome, 5 to 10%
+// of the windows, overflows only where nearly all of them are distinct, which
+// costs a second pipeline. 100 kB of random reads with and without a split: at k =
+// 31 84 against 67 us, k = 55 90 against 71, k = 100 87 against 73; of 80% AT 106
+// against 78, 138 against 191 and 141 against 122; of A and T alone 145 against
+// 405, 516 against 662 and 280 against 581. 500 kB of 80% AT at k = 31: 600 against
+// 860.)
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
                     int slots_log2) {
-  return tiny_leaves(words, max_leaves, slots_log2, 0, false, false) &&
-         rec_bound <= (uint64_t)kRescueCmax64 / 8 << shard_bits;
+  if (words == 1)
+    return tiny_leaves(words, max_leaves, slots_log2, 0, false, false) &&
+           rec_bound <= (uint64_t)kRescueCmax64 / 8 << shard_bits;
+  return max_leaves <= kFewLeaves && slots_log2 == max_leaf_slots_log2(words) &&
+         rec_bound <= (uint64_t)kRescueCmaxW / 8 << shard_bits;
 }
 
 // Which leaves go where (see classify_leaves).
@@ -3349,7 +3354,7 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
                              const Leaf* leaves, DevState* st, uint64_t max_leaves,
                              uint32_t* d_out, int slots_log2, const uint32_t* large_list,
                              uint32_t* ovf_list, hipStream_t s, int mode, bool refine,
-                             bool merged) {
+                             bool merged, bool unsplit) {
   const bool wide = words == 2;
   // (max_leaves is a bound, two to four times the leaves: fewer workgroups for
   // inputs of few, or most start only to end, in the way of other streams' work)
@@ -3374,7 +3379,8 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
   uint32_t* const second = slots_log2 < second_slots_log2(words) ? ovf_list : nullptr;
   // few leaves: from the leaf table, but for those planned for the second count
   const bool direct = max_leaves <= kFewLeaves;
-  const uint64_t small_max = second ? 8ull << slots_log2 : ~0ull;  // (without a list)
+  // (unsplit: none is planned for it)
+  const uint64_t small_max = second && !unsplit ? 8ull << slots_log2 : ~0ull;  // (without a list)
   const uint32_t* const list = direct ? nullptr : large_list;
   if (tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged)) {
     hipLaunchKernelGGL((k_leaf_count64<kRescueTB, kRescueCmax64, 4, true, false>), dim3(glarge),

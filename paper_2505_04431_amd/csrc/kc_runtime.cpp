@@ -646,7 +646,7 @@ void refine_overflowed(Ctx& c, Call& q, kc_stats& S, Timer& tm, uint64_t nl0,
     hipchk(kc::launch_leaf_large(q.words, q.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                  (kc::Leaf*)c.aleaves.p, dst_state, na, (uint32_t*)c.adcnt.p,
                                  q.slots_log2, (uint32_t*)c.alarge.p, (uint32_t*)c.aovfl.p, st,
-                                 q.o.mode, true, q.merged),
+                                 q.o.mode, true, q.merged, false),
            "leaf count launch");
     hipchk(kc::launch_leaf_second(q.words, q.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                   (kc::Leaf*)c.aleaves.p, dst_state, na, (uint32_t*)c.adcnt.p,
@@ -908,7 +908,7 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
   hipchk(kc::launch_leaf_large(p.words, p.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                (kc::Leaf*)c.leaves.p, dstate, p.max_leaves, (uint32_t*)c.dcnt.p,
                                p.slots_log2, (uint32_t*)c.large.p, (uint32_t*)c.ovfl.p, st,
-                               p.mode, false, p.merge_cshift != 0),
+                               p.mode, false, p.merge_cshift != 0, p.unsplit),
          "leaf count launch");
   tm.mark(ST_LEAF);
   hipchk(kc::launch_leaf_second(p.words, p.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
