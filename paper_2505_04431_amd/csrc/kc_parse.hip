@@ -419,7 +419,8 @@ __device__ __forceinline__ void store_bytes(uint8_t* p, unsigned __int128 v, uin
 // per-round prefixes of the tile's chunks come from one block scan each, the
 // four rounds packed in 16-bit fields (a round holds at most 4096 bytes).
 // Nothing is written unless the outputs have room for all of it and the text
-// can be of the format; out_offsets[records] is written by the last block.
+// can be of the format by its first byte and its number of lines;
+// out_offsets[records] is written by the last block.
 __global__ void __launch_bounds__(kTB) k_fx_write(const uint8_t* __restrict__ B, Info* info,
                                                   const ull* __restrict__ t_nl,
                                                   const ull* __restrict__ t_hd,
@@ -440,7 +441,9 @@ __global__ void __launch_bounds__(kTB) k_fx_write(const uint8_t* __restrict__ B,
   const ull lines = g_nl[ng] + 1, keep_all = g_keep[ng];
   const ull records = fasta ? g_hd[ng] : lines / 4;
   const bool fits = (fasta ? info->first == '>' : lines % 4 == 0) && records <= max_records;
-  const bool store = fits && keep_all <= reads_capacity && (out_reads || !keep_all);
+  // (a FASTQ text that starts otherwise is refused; its layout check names line 0)
+  const bool store = fits && (fasta || info->first == '@') && keep_all <= reads_capacity &&
+                     (out_reads || !keep_all);
   if (!fits) return;
   if (store && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out_offsets[records] = keep_all;
   const uint64_t tile0 = (uint64_t)blockIdx.x * kTile;
