@@ -166,7 +166,10 @@ __global__ void __launch_bounds__(kScanTB) k_scan_tiles(unsigned long long* __re
 // ballots (the kept pairs of earlier lanes, then the lane's own earlier ones):
 // one exchange between the waves per tile instead of two barriers per row
 // (36M pairs of one word, 18% kept: 145 -> 110 us, bound by the keys of kept
-// pairs, which touch four of five 64-byte segments).
+// pairs, which touch four of five 64-byte segments). Wider keys are copied word
+// by word from the wave's list of kept places, consecutive lanes consecutive
+// words (a lane that copies its four pairs' keys itself stores 8 bytes 64 or
+// 128 apart: 20M pairs all kept, two words 372 -> 188 us, four words 674 -> 310).
 template <int W>
 __global__ void __launch_bounds__(kTB) k_keep_write(const uint64_t* __restrict__ keys,
                                                     const uint32_t* __restrict__ counts,
@@ -203,6 +206,18 @@ __global__ void __launch_bounds__(kTB) k_keep_write(const uint64_t* __restrict__
       keep[j] |= (k ? 1u : 0u) << q;
     }
   }
+  // places of the wave's kept pairs, in their order
+  constexpr int PER_WAVE = kTile / (kTB / 64);
+  __shared__ uint16_t s_pos[W > 1 ? kTile : 1];
+  if constexpr (W > 1) {
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+      uint32_t r = w * PER_WAVE + rank[j];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (keep[j] >> q & 1) s_pos[r++] = (uint16_t)(j * 256 + lane * 4 + q);
+    }
+  }
   if (lane == 0) wsum[w] = sum;
   __syncthreads();
   unsigned long long at = tsum[blockIdx.x];
@@ -213,11 +228,25 @@ __global__ void __launch_bounds__(kTB) k_keep_write(const uint64_t* __restrict__
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       if (!(keep[j] >> q & 1)) continue;
-      const uint64_t i = base + (uint64_t)j * 256 + lane * 4 + q;
       out_counts[o] = c[j][q];
-#pragma unroll
-      for (int x = 0; x < W; ++x) out_keys[W * o + x] = keys[W * i + x];
+      if constexpr (W == 1) out_keys[o] = keys[base + (uint64_t)j * 256 + lane * 4 + q];
       ++o;
+    }
+  }
+  if constexpr (W > 1) {
+    constexpr uint32_t U = 4;
+    const uint64_t* const src = keys + W * base;
+    uint64_t* const dst = out_keys + W * at;
+    for (uint32_t t0 = lane; t0 < W * sum; t0 += 64 * U) {
+      uint64_t x[U];
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u) {
+        const uint32_t t = t0 + u * 64;
+        if (t < W * sum) x[u] = src[W * s_pos[w * PER_WAVE + t / W] + t % W];
+      }
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+        if (t0 + u * 64 < W * sum) dst[t0 + u * 64] = x[u];
     }
   }
 }
