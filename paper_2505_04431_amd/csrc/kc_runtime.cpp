@@ -953,8 +953,13 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   // 1,000,000 reads at k = 31 / 21: 2.76 / 2.71 ms per call against 3.05 /
   // 3.00 ms at three quarters of a table, no overflow; the per-leaf work of
   // clearing, compacting and sorting the table is spread over more records).
-  // Two-word keys: one table (60 MB of 10 kbp reads at k = 55: 2.32 ms per call
-  // against 2.40 at three quarters and 2.69 at 1.25 tables). Four-word keys,
+  // Two-word keys: 27/32 of a table, so that inputs whose windows are nearly all
+  // distinct fit it too (a leaf of that mean is 1.5 standard deviations below
+  // the 7/8 at which its table gives up). At one whole table every leaf above 7/8
+  // of one was counted twice there: 100 MB of random reads at k = 33 / 55 5.84 /
+  // 4.28 ms against 4.81 / 3.64, 4 MB 508 / 431 us against 447 / 378; reads that
+  // cover their genome 20 times pay 0 to 5% for it (100 MB of 150 bp reads at k =
+  // 55 1.95 against 2.04 ms, 60 MB of 10 kbp reads 1.90 against 1.93). Four-word keys,
   // mostly distinct: three quarters (1,000,000 reads at k = 100: 6.4 ms
   // against 7.3 at one table). The sort-based leaves (mode 1) sort
   // all their records in LDS, so they keep three quarters of a table too
@@ -962,7 +967,7 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   const bool big = words == 1 && o.mode != 1;
   T = o.leaf_target > 0 ? (uint64_t)o.leaf_target
       : big                ? (C * 3) / 2
-      : words == 2 && o.mode != 1 ? C
+      : words == 2 && o.mode != 1 ? (C * 27) / 32
                            : (C * 3) / 4;
   H = o.leaf_attempt > 0 ? (uint64_t)o.leaf_attempt : (C * 7) / 8;
 }
