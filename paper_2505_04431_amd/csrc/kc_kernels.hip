@@ -1890,8 +1890,14 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
         }
       }
       if (track) {
-        for (int off = 32; off > 0; off >>= 1) claims += __shfl_xor(claims, off);
-        if ((threadIdx.x & 63) == 0 && claims && atomicAdd(&s_nd, claims) + claims >= limit)
+        // (summed by ballots of its bits: shuffles, six LDS operations in a chain,
+        // made inputs of few distinct keys 4% slower, 10 MB of A 14.0 -> 14.6
+        // ms; so 13.7, and 20,000,000 reads at k = 31 41.1 -> 40.7)
+        uint32_t fresh = 0;
+#pragma unroll
+        for (int b = 0; (1 << b) <= R; ++b)
+          fresh += (uint32_t)__popcll(__ballot(claims >> b & 1)) << b;
+        if ((threadIdx.x & 63) == 0 && fresh && atomicAdd(&s_nd, fresh) + fresh >= limit)
           ovf_set(&s_ovf);
       }
     }
