@@ -168,39 +168,52 @@ __device__ __forceinline__ uint32_t last_start(uint32_t nlm, int r) {
 struct Info {
   uint64_t lo, hi;      // the text without line ends at its ends, positions in B
   uint32_t fasta, first;  // format taken; the first byte
-  uint32_t missing;     // 1, 2: nothing but line ends in the first, last kPeek bytes
-  uint32_t pad;
+  uint32_t missing;     // 1, 2: nothing but line ends in the first, last kPeekMost bytes
+  uint32_t tail;        // line ends after the last byte, if not missing
   ull newlines, headers, keep, err;  // err: first malformed FASTQ line, ~0 if none
 };
 
-constexpr uint64_t kPeek = 4096;
+// How far from its ends the device looks for a text's first and last byte, and
+// the bytes it looks at in a step: a round of memory latency each, 1.1 ms for 1
+// MiB of line ends. The host then goes on from there, a copy and a wait for
+// each kPeek bytes, 5.2 ms a MiB. (With 4 KiB looked at here, 5,000 line ends
+// before a text of 143 us cost 256 us: the passes were launched for nothing, then
+// the host looked further, then they were launched again. Now they cost nothing.)
+constexpr uint64_t kPeek = 4096, kPeekMost = 1 << 20;
 
 // One block: [lo, hi), the first byte and the format, if the first and last
-// kPeek bytes each hold a byte that is not CR/LF (else the host looks further).
+// kPeekMost bytes each hold a byte that is not CR/LF (else the host looks further).
 __global__ void __launch_bounds__(kTB) k_fx_ends(const uint8_t* __restrict__ text, uint64_t n,
                                                  uint64_t a0, int format, Info* info) {
-  __shared__ uint32_t s_head, s_tail;
-  if (threadIdx.x == 0) {
-    s_head = ~0u;
-    s_tail = 0;
-  }
+  __shared__ uint32_t s_head, s_tail;  // bytes before the first, after the last; ~0: none yet
+  if (threadIdx.x == 0) s_head = s_tail = ~0u;
   __syncthreads();
-  const uint32_t nh = (uint32_t)(n < kPeek ? n : kPeek);
-  uint32_t head = ~0u, tail = 0;
-  for (uint32_t i = threadIdx.x; i < nh; i += kTB) {
-    const uint8_t x = text[i], y = text[n - nh + i];
-    if (x != '\n' && x != '\r' && head == ~0u) head = i;
-    if (y != '\n' && y != '\r') tail = i + 1;
+  const uint32_t most = (uint32_t)(n < kPeekMost ? n : kPeekMost);
+  bool need_head = true, need_tail = true;
+  for (uint32_t c = 0; c < most && (need_head || need_tail); c += (uint32_t)kPeek) {
+    uint32_t head = ~0u, tail = ~0u;
+#pragma unroll
+    for (uint32_t j = 0; j < kPeek / kTB; ++j) {
+      const uint32_t i = c + j * kTB + threadIdx.x;
+      if (i >= most) break;
+      const uint8_t x = text[i], y = text[n - 1 - i];
+      if (x != '\n' && x != '\r' && head == ~0u) head = i;
+      if (y != '\n' && y != '\r' && tail == ~0u) tail = i;
+    }
+    if (need_head && head != ~0u) atomicMin(&s_head, head);
+    if (need_tail && tail != ~0u) atomicMin(&s_tail, tail);
+    __syncthreads();
+    need_head = s_head == ~0u;
+    need_tail = s_tail == ~0u;
+    __syncthreads();  // all have read them before the next step writes
   }
-  if (head != ~0u) atomicMin(&s_head, head);
-  if (tail) atomicMax(&s_tail, tail);
-  __syncthreads();
   if (threadIdx.x != 0) return;
   Info r = {};
-  r.missing = n > nh ? (s_head == ~0u ? 1u : 0u) | (s_tail == 0 ? 2u : 0u) : 0u;
-  const uint64_t s0 = s_head == ~0u ? n : s_head;
+  r.missing = n > most ? (need_head ? 1u : 0u) | (need_tail ? 2u : 0u) : 0u;
+  const uint64_t s0 = need_head ? n : s_head;
   r.lo = a0 + s0;
-  r.hi = s_tail == 0 ? r.lo : a0 + n - nh + s_tail;
+  r.tail = s_tail;
+  r.hi = need_tail ? r.lo : a0 + n - s_tail;
   if (r.missing) r.hi = r.lo;  // the passes that follow see no text
   r.first = s0 < n ? text[s0] : 0;
   r.fasta = format == KC_FASTA || (format == KC_FASTX_AUTO && r.first == '>');
@@ -718,9 +731,12 @@ extern "C" int kc_parse_fastx(const uint8_t* text, uint64_t n_bytes, int format,
     hipLaunchKernelGGL(k_fx_ends, dim3(1), dim3(kTB), 0, st, text, n_bytes, a, format, info);
     passes();
     if (pub->missing) {
-      // more than kPeek line ends at an end of the text: the host looks past them
-      const uint64_t s0 = trim(text, 0, n_bytes, 1, st);
-      const uint64_t e0 = s0 < n_bytes ? trim(text, s0, n_bytes, -1, st) : s0;
+      // more than kPeekMost line ends at an end of the text: the host looks past them
+      // (with the first byte among the last kPeekMost, the last one is too)
+      const uint64_t s0 = pub->missing & 1 ? trim(text, kPeekMost, n_bytes, 1, st) : pub->lo - a;
+      const uint64_t e0 = s0 >= n_bytes           ? s0
+                          : pub->missing & 2 ? trim(text, s0, n_bytes - kPeekMost, -1, st)
+                                             : n_bytes - pub->tail;
       if (s0 < e0) {
         Info in = *pub;
         in.lo = a + s0;
