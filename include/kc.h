@@ -97,7 +97,8 @@ typedef struct kc_stats {
   uint64_t valid_windows;  /* W: valid windows (= sum of the output counts) */
   uint64_t distinct;       /* D: distinct canonical keys (= *n_out) */
   uint64_t n_leaves;       /* leaf partitions counted */
-  uint64_t n_levels;       /* partitioning levels below the shard level */
+  uint64_t n_levels;       /* partitioning levels below the shard level (0: a small input
+                              whose shards were counted whole) */
   uint64_t n_overflow;     /* leaf attempts that overflowed their table and were split
                               (after a second count with a table twice
                               as large also overflowed) */

@@ -3211,7 +3211,8 @@ static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode
 // 31 84 against 67 us, k = 55 90 against 71, k = 100 87 against 73; of 80% AT 106
 // against 78, 138 against 191 and 141 against 122; of A and T alone 145 against
 // 405, 516 against 662 and 280 against 581. 500 kB of 80% AT at k = 31: 600 against
-// 860.)
+// 860. One-word keys of more than 256 shards, P > 256, are always split: the bound
+// of their leaves that the host has is past kTinyLeaves.)
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
                     int slots_log2) {
   if (words == 1)

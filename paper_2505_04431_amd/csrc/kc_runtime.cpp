@@ -1137,7 +1137,7 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
     if (!ds.overflow || !p.unsplit) break;
     p.unsplit = false;  // a shard of very many distinct keys: again, split
   }
-  S.n_levels = 1;
+  S.n_levels = p.unsplit ? 0 : 1;
   S.n_leaves = ds.n_leaves;
   // the block-wide leaf kernel's own launch (refinement launches are counted apart)
   S.large_records = ds.large_records;
