@@ -119,7 +119,9 @@ typedef struct kc_stats {
                                5 small-leaf count (with leaf classification), 6 large-leaf
                                count, 7 output offsets, 8 concat, 9 self-check, 10 refinement
                                of overflowed leaves (its splits and part counts), 11 second
-                               count of the leaves whose table overflowed */
+                               count of the leaves whose table overflowed. A small input
+                               whose shards are split after one of them overflowed has both
+                               counts of its leaves in 5 to 8 */
 } kc_stats;
 
 /* Count canonical k-mers (plain form).

@@ -49,3 +49,18 @@ def test_overflowing_shard_is_split(k):
     assert s["n_levels"] >= 1, s
     assert_same(got, oracle.count(r, o, k), "k %d" % k)
     assert s["valid_windows"] == int(got[1].sum())
+
+
+@pytest.mark.parametrize("k", [21, 31, 64, 100])
+def test_overflowing_shard_keeps_its_records(k):
+    # the input is packed and its histogram taken once, as when it is split at once
+    # (shard_bits = 8 gives the same shards)
+    r, o = _reads(262_000 if k <= 32 else 131_000, b"AT", 3)
+    best = {}
+    for name, opts in (("after", dict(timing=1)), ("at once", dict(timing=1, shard_bits=8))):
+        best[name] = 1e9
+        for _ in range(15):
+            gpu_count(r, o, k, **opts)
+            t = kc.last_stats()["ms_stage"]
+            best[name] = min(best[name], sum(t[s] for s in ("pack", "window_hist")))
+    assert best["after"] < 1.5 * best["at once"], best
