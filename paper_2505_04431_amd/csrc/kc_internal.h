@@ -241,7 +241,7 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
 hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                               const Leaf* leaves, DevState* st, uint64_t max_leaves,
                               uint32_t* d_out, int slots_log2, const uint32_t* ovf_list,
-                              hipStream_t s, int mode, bool refine, bool merged);
+                              hipStream_t s, int mode, bool refine, bool merged, bool unsplit);
 uint64_t small_leaf_max(int words);
 
 // Exclusive scan of leaf counts into output offsets; st->D = total. bsum

@@ -1598,14 +1598,15 @@ __device__ __forceinline__ uint32_t slot_hash(uint64_t key, int bits) {
   return (f ^ (f >> 15)) * 0x2C1B3C6Du >> (32 - bits);
 }
 
-// Wider keys' tables: probes after which a lane gives its leaf up as overflowed,
-// where the leaf has records enough for that (chains of a table below its limit
-// are far shorter), and it looks every 64 probes whether another lane has. A
-// batch may hold as many new keys as the table has slots, and each of its lanes
-// probed a full table round: 100 overflowing leaves among 30,000 (10 kbp reads, k =
-// 55) took the launch from 0.9 to 1.7 ms, so 1.1; those of 1,000,000 reads at k =
-// 100 3.9 -> 2.7 ms.
-constexpr uint32_t kMaxProbesW = 512;
+// Probes after which a lane gives its leaf up as overflowed, where the leaf has
+// records enough for that (chains of a table below its limit are far shorter), and
+// it looks every 64 probes whether another lane has. A batch may hold as many new
+// keys as the table has slots, and each of its lanes probed a full table round, or
+// 512 slots whatever the others had found: 100 overflowing leaves among 30,000
+// (10 kbp reads, k = 55) took the launch from 0.9 to 1.7 ms, so 1.1; those of
+// 1,000,000 reads at k = 100 3.9 -> 2.7 ms; one-word keys, 20 MB of A and T at k =
+// 31 4.4 -> 3.0 ms, 4 MB of random reads at k = 32 537 -> 389 us.
+constexpr uint32_t kMaxProbes = 512;  // a multiple of 64, as table sizes are
 
 // Workgroup-scope flag in LDS (a volatile LDS variable would be accessed with
 // flat instructions that also wait for all outstanding global memory operations).
@@ -1833,7 +1834,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
     // new keys are counted per wave and batch, not one by one (a shared counter
     // takes its lanes one after the other), so a batch may fill the table past
     // its limit: a probe chain that only such a table has ends the attempt
-    const uint32_t max_probes = track ? min(Cn, 512u) : Cn;
+    const uint32_t max_probes = track ? min(Cn, kMaxProbes) : Cn;
     // records are loaded R per thread before inserting, so that the loads of a
     // batch are in flight together instead of one round trip per insert. The
     // probe loop has a single exit flag (always-CAS: a CAS on a slot holding
@@ -1885,8 +1886,11 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
           if (todo) take(nx);
         } else {
           pos = (pos + 1) & cmask;
-          todo = ++probes < max_probes;
-          if (!todo) ovf_set(&s_ovf);  // table full: the leaf overflows
+          if ((++probes & 63) == 0) {
+            // table full: the leaf overflows (or does already)
+            todo = probes < max_probes && !ovf_get(&s_ovf);
+            if (!todo) ovf_set(&s_ovf);
+          }
         }
       }
       if (track) {
@@ -2024,7 +2028,7 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
     __syncthreads();
     const uint32_t limit = Cn - (Cn >> 3);
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
-    const uint32_t max_probes = track ? min(Cn, kMaxProbesW) : Cn;
+    const uint32_t max_probes = track ? min(Cn, kMaxProbes) : Cn;
     for (uint64_t base = lf.begin; base < lf.end; base += (uint64_t)TB * R) {
       if (ovf_get(&s_ovf)) break;
       u128 kb[R];
@@ -2207,7 +2211,7 @@ __device__ __forceinline__ void leaf_countw_body(
     __syncthreads();
     const uint32_t limit = Cn - (Cn >> 3);
     const bool track = n >= limit;  // fewer records than the limit cannot overflow
-    const uint32_t max_probes = track ? min(Cn, kMaxProbesW) : Cn;
+    const uint32_t max_probes = track ? min(Cn, kMaxProbes) : Cn;
     // What a slot held before it was claimed for x. The second count looks first
     // (a slot claimed once never changes) in leaves of many records to a slot, so
     // of few keys: lanes that CAS one word take turns, but read it at once (10 MB
@@ -3193,26 +3197,27 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
   return hipGetLastError();
 }
 
-// Inputs of one-word keys with up to kTinyLeaves leaves: the second count's table
-// for all of them from the start. There is a CU for each, or nearly, so a
-// workgroup that fills one takes no longer (13.0 against 12.7 us for 667 reads),
-// and the second launch, mostly with nothing to do, goes (4 to 5 us).
+// Inputs of one-word keys with up to kTinyLeaves leaves, and of wider keys where
+// nothing is split: the second count's table for all of them from the start. There is a CU for each, or nearly, so a workgroup that fills one
+// takes no longer (13.0 against 12.7 us for 667 reads), and the second launch,
+// mostly with nothing to do, goes (4 to 5 us), as does the first try of a leaf that
+// needs the larger table (100 kB of 80% AT at k = 55 181 -> 127 us, k = 100 129 -> 96).
 constexpr uint64_t kTinyLeaves = 3 * kRescueGrid;
 static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode, bool refine,
-                        bool merged) {
-  return words == 1 && mode != 1 && !refine && !merged && max_leaves <= kTinyLeaves &&
-         (1 << slots_log2) == kLeafCmax64;
+                        bool merged, bool unsplit = false) {
+  return (words == 1 || unsplit) && mode != 1 && !refine && !merged && max_leaves <= kTinyLeaves &&
+         slots_log2 == max_leaf_slots_log2(words);
 }
 
 // (The line: an eighth of the larger table, 1,024 bytes a shard for one-word keys
 // and 512 for wider ones, so that the fullest shard of an AT-rich genome, 5 to 10%
 // of the windows, overflows only where nearly all of them are distinct, which
-// costs a second pipeline. 100 kB of random reads with and without a split: at k =
-// 31 84 against 67 us, k = 55 90 against 71, k = 100 87 against 73; of 80% AT 106
-// against 78, 138 against 191 and 141 against 122; of A and T alone 145 against
-// 405, 516 against 662 and 280 against 581. 500 kB of 80% AT at k = 31: 600 against
-// 860. One-word keys of more than 256 shards, P > 256, are always split: the bound
-// of their leaves that the host has is past kTinyLeaves.)
+// costs the leaf kernel twice. 100 kB of random reads with and without a split: at
+// k = 31 77 against 67 us, k = 55 81 against 69, k = 100 83 against 72; of 80% AT 99
+// against 77, 128 against 140 and 130 against 90; of A and T alone, which overflow,
+// 137 against 255, 261 against 345 and 269 against 413. One-word keys of more than
+// 256 shards, P > 256, are always split: the bound of their leaves that the host has
+// is past kTinyLeaves.)
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
                     int slots_log2) {
   if (words == 1)
@@ -3399,12 +3404,17 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
   // (unsplit: none is planned for it)
   const uint64_t small_max = second && !unsplit ? 8ull << slots_log2 : ~0ull;  // (without a list)
   const uint32_t* const list = direct ? nullptr : large_list;
-  if (tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged)) {
-    hipLaunchKernelGGL((k_leaf_count64<kRescueTB, kRescueCmax64, 4, true, false>), dim3(glarge),
-                       dim3(kRescueTB), 0, s, keybits, (uint64_t*)bufA, (uint64_t*)bufB, tmp_cnt,
-                       leaves, st, d_out, slots_log2 + 1, (const uint32_t*)nullptr,
-                       (const unsigned long long*)nullptr, (uint32_t*)nullptr,
-                       &st->large_records, ~0ull);
+  if (tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged, unsplit)) {
+#define KC_TINY(KRN, KT, ...)                                                                     \
+  hipLaunchKernelGGL((KRN<kRescueTB, __VA_ARGS__>), dim3(glarge), dim3(kRescueTB), 0, s, keybits,  \
+                     (KT*)bufA, (KT*)bufB, tmp_cnt, leaves, st, d_out, slots_log2 + 1,            \
+                     (const uint32_t*)nullptr, (const unsigned long long*)nullptr,                \
+                     (uint32_t*)nullptr, &st->large_records, ~0ull)
+    if (words == 4) KC_TINY(k_leaf_countw256, u256, kRescueCmaxW, 1, true);
+    else if (wide && keybits <= 126) KC_TINY(k_leaf_count128, u128, kRescueCmaxW, 2, true);
+    else if (wide) KC_TINY(k_leaf_countw128, u128, kRescueCmaxW, 2, true);
+    else KC_TINY(k_leaf_count64, uint64_t, kRescueCmax64, 4, true, false);
+#undef KC_TINY
     return hipGetLastError();
   }
 #define KC_LARGEW(KRN, KT, CM, R, FF)                                                             \
@@ -3440,9 +3450,9 @@ hipError_t launch_leaf_large(int words, int keybits, void* bufA, void* bufB, uin
 hipError_t launch_leaf_second(int words, int keybits, void* bufA, void* bufB, uint32_t* tmp_cnt,
                               const Leaf* leaves, DevState* st, uint64_t max_leaves,
                               uint32_t* d_out, int slots_log2, const uint32_t* ovf_list,
-                              hipStream_t s, int mode, bool refine, bool merged) {
+                              hipStream_t s, int mode, bool refine, bool merged, bool unsplit) {
   if (mode == 1 || slots_log2 >= second_slots_log2(words) || !ovf_list ||
-      tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged))
+      tiny_leaves(words, max_leaves, slots_log2, mode, refine, merged, unsplit))
     return hipSuccess;
   // the leaves whose table overflowed are counted again at once by a
   // workgroup per CU with a table twice as large (a leaf overflows because of

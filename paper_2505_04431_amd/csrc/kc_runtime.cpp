@@ -651,7 +651,7 @@ void refine_overflowed(Ctx& c, Call& q, kc_stats& S, Timer& tm, uint64_t nl0,
     hipchk(kc::launch_leaf_second(q.words, q.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                   (kc::Leaf*)c.aleaves.p, dst_state, na, (uint32_t*)c.adcnt.p,
                                   q.slots_log2, (uint32_t*)c.aovfl.p, st, q.o.mode, true,
-                                  q.merged),
+                                  q.merged, false),
            "leaf count launch");
     tm.mark(ST_REFINE);
     uint32_t* hd = (uint32_t*)host_stage(c, na * 4 + 64);
@@ -918,7 +918,7 @@ void enqueue_pipeline(Ctx& c, const Pipe& p, kc::DevState* dstate, Timer& tm, co
   hipchk(kc::launch_leaf_second(p.words, p.keybits, c.bufA.p, c.bufB.p, (uint32_t*)c.tmpcnt.p,
                                 (kc::Leaf*)c.leaves.p, dstate, p.max_leaves, (uint32_t*)c.dcnt.p,
                                 p.slots_log2, (uint32_t*)c.ovfl.p, st, p.mode, false,
-                                p.merge_cshift != 0),
+                                p.merge_cshift != 0, p.unsplit),
          "leaf count launch");
   tm.mark(ST_LEAF_SECOND);
   // few leaves: the concat finds the output offsets itself
@@ -1144,7 +1144,7 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
     // records are where they were (a leaf's pairs go to the other buffer), as are
     // the histogram and the split's counters, which nothing has touched since they
     // were cleared; only the state starts anew. (From the input on: 10 to 40
-    // us more, 100 kB of 80% AT at k = 21 410 against 380.)
+    // us more, 250 kB of 80% AT at k = 21 400 against 380.)
     p.unsplit = false;
     po.sharded = true;
     tm.mark(ST_NONE);
