@@ -995,12 +995,14 @@ Pipe plain_pipe(uint64_t n_bytes, int k, int P, const kc_options& o) {
   uint64_t C = 0;
   table_params(o, p.words, p.slots_log2, C, p.T, p.H);
   p.sb = shard_bits_for(o, P, n_bytes, p.T, p.keybits);
-  // two-word keys of larger inputs: one more shard bit shortens the split's runs
-  // more than it lengthens the owner scatter's (k = 55, 150 MB of 150 bp reads
-  // 4.12 against 4.17 ms, 60 MB of 10 kbp reads 2.19 against 2.21; below, the
-  // plans of twice the shards cost more: 4 MB 225 against 211 us, 0.1 MB 108
-  // against 97)
-  if (p.words == 2 && o.shard_bits <= 0 && n_bytes >= (48u << 20))
+  // two-word keys: a ninth shard bit where a shard of eight would be split into
+  // more than 256 leaves, 113 MB at the automatic target (the split's runs are then
+  // 16 records and fewer; below, the plans and the owner scatter of twice the
+  // shards cost more). 9 against 8 bits at k = 55, 10 kbp reads: 4 MB 253 against
+  // 241 us, 16 MB 598 against 589, 60 MB 1.92 against 1.90 ms, 100 MB 3.15 both, 130
+  // MB 4.11 against 4.14, 200 MB 6.44 against 6.59; 150 bp reads: 60 MB 1.32 against
+  // 1.29, 112 MB 2.30 against 2.28, 150 MB 3.01 against 3.02, 300 MB 6.16 against 6.29)
+  if (p.words == 2 && o.shard_bits <= 0 && n_bytes > p.T << 16)
     p.sb = std::min(std::max(p.sb, 9), kc::max_shard_bits());
   p.byte_begin = 0;
   p.byte_end = n_bytes;
