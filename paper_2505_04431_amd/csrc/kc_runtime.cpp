@@ -1288,15 +1288,28 @@ struct kc_batch {
 
 namespace {
 
+// Whether a class of keys of 2k + set_bits bits, sb shard bits, is counted with
+// one-word records: up to 64 bits, or cut to 64 where the shard holds the rest
+// (kc::BatchSets). If it is with set_bits, it is with fewer.
+bool one_word_class(int k, int set_bits, int sb) {
+  return 2 * k + set_bits <= 64 || (set_bits <= sb && 2 * k + set_bits - sb <= 64);
+}
+
+// Shard bits of a class of set_bits at least, by the options or automatically.
+int class_shard_bits(const kc_options& o, int set_bits) {
+  return o.shard_bits > 0 ? std::min(o.shard_bits, kc::max_shard_bits())
+                          : std::min(kc::max_shard_bits(), set_bits + 3);
+}
+
 // Device bytes of one batch pipeline over `bytes` bytes of sets of one k with
-// up to `n_sets` sets in a class (keys widen to two words when the set id
-// bits and 2k pass 64 bits).
+// up to `n_sets` sets in a class.
 uint64_t class_pipe_bytes(uint64_t bytes, int k, uint64_t n_sets, const kc_options& o) {
   if (bytes == 0) return 0;
   Pipe p;
   p.k = k;
-  p.keybits = 2 * k + ceil_log2(std::max<uint64_t>(n_sets, 1));
-  p.words = p.keybits > 64 ? 2 : 1;
+  const int set_bits = std::min(ceil_log2(std::max<uint64_t>(n_sets, 1)), kc::kMaxShardBits);
+  p.keybits = 2 * k + set_bits;
+  p.words = one_word_class(k, set_bits, class_shard_bits(o, set_bits)) ? 1 : 2;
   uint64_t C;
   table_params(o, p.words, p.slots_log2, C, p.T, p.H);
   p.sb = kc::max_shard_bits();
@@ -1465,9 +1478,9 @@ int batch_plan_impl(const uint64_t* host_set_reads, const uint64_t* host_set_byt
         uint64_t Cslots;
         p.words = words;
         table_params(b->o, words, p.slots_log2, Cslots, p.T, p.H);
-        p.sb = b->o.shard_bits > 0 ? std::min(b->o.shard_bits, kc::max_shard_bits())
-                                   : std::max(shard_bits_for(b->o, P, p.rec_bound, p.T, p.keybits),
-                                              std::min(kc::max_shard_bits(), C.set_bits + 3));
+        p.sb = class_shard_bits(b->o, C.set_bits);
+        if (b->o.shard_bits <= 0)
+          p.sb = std::max(p.sb, shard_bits_for(b->o, P, p.rec_bound, p.T, p.keybits));
         p.sb = std::max(1, std::min(p.sb, p.keybits));
       };
       plan(1);
@@ -1476,7 +1489,7 @@ int batch_plan_impl(const uint64_t* host_set_reads, const uint64_t* host_set_byt
         // of two-word ones through every step (48 sets, 24 of them of k = 31:
         // 3.29 -> 2.36 ms, of it the owner scatter 560 -> 285 us, the split 611 ->
         // 357, the leaves 635 -> 300)
-        p.cut = b->o.mode == 0 && C.set_bits <= p.sb && p.keybits - p.sb <= 64;
+        p.cut = one_word_class(C.k, C.set_bits, p.sb);
         if (!p.cut) plan(2);
       }
       p.byte_begin = lo & ~31ull;
