@@ -361,9 +361,10 @@ void kc_pred_free(kc_predictor* pred);
  *   if a sum exceeds 2^32-1. Lets inputs larger than device memory be counted
  *   in pieces whose results are merged. Synchronous on stream.
  * The temporaries of kc_spectrum (8 bytes a bin), kc_merge_counts (24 bytes per
- * 1,792 pairs of na + nb, or fewer of wider keys) and kc_filter_min_count sit in
- * one device buffer per host thread, part of the thread's scratch arena: it grows stream-ordered from the library pool as
- * needed and is kept between calls (kc_release_scratch frees it).
+ * 1,792 pairs of na + nb, 1,280 of two-word keys, 768 of four-word keys) and
+ * kc_filter_min_count (8 bytes per 4,096 pairs) sit in one device buffer per host
+ * thread, part of the thread's scratch arena: it grows stream-ordered from the
+ * library pool as needed and is kept between calls (kc_release_scratch frees it).
  * All return KC_OK, KC_E_INVAL, KC_E_NOMEM or KC_E_DEVICE (and as stated). */
 int kc_spectrum(const uint32_t* counts, uint64_t n, uint32_t max_count, uint64_t* host_hist,
                 void* stream);
@@ -440,8 +441,8 @@ uint64_t kc_max_outputs(const uint64_t* host_offsets, uint64_t n_reads, int k);
  * or KC_E_INVAL if out is NULL. */
 int kc_last_stats(kc_stats* out);
 
-/* Release this thread's scratch arena and the temporary buffer of
- * kc_merge_counts / kc_filter_min_count, and return the idle blocks of the
+/* Release this thread's scratch arena and the temporary buffer of kc_merge_counts,
+ * kc_filter_min_count, kc_spectrum and kc_parse_fastx, and return the idle blocks of the
  * library's device memory pool (the arenas of kc_count grow stream-ordered
  * from that pool, which keeps freed blocks for reuse instead of handing them
  * back to the driver at once) to the device. */

@@ -89,9 +89,9 @@ int count_in_block(WorkerArena* wa, void* block, uint64_t block_bytes, Slab* spi
                    const kc_options* opt, hipStream_t st, const OutAlloc& oa, uint64_t* n_out,
                    kc_stats* stats, std::string* err);
 
-// Device temporaries of the merge, the filter, the spectrum and the parser: a buffer of the calling
-// thread's context on the current device, grown stream-ordered on st from the
-// library pool and kept between calls (the callers are synchronous, so the
+// Device temporaries of the merge, the filter, the spectrum and the parser: a
+// buffer of the calling thread's context on the current device, grown
+// stream-ordered on st from the library pool and kept between calls (the callers are synchronous, so the
 // buffer is idle when a call starts). Returns nullptr on failure, with the
 // error message in *err and its status in *code.
 void* thread_scratch(size_t bytes, hipStream_t st, std::string* err, int* code) noexcept;

@@ -1,20 +1,28 @@
 // Device kernels of the canonical k-mer counting path for gfx950 (CDNA4).
 //
 // Path (one call):
-//   pack           ASCII -> 2-bit bases (32 per uint64, base i at bits 2i) plus
-//                  two bit masks: invalid byte, last byte of a read.
-//   window_hist    every valid window -> canonical key -> histogram over the
-//                  first-level key-range shards (top bits of the key).
-//   window_scatter every valid window -> its shard's slice of the owner-major
-//                  record buffer (each owner's shards are contiguous: the
-//                  owner's receive buffer), staged in LDS so that each shard
-//                  gets one coalesced run per tile.
-//   split_hist /   partitions too large for one LDS table are split by the next
-//   split_scatter  key bits (MSD radix step) into sub-partitions.
-//   leaf_count     one workgroup per leaf partition: open-addressing hash table
-//                  in LDS (linear probing, CAS claim of an EMPTY slot, atomic
-//                  add of the count), overflow detection, compaction, bitonic
-//                  sort of the distinct keys -> sorted (key, count) pairs.
+//   front          ASCII -> 2-bit bases (32 per uint64, base i at bits 2i) and one
+//                  bit per byte: whether the window that starts there is valid (k
+//                  bases of one read). A batch, packed once for several k, does so
+//                  in steps: pack and read_ends (masks of invalid bytes and of
+//                  reads' last bytes), valid_mask for each k.
+//   window_hist    every valid window -> its shard's count: the first-level
+//                  key-range shards are the top bits of the canonical key.
+//   plan_shards    where each shard's slice lies and how it is split.
+//   window_scatter every valid window -> its canonical key in its shard's slice of
+//                  the owner-major record buffer (each owner's shards are
+//                  contiguous: the owner's receive buffer), staged in LDS so that
+//                  each shard gets one coalesced run per tile.
+//   split_hist /   shards too large for one LDS table are split by the next key
+//   plan_leaves /  bits (MSD radix step) into leaves. Small inputs are not: every
+//   split_scatter  shard is a leaf.
+//   leaf_count     a leaf at a time: open-addressing hash table in LDS (linear
+//                  probing, CAS claim of an EMPTY slot, atomic add of the count),
+//                  overflow detection, compaction, then a counting sort of the
+//                  distinct keys and a rank within each of its groups (a bitonic
+//                  sort where a group is large) -> sorted (key, count) pairs.
+//                  Leaves that overflow get a second count with a table twice as
+//                  large; what overflows that is refined under host control.
 //   concat         leaves are disjoint key ranges, so concatenating their
 //                  sorted pairs in key-range order gives the sorted output.
 //   check          device self-check of the output.
@@ -46,23 +54,11 @@ __device__ __forceinline__ uint64_t rev2(uint64_t x) {
   return ((x >> 1) & 0x5555555555555555ull) | ((x & 0x5555555555555555ull) << 1);
 }
 
-// MurmurHash3 64-bit finalizer (Appleby): slot selection inside hash tables.
-__device__ __forceinline__ uint64_t fmix64(uint64_t h) {
-  h ^= h >> 33;
-  h *= 0xff51afd7ed558ccdull;
-  h ^= h >> 33;
-  h *= 0xc4ceb9fe1a85ec53ull;
-  h ^= h >> 33;
-  return h;
-}
-
 template <typename K> struct Key;
 
 template <> struct Key<uint64_t> {
   static constexpr bool kWide = false;
   static constexpr int kWords = 1;
-  __device__ static uint64_t empty() { return ~0ull; }
-  __device__ static uint64_t hash(uint64_t x) { return fmix64(x); }
   __device__ static uint32_t bits(uint64_t x, int shift, int nbits) {
     return (uint32_t)(x >> shift) & ((1u << nbits) - 1u);
   }
@@ -95,10 +91,6 @@ template <> struct Key<unsigned long long> : Key<uint64_t> {};
 template <> struct Key<u128> {
   static constexpr bool kWide = true;
   static constexpr int kWords = 2;
-  __device__ static u128 empty() { return ~(u128)0; }
-  __device__ static uint64_t hash(u128 x) {
-    return fmix64((uint64_t)x ^ fmix64((uint64_t)(x >> 64) + 0x9E3779B97F4A7C15ull));
-  }
   __device__ static uint32_t bits(u128 x, int shift, int nbits) {
     return (uint32_t)(x >> shift) & ((1u << nbits) - 1u);
   }
@@ -188,7 +180,6 @@ __device__ __forceinline__ u128 low_bits128(int bits) {
 // Keys of more than 64 bases: built from five packed words (up to 128 bases
 // starting anywhere in the first word).
 template <> struct Key<u256> {
-  static constexpr bool kWide = true;
   static constexpr int kWords = 4;
   __device__ static u256 mask(int k) {
     const int b = 2 * k;
@@ -196,12 +187,6 @@ template <> struct Key<u256> {
   }
   __device__ static uint32_t bits(const u256& x, int shift, int nbits) {
     return (uint32_t)(x >> shift) & ((1u << nbits) - 1u);
-  }
-  __device__ static uint64_t hash(const u256& x) {
-    uint64_t h = fmix64((uint64_t)(x.hi >> 64) + 0x9E3779B97F4A7C15ull);
-    h = fmix64((uint64_t)x.hi ^ h);
-    h = fmix64((uint64_t)(x.lo >> 64) ^ h);
-    return fmix64((uint64_t)x.lo ^ h);
   }
   // Bases [s/2, s/2 + k) of the little-endian base stream in p[0..4] (base j
   // of the window at bits 2j), s even, 0 <= s <= 62.
@@ -1633,7 +1618,8 @@ __device__ __forceinline__ uint32_t leaf_slots(uint64_t n, uint32_t cmax_rt) {
 // Epilogue shared by all key widths: the table has been filled with Cn slots;
 // table.load(s, ref, count) reads slot s (count 0: empty), table.bits(ref, shift,
 // nbits) gives key bits of what the slot refers to and table.key(ref) its key;
-// tk and tc, where the table may have been, then hold the distinct keys. These are grouped by a counting sort on the key bits
+// tk and tc, where the table may have been, then hold the distinct keys. These are
+// grouped by a counting sort on the key bits
 // just below the leaf's common prefix; each key then finds its place inside
 // its group by counting the smaller keys of the group, and the pair is written
 // to dst/tmp_cnt at [begin, begin + d) in key order. Keys of one group share a
@@ -1641,9 +1627,11 @@ __device__ __forceinline__ uint32_t leaf_slots(uint64_t n, uint32_t cmax_rt) {
 // copies of one k-mer), so groups are not always tiny; a group larger than
 // kRankMax switches the leaf to a bitonic sort. Cn >> GSHIFT groups: aux holds
 // 2 * Cn >> GSHIFT counters. Returns d.
-// (wider keys: groups of up to 1,024 are still ranked sooner
-// than a bitonic sort moves its 20 to 36 bytes a key: the large leaves of
-// 1,000,000 reads at k = 100, 12% repeats, 3.36 -> 2.84 ms)
+// (wider keys: groups of up to 1,024 are still ranked sooner than a bitonic sort
+// moves its 20 to 36 bytes a key: four words, the large leaves of 1,000,000 reads
+// at k = 100, 12% repeats, 3.36 -> 2.84 ms; two words, 20 MB of reads of a genome
+// of 40% repeats at k = 63 760 -> 691 us, 60 MB of it 1.80 -> 1.86 ms, and no
+// difference on inputs of fewer repeats)
 template <typename K> constexpr uint32_t kRankMax = sizeof(K) > 8 ? 1024 : 256;
 
 template <typename K, int TB, int PER, int GSHIFT, typename Table>
@@ -2957,6 +2945,8 @@ constexpr int kScatterS256 = 4, kScatterS128 = 4;
 constexpr int kScatterSCut = 8, kScatterTBCut = 512;
 // One-word keys of a batch: the same tiles (a batch's kernel keeps too many values
 // live for two workgroups of 1,024 threads a CU: 244 against 193 us in that batch).
+// Both hold for large sets: 1,024 threads took 12 sets of 3 to 10 Mbp from 21.4 to
+// 22.6 ms (k = 21), with cut keys from 17.6 to 18.7 (k = 32).
 constexpr int kScatterTBBatch64 = 512;
 inline int scatter_threads(int words, bool batch, bool cut, int starts) {
   return cut          ? kScatterTBCut
@@ -3320,7 +3310,7 @@ hipError_t launch_split_scatter(int words, const void* src, void* dst, const Spl
 }
 
 uint64_t small_leaf_max(int words) {
-  // n + n/7 + 1 <= slots of the one-wave kernel (256-bit keys: sort-based only)
+  // n + n/7 + 1 <= slots of the one-wave kernel (none for four-word keys)
   return words == 4 ? 0 : words == 2 ? 447 : 895;
 }
 

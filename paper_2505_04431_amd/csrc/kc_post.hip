@@ -394,7 +394,6 @@ __device__ __forceinline__ bool operator<(const Key4& a, const Key4& b) {
 __device__ __forceinline__ bool operator==(const Key4& a, const Key4& b) {
   return a.hi == b.hi && a.lo == b.lo;
 }
-__device__ __forceinline__ bool operator!=(const Key4& a, const Key4& b) { return !(a == b); }
 
 template <int W> struct KeyOf { typedef unsigned __int128 type; };
 template <> struct KeyOf<4> { typedef Key4 type; };

@@ -101,7 +101,7 @@ struct Ctx {
   DevBuf large, ovfl, bsum, itemoff;
   // overflow refinement: overflowed leaves, part attempts, the spliced list
   DevBuf rlist, rleaves, rcount, aleaves, adcnt, alarge, aovfl, rparts, rcnt, leaves2, dcnt2;
-  DevBuf post;  // temporaries of kc_merge_counts / kc_filter_min_count
+  DevBuf post;  // temporaries of the merge, filter, spectrum and parser
   std::vector<int> order_host;
   int order_P = -1, order_sb = -1;
   void* host = nullptr;  // pinned staging for small device<->host copies
@@ -1827,13 +1827,13 @@ hipError_t device_pool(int device, hipMemPool_t* pool) {
 void* thread_scratch(size_t bytes, hipStream_t st, std::string* err, int* code) noexcept {
   try {
     Ctx& c = context();
-    grow(c.post, bytes, "merge and filter temporaries", st);
+    grow(c.post, bytes, "merge, filter, spectrum or parse temporaries", st);
     return c.post.p;
   } catch (const Fail& f) {
     if (err) *err = g_err;
     if (code) *code = f.code;
   } catch (...) {
-    if (err) *err = "merge and filter temporaries: allocation failed";
+    if (err) *err = "merge, filter, spectrum or parse temporaries: allocation failed";
     if (code) *code = KC_E_NOMEM;
   }
   return nullptr;
