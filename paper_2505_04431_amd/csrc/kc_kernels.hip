@@ -1578,6 +1578,7 @@ __device__ __forceinline__ void bitonic_sort(K* keys, C* cnt, uint32_t n) {
 
 // Table slot of a 64-bit key: multiply-shift (Knuth) of a 32-bit fold of the
 // key; collisions are resolved by linear probing, so only speed depends on it.
+// (Multipliers: two 32-bit primes of Collet's xxHash, one of Wellons' hash search.)
 __device__ __forceinline__ uint32_t slot_hash(uint64_t key, int bits) {
   const uint32_t f = (uint32_t)key * 0x9E3779B1u + (uint32_t)(key >> 32) * 0x85EBCA77u;
   return (f ^ (f >> 15)) * 0x2C1B3C6Du >> (32 - bits);
@@ -1945,11 +1946,12 @@ template <typename K> struct Hash2 {
   uint32_t pos, tag;  // independent hashes of a key
   __device__ __forceinline__ explicit Hash2(const K& key) {
     // multilinear in the key's 32-bit words (Dietzfelbinger): two sums of
-    // words times odd constants, each finished by a multiply-shift
-    constexpr uint32_t c[16] = {0x9E3779B1u, 0x85EBCA77u, 0xC2B2AE3Du, 0x27D4EB2Fu,
-                                0x165667B1u, 0xD3A2646Du, 0xFD7046C5u, 0xB55A4F09u,
-                                0x8CB92BA7u, 0xE6546B65u, 0x9C8F4D2Bu, 0x51ED2703u,
-                                0xA0761D65u, 0xE7037ED1u, 0x8EBC6AF1u, 0x589965CDu};
+    // words times odd constants, each finished by a multiply-shift. The constants
+    // are the first words of pi's binary fraction, made odd.
+    constexpr uint32_t c[16] = {0x243F6A89u, 0x85A308D3u, 0x13198A2Fu, 0x03707345u,
+                                0xA4093823u, 0x299F31D1u, 0x082EFA99u, 0xEC4E6C89u,
+                                0x452821E7u, 0x38D01377u, 0xBE5466CFu, 0x34E90C6Du,
+                                0xC0AC29B7u, 0xC97C50DDu, 0x3F84D5B5u, 0xB5470917u};
     uint32_t w[2 * Key<K>::kWords];
     __builtin_memcpy(w, &key, sizeof(K));
     uint32_t a = 0, b = 0;
@@ -1958,8 +1960,8 @@ template <typename K> struct Hash2 {
       a += w[i] * c[i];
       b += (w[i] ^ (w[i] >> 16)) * c[8 + i];
     }
-    pos = (a ^ (a >> 15)) * 0x2C1B3C6Du;
-    tag = (b ^ (b >> 15)) * 0x846CA68Bu;
+    pos = (a ^ (a >> 15)) * 0x9216D5D9u;
+    tag = (b ^ (b >> 15)) * 0x8979FB1Bu;
   }
 };
 
