@@ -195,8 +195,7 @@ __global__ void __launch_bounds__(kTB) k_fx_ends(const uint8_t* __restrict__ tex
 #pragma unroll
     for (uint32_t j = 0; j < kPeek / kTB; ++j) {
       const uint32_t i = c + j * kTB + threadIdx.x;
-      if (i >= most) break;
-      const uint8_t x = text[i], y = text[n - 1 - i];
+      const uint8_t x = i < most ? text[i] : '\n', y = i < most ? text[n - 1 - i] : '\n';
       if (x != '\n' && x != '\r' && head == ~0u) head = i;
       if (y != '\n' && y != '\r' && tail == ~0u) tail = i;
     }
