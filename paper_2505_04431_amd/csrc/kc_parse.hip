@@ -174,7 +174,7 @@ struct Info {
 };
 
 // How far from its ends the device looks for a text's first and last byte, and
-// the bytes it looks at in a step: a round of memory latency each, 1.1 ms for 1
+// the bytes it looks at in a step: a round of memory latency each, 1.0 ms for 1
 // MiB of line ends. The host then goes on from there, a copy and a wait for
 // each kPeek bytes, 5.2 ms a MiB. (With 4 KiB looked at here, 5,000 line ends
 // before a text of 143 us cost 256 us: the passes were launched for nothing, then
