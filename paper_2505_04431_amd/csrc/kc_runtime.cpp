@@ -957,13 +957,13 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   // 1,000,000 reads at k = 31 / 21: 2.76 / 2.71 ms per call against 3.05 /
   // 3.00 ms at three quarters of a table, no overflow; the per-leaf work of
   // clearing, compacting and sorting the table is spread over more records).
-  // Two-word keys: 27/32 of a table, so that inputs whose windows are nearly all
-  // distinct fit it too (a leaf of that mean is 1.5 standard deviations below
-  // the 7/8 at which its table gives up). At one whole table every leaf above 7/8
-  // of one was counted twice there: 100 MB of random reads at k = 33 / 55 5.84 /
-  // 4.28 ms against 4.81 / 3.64, 4 MB 508 / 431 us against 447 / 378; reads that
-  // cover their genome 20 times pay 0 to 5% for it (100 MB of 150 bp reads at k =
-  // 55 1.95 against 2.04 ms, 60 MB of 10 kbp reads 1.90 against 1.93). Four-word keys,
+  // Two-word keys: 15/16 of a table. At a whole one, inputs whose windows are nearly
+  // all distinct had a fifth of their records, the leaves above the 7/8 at which a
+  // table gives up, counted twice, and were slower than at the three quarters from
+  // before (random reads, 120 MB at k = 64 6.06 against 6.52 ms, at 15/16 5.12; 4 MB
+  // 456 against 493 us, at 15/16 397); reads that cover their genome 20 times pay 1
+  // to 2% for it (38 MB of 150 bp reads at k = 33 918 against 936 us; at 27/32, where
+  // no leaf overflows, 956). Four-word keys,
   // mostly distinct: three quarters (1,000,000 reads at k = 100: 6.4 ms
   // against 7.3 at one table). The sort-based leaves (mode 1) sort
   // all their records in LDS, so they keep three quarters of a table too
@@ -971,7 +971,7 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   const bool big = words == 1 && o.mode != 1;
   T = o.leaf_target > 0 ? (uint64_t)o.leaf_target
       : big                ? (C * 3) / 2
-      : words == 2 && o.mode != 1 ? (C * 27) / 32
+      : words == 2 && o.mode != 1 ? (C * 15) / 16
                            : (C * 3) / 4;
   H = o.leaf_attempt > 0 ? (uint64_t)o.leaf_attempt : (C * 7) / 8;
 }
@@ -996,7 +996,7 @@ Pipe plain_pipe(uint64_t n_bytes, int k, int P, const kc_options& o) {
   table_params(o, p.words, p.slots_log2, C, p.T, p.H);
   p.sb = shard_bits_for(o, P, n_bytes, p.T, p.keybits);
   // two-word keys: a ninth shard bit where a shard of eight would be split into
-  // more than 256 leaves, 113 MB at the automatic target (the split's runs are then
+  // more than 256 leaves, 126 MB at the automatic target (the split's runs are then
   // 16 records and fewer; below, the plans and the owner scatter of twice the
   // shards cost more). 9 against 8 bits at k = 55, 10 kbp reads: 4 MB 253 against
   // 241 us, 16 MB 598 against 589, 60 MB 1.92 against 1.90 ms, 100 MB 3.15 both, 130

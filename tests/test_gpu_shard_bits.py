@@ -8,7 +8,7 @@ from gpu_util import assert_same, gpu_count
 
 pytestmark = pytest.mark.gpu
 
-LINE = 1728 << 16  # bytes: 256 leaves of the target in each of 256 shards
+LINE = 1920 << 16  # bytes: 256 leaves of the target in each of 256 shards
 
 
 @pytest.mark.parametrize("k", [40, 64])
