@@ -283,9 +283,8 @@ def batched_leg(n_sets: int, budget_gib: float, tune: bool) -> dict:
         del rt, ot, keys, cnts
         return info
 
-    # one plan per k (the sets are in k order), tuned on its own first wave:
-    # the best leaf size differs between one-word keys and the two-word keys
-    # of k = 31 classes
+    # one plan per k (the sets are in k order), tuned on its own first wave: the
+    # best options differ with k (a class's keys may be whole or cut to one word)
     groups = []
     lo = 0
     while lo < len(ks):
