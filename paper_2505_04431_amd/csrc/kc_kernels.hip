@@ -1843,7 +1843,7 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
       // the sum over the R records of the slowest lane's probes (records past
       // the leaf's end, EMPTY, come last)
       unsigned long long key = EMPTY;
-      uint32_t cnt = 1, pos = 0, probes = 0, claims = 0;
+      uint32_t cnt = 1, pos = 0, left = 64, rounds = 0, claims = 0;  // of 64 probes each
       int j = 0;
       auto take = [&](unsigned long long x) {
         key = x;
@@ -1856,7 +1856,8 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
           }
         }
         pos = slot_hash(key, slot_bits);
-        probes = 0;
+        left = 64;
+        rounds = 0;
       };
       bool todo = kb[0] != EMPTY;
       if (todo) take(kb[0]);
@@ -1875,9 +1876,10 @@ k_leaf_count64(int keybits, uint64_t* bufA, uint64_t* bufB,
           if (todo) take(nx);
         } else {
           pos = (pos + 1) & cmask;
-          if ((++probes & 63) == 0) {
+          if (--left == 0) {
             // table full: the leaf overflows (or does already)
-            todo = probes < max_probes && !ovf_get(&s_ovf);
+            left = 64;
+            todo = ++rounds < max_probes / 64 && !ovf_get(&s_ovf);
             if (!todo) ovf_set(&s_ovf);
           }
         }
