@@ -2031,12 +2031,13 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
       }
       // one probe loop over the thread's R records, as for one-word keys
       u128 key = 0;
-      uint32_t pos = 0, probes = 0, spins = 0;
+      uint32_t pos = 0, left = 64, rounds = 0, spins = 0;  // of 64 probes each
       int j = 0;
       const auto take = [&](const u128& x) {
         key = x;
         pos = Hash2<u128>(x).pos >> (32 - slot_bits);
-        probes = 0;
+        left = 64;
+        rounds = 0;
       };
       bool todo = (unsigned long long)(kb[0] >> 64) != ~0ull;
       if (todo) take(kb[0]);
@@ -2058,7 +2059,10 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
             // the bound only guards against a hang; giving up marks the leaf
             // overflowed, so it is counted again
             wait = ++spins <= (1u << 22);
-            if (!wait) probes = max_probes;
+            if (!wait) {
+              left = 1;
+              rounds = max_probes / 64;
+            }
           } else if (w[0] == klo) {
             __hip_atomic_fetch_add(&tc[pos], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             hit = true;
@@ -2074,8 +2078,11 @@ k_leaf_count128(int keybits, u128* bufA, u128* bufB, uint32_t* __restrict__ tmp_
           if (todo) take(nx);
         } else if (!wait) {
           pos = (pos + 1) & cmask;
-          todo = ++probes < max_probes && ((probes & 63) != 0 || !ovf_get(&s_ovf));
-          if (!todo) ovf_set(&s_ovf);
+          if (--left == 0) {
+            left = 64;
+            todo = ++rounds < max_probes / 64 && !ovf_get(&s_ovf);
+            if (!todo) ovf_set(&s_ovf);
+          }
         }
       }
     }
