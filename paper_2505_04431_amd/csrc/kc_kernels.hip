@@ -2248,7 +2248,7 @@ __device__ __forceinline__ void leaf_countw_body(
           todo = prev != EMPTY && (uint32_t)(prev >> kIdxBits) != tag[j];
           if (todo) {
             pos[j] = (pos[j] + 1) & cmask;
-            if (++probes[j] >= max_probes || ((probes[j] & 63) == 0 && ovf_get(&s_ovf))) {
+            if ((++probes[j] & 63) == 0 && (probes[j] >= max_probes || ovf_get(&s_ovf))) {
               ovf_set(&s_ovf);  // table full: the leaf overflows
               probes[j] = Cn;
               todo = false;
@@ -2272,7 +2272,7 @@ __device__ __forceinline__ void leaf_countw_body(
           bool todo = true;
           while (todo) {
             pos[j] = (pos[j] + 1) & cmask;
-            if (++probes[j] >= max_probes || ((probes[j] & 63) == 0 && ovf_get(&s_ovf))) {
+            if ((++probes[j] & 63) == 0 && (probes[j] >= max_probes || ovf_get(&s_ovf))) {
               probes[j] = Cn;
               break;
             }
