@@ -3214,9 +3214,9 @@ static bool tiny_leaves(int words, uint64_t max_leaves, int slots_log2, int mode
 // and 512 for wider ones, so that the fullest shard of an AT-rich genome, 5 to 10%
 // of the windows, overflows only where nearly all of them are distinct, which
 // costs the leaf kernel twice. 100 kB of random reads with and without a split: at
-// k = 31 77 against 67 us, k = 55 81 against 69, k = 100 83 against 72; of 80% AT 99
-// against 77, 128 against 140 and 130 against 90; of A and T alone, which overflow,
-// 137 against 255, 261 against 345 and 269 against 413. One-word keys of more than
+// k = 31 88 against 69 us, k = 55 89 against 71, k = 100 91 against 73; of 80% AT 110
+// against 79, 137 against 125 and 128 against 90; of A and T alone, which overflow,
+// 150 against 260, 515 against 588 and 232 against 353. One-word keys of more than
 // 256 shards, P > 256, are always split: the bound of their leaves that the host has
 // is past kTinyLeaves.)
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,

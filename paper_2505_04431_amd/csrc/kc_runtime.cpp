@@ -958,12 +958,13 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   // 3.00 ms at three quarters of a table, no overflow; the per-leaf work of
   // clearing, compacting and sorting the table is spread over more records).
   // Two-word keys: 15/16 of a table. At a whole one, inputs whose windows are nearly
-  // all distinct had a fifth of their records, the leaves above the 7/8 at which a
-  // table gives up, counted twice, and were slower than at the three quarters from
-  // before (random reads, 120 MB at k = 64 6.06 against 6.52 ms, at 15/16 5.12; 4 MB
-  // 456 against 493 us, at 15/16 397); reads that cover their genome 20 times pay 1
-  // to 2% for it (38 MB of 150 bp reads at k = 33 918 against 936 us; at 27/32, where
-  // no leaf overflows, 956). Four-word keys,
+  // all distinct have a fifth of their records counted twice, the leaves above the
+  // 7/8 at which a table gives up; at 27/32 none, but reads that cover their genome,
+  // which is what is mostly counted, have more leaves. At 1, 15/16 and 27/32: random
+  // reads, 120 MB at k = 64 5.28, 4.37 and 3.81 ms, 60 MB at k = 55 2.36, 2.19 and
+  // 2.03, 4 MB at k = 33 460, 446 and 417 us; 20-fold coverage, 38 MB of 150 bp reads
+  // at k = 33 925, 938 and 962 us, 100 MB at k = 55 1.94, 1.96 and 2.02 ms, 60 MB of
+  // 10 kbp reads 1.85, 1.85 and 1.89. Four-word keys,
   // mostly distinct: three quarters (1,000,000 reads at k = 100: 6.4 ms
   // against 7.3 at one table). The sort-based leaves (mode 1) sort
   // all their records in LDS, so they keep three quarters of a table too
@@ -998,10 +999,10 @@ Pipe plain_pipe(uint64_t n_bytes, int k, int P, const kc_options& o) {
   // two-word keys: a ninth shard bit where a shard of eight would be split into
   // more than 256 leaves, 126 MB at the automatic target (the split's runs are then
   // 16 records and fewer; below, the plans and the owner scatter of twice the
-  // shards cost more). 9 against 8 bits at k = 55, 10 kbp reads: 4 MB 253 against
-  // 241 us, 16 MB 598 against 589, 60 MB 1.92 against 1.90 ms, 100 MB 3.15 both, 130
-  // MB 4.11 against 4.14, 200 MB 6.44 against 6.59; 150 bp reads: 60 MB 1.32 against
-  // 1.29, 112 MB 2.30 against 2.28, 150 MB 3.01 against 3.02, 300 MB 6.16 against 6.29)
+  // shards cost more). 9 against 8 bits at k = 55, 10 kbp reads: 4 MB 254 against
+  // 248 us, 16 MB 583 against 575, 60 MB 1.88 against 1.86 ms, 112 MB 3.43 both, 150
+  // MB 4.65 against 4.69, 200 MB 6.31 against 6.45; 150 bp reads: 60 MB 1.29 against
+  // 1.28, 112 MB 2.24 against 2.22, 200 MB 3.87 both, 300 MB 6.05 against 6.17)
   if (p.words == 2 && o.shard_bits <= 0 && n_bytes > p.T << 16)
     p.sb = std::min(std::max(p.sb, 9), kc::max_shard_bits());
   p.byte_begin = 0;
@@ -1145,8 +1146,8 @@ int count_impl(const uint8_t* reads, const uint64_t* offsets, uint64_t n_reads, 
     // A shard of very many distinct keys: the shards are split after all. Their
     // records are where they were (a leaf's pairs go to the other buffer), as are
     // the histogram and the split's counters, which nothing has touched since they
-    // were cleared; only the state starts anew. (From the input on: 10 to 40
-    // us more, 250 kB of 80% AT at k = 21 400 against 380.)
+    // were cleared; only the state starts anew. (From the input on: about
+    // 20 us more, 250 kB of 80% AT at k = 21 400 against 380.)
     p.unsplit = false;
     po.sharded = true;
     tm.mark(ST_NONE);
