@@ -162,7 +162,7 @@ hipError_t launch_plan_shards(unsigned long long* hist, const int* order, int sh
 // leaf (launch_plan_shards lists them in leaves, nullptr elsewhere), whatever its
 // records. On average a shard then holds an eighth of the larger table's slots at
 // most; where one still has more distinct keys than that table, st->overflow is
-// set and the caller counts again with a split.
+// set and the caller splits the shards and counts the leaves of that.
 bool counts_unsplit(int words, uint64_t rec_bound, int shard_bits, uint64_t max_leaves,
                     int slots_log2);
 
@@ -217,7 +217,9 @@ hipError_t launch_leaf_ends(Leaf* leaves, const unsigned long long* cursor, cons
 // ovf_list (max_leaves entries, or nullptr): in mode 0 the leaves whose table
 // overflows are listed there, for launch_leaf_second.
 // With few leaves (max_leaves) none is small: all go to the block-wide kernel,
-// which then takes them from the leaf table, not from large_list.
+// which then takes them from the leaf table, not from large_list. unsplit: the
+// leaves are whole shards, which wider keys too then count with the larger table
+// at once (one-word keys do wherever the leaves are few), with no second count.
 // launch_leaf_small also classifies the leaves unless launch_plan_leaves has
 // (classified): large ones into large_list;
 // in mode 0 with ovf_list (and the second count running,

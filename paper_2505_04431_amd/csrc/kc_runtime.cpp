@@ -954,9 +954,10 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   C = 1ull << slots_log2;
   // default leaf size in records. One-word keys: 1.5 tables, so that a leaf
   // fits its table while at most 58% of its records are distinct (on
-  // 1,000,000 reads at k = 31 / 21: 2.76 / 2.71 ms per call against 3.05 /
-  // 3.00 ms at three quarters of a table, no overflow; the per-leaf work of
-  // clearing, compacting and sorting the table is spread over more records).
+  // 1,000,000 reads at k = 31 / 21: 1.94 / 1.93 ms per call against 2.01 / 1.99
+  // at one table and 2.09 / 2.11 at three quarters, no overflow; the per-leaf
+  // work of clearing, compacting and sorting the table is spread over more
+  // records; 40,000,000 reads at k = 31: 83.4 against 84.2 at three quarters).
   // Two-word keys: 15/16 of a table. At a whole one, inputs whose windows are nearly
   // all distinct have a fifth of their records counted twice, the leaves above the
   // 7/8 at which a table gives up; at 27/32 none, but reads that cover their genome,
@@ -964,9 +965,9 @@ void table_params(const kc_options& o, int words, int& slots_log2, uint64_t& C, 
   // reads, 120 MB at k = 64 5.28, 4.37 and 3.81 ms, 60 MB at k = 55 2.36, 2.19 and
   // 2.03, 4 MB at k = 33 460, 446 and 417 us; 20-fold coverage, 38 MB of 150 bp reads
   // at k = 33 925, 938 and 962 us, 100 MB at k = 55 1.94, 1.96 and 2.02 ms, 60 MB of
-  // 10 kbp reads 1.85, 1.85 and 1.89. Four-word keys,
-  // mostly distinct: three quarters (1,000,000 reads at k = 100: 6.4 ms
-  // against 7.3 at one table). The sort-based leaves (mode 1) sort
+  // 10 kbp reads 1.85, 1.85 and 1.89. Four-word keys: three quarters (1,000,000
+  // reads at k = 100: 4.80 ms, and 4.81 at one table, which mostly distinct keys
+  // would overflow as above). The sort-based leaves (mode 1) sort
   // all their records in LDS, so they keep three quarters of a table too
   // (1.5 tables: 39 ms against 12 ms on the 1,000,000 reads).
   const bool big = words == 1 && o.mode != 1;
